@@ -29,8 +29,8 @@
 //        merged as above while their sum is <= w* or the bin has no room to
 //        split its heavy walkers (sum_k max(1, ceil(w_k/(2w*))) > M, which
 //        includes n > M); the survivors are then replicated up to M as above.
-//        Up to 64 walkers a bin is held one walker per lane in registers and
-//        each merge takes two DPP wave minima.  Larger bins are sorted once
+//        Up to 256 walkers a bin is held in registers, up to four walkers per
+//        lane, and each merge takes two DPP wave minima.  Larger bins are sorted once
 //        by (weight, slot); merged walkers queue up in the order they are
 //        made, which is also non-decreasing in weight, so each merge only
 //        compares the heads of the two queues (ties of equal sums ordered by
@@ -573,69 +573,117 @@ __device__ void split_survivors(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
     }
 }
 
-// Weight-equalizing rule with at most 64 walkers: walker q lives in lane q.
-// The merges are merge_bin_lanes' (same pairs, draws and sums) under the
-// rule's condition; the survivors are then replicated as in split_bin_lanes
-// (merged-away lanes hold +inf and get no copy).
-template <class Idx>
+// Weight-equalizing rule with at most 64 K walkers: walker q lives in lane
+// q % 64, register q / 64.  The merges are merge_bin_lanes' (same pairs, draws
+// and sums) under the rule's condition; the survivors are then replicated by
+// the same hand-out as split_bin (the largest share, ties to the lowest slot:
+// the lowest register, then the lowest lane), merged-away ones holding +inf
+// and getting no copy.  Every step of a bin is a chain of wave reductions, so
+// what bounds it is their latency: in registers a merge takes two wave minima
+// (about a thousand cycles) where merge_bin's queues wait on several dependent
+// loads of the bin's arrays.  Ten futile-cycle runs of 101 bins x 100 walkers:
+// 428 -> 252 us per interval with bins of 65 to 256 walkers on this path.
+template <int K, class Idx>
 __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b,
                                    int32_t o0, const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1,
                                    int lane) {
     const double inf = __builtin_huge_val();
-    const bool own = lane < nb;
-    double wv = own ? wk.w[p0 + lane] : inf;
+    double wv[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) wv[k] = 64 * k + lane < nb ? wk.w[p0 + 64 * k + lane] : inf;
+    // the lowest slot whose entry of v equals w, given that there is one
+    auto lowest = [&](const double *v, double w) {
+        int32_t q = -1;
+#pragma unroll
+        for (int k = K - 1; k >= 0; --k) {
+            const unsigned long long m = __ballot(v[k] == w);
+            if (m) q = 64 * k + __ffsll((long long)m) - 1;
+        }
+        return q;
+    };
     double Wb = 0.0;                      // the bin's weight, in slot order
-    for (int32_t q = 0; q < nb; ++q) Wb = Wb + wk.w[p0 + q];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        for (int32_t l = 0; l < min(nb - 64 * k, 64); ++l) Wb = Wb + rs_readlane(wv[k], l);
     const bool eq = Wb > 0.0;
     const double ideal = Wb / (double)M;
     const double two_ideal = ideal + ideal;
-    int32_t need = eq ? wave_sum_i32(own ? need_copies(wv, two_ideal) : 0) : 0;
+    int32_t nl = 0;
+    if (eq) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) nl += 64 * k + lane < nb ? need_copies(wv[k], two_ideal) : 0;
+    }
+    int32_t need = wave_sum_i32(nl);
     int32_t n = nb;
     double ul = 0.0;
     for (int32_t m = 0; n > 1; ++m) {
-        const double wi = wave_min(wv);
-        const int qi = __ffsll((long long)__ballot(wv == wi)) - 1;
-        const double wrest = lane == qi ? inf : wv;
-        const double wj = wave_min(wrest);
-        const int qj = __ffsll((long long)__ballot(wrest == wj)) - 1;
+        double lm = wv[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) lm = fmin(lm, wv[k]);
+        const double wi = wave_min(lm);
+        const int32_t qi = lowest(wv, wi);
+        double wr[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) wr[k] = 64 * k + lane == qi ? inf : wv[k];
+        double lr = wr[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) lr = fmin(lr, wr[k]);
+        const double wj = wave_min(lr);
         const double sum = wi + wj;
         const bool go = eq ? (sum <= ideal || need > M) : (n > M);
         if (!go) break;
+        const int32_t qj = lowest(wr, wj);
         if ((m & 63) == 0) {   // the next 64 merge draws, one per lane
             const U4 rr = philox4x32_10((uint32_t)(m + lane), (uint32_t)b, iter, 1u, k0, k1);
             ul = uniform53(rr.x, rr.y);
         }
         const double u = rs_readlane(ul, m & 63);
         const double p_i = wi / sum;
-        const int keep = (u < p_i) ? qi : qj;
-        const int drop = (keep == qi) ? qj : qi;
+        const int32_t keep = (u < p_i) ? qi : qj;
+        const int32_t drop = (keep == qi) ? qj : qi;
         if (eq) need = need - need_copies(wi, two_ideal) - need_copies(wj, two_ideal) + need_copies(sum, two_ideal);
-        if (lane == keep) wv = sum;
-        if (lane == drop) wv = inf;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (64 * k + lane == keep) wv[k] = sum;
+            if (64 * k + lane == drop) wv[k] = inf;
+        }
         n -= 1;
     }
-    const bool live = own && wv != inf;
-    int32_t c = live ? 1 : 0;
-    double bs = live ? wv / 1.0 : -1.0;
-    for (int32_t e = n; e < M; ++e) {
-        const double mx = wave_max(bs);
-        const int wl = __ffsll((long long)__ballot(bs == mx)) - 1;
-        if (lane == wl) {
-            c += 1;
-            bs = wv / (double)c;
-        }
+    int32_t c[K];
+    double sh[K];                         // per-copy shares; -1: not a survivor
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool live = 64 * k + lane < nb && wv[k] != inf;
+        c[k] = live ? 1 : 0;
+        sh[k] = live ? wv[k] : -1.0;
     }
-    int32_t tot;
-    int32_t o = o0 + wave_excl_scan(c, lane, &tot);
-    if (live) {
-        const double share = wv / (double)c;
-        const int32_t k = wk.list[p0 + lane];
-        for (int32_t r = 0; r < c; ++r) {
-            out.orig[o] = k;
-            out.wn[o] = share;
-            out.obin[o] = b;
-            ++o;
+    for (int32_t e = n; e < M; ++e) {
+        double lm = sh[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) lm = fmax(lm, sh[k]);
+        const int32_t q = lowest(sh, wave_max(lm));
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (64 * k + lane == q) {
+                c[k] += 1;
+                sh[k] = wv[k] / (double)c[k];
+            }
+    }
+    int32_t o = o0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        int32_t tot;
+        int32_t ok = o + wave_excl_scan(c[k], lane, &tot);
+        if (c[k] > 0) {
+            const int32_t kk = wk.list[p0 + 64 * k + lane];
+            for (int32_t r = 0; r < c[k]; ++r) {
+                out.orig[ok] = kk;
+                out.wn[ok] = sh[k];
+                out.obin[ok] = b;
+                ++ok;
+            }
         }
+        o += tot;
     }
 }
 
@@ -764,15 +812,17 @@ __device__ void merge_bin(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_
 
 // One bin's split/merge (and its row of the reweighting flux matrix) on the
 // calling wave: the walkers at positions [p0, p0 + nb) of wk, the output at
-// slots [o0, o0 + M).
-template <class Idx>
+// slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).
+template <class Idx, int RULE>
 __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const BinOut &out, int32_t run, int32_t b,
                              int32_t nb, int32_t p0, int32_t o0, uint32_t iter, uint32_t k0, uint32_t k1,
                              bool rw_acc, int lane) {
     const int32_t NB = a.n_bins, M = a.m_targ;
     if (rw_acc) rw_flux_bin(a.rw_F + ((size_t)run * NB + b) * NB, wk, p0, nb, lane);
-    if (a.rs_rule == 1) {
-        if (nb <= 64) equalize_bin_lanes(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+    if (RULE < 0 ? a.rs_rule == 1 : RULE == 1) {
+        if (nb <= 64) equalize_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (RULE >= 0 && nb <= 128) equalize_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (RULE >= 0 && nb <= 256) equalize_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else merge_bin<Idx, true>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
     } else if (nb == M) {
         for (int32_t q = lane; q < nb; q += 64) {
@@ -803,12 +853,13 @@ __device__ __forceinline__ RunWork<int32_t> global_work(const SimArgs &a, size_t
     return wk;
 }
 
-// binfo != NULL (device arrays only, use_lds 0): stop after placement and
-// staging, and leave each bin's count, first position and first output slot
-// in binfo[run][3][n_bins] for we_resample_bins_kernel.
-template <class Idx>
+// LDS: the run's working arrays in LDS (Idx uint16), else in device memory
+// (Idx int32).  PLACE (device arrays only): stop after placement and staging,
+// and leave each bin's count, first position and first output slot in
+// binfo[run][3][n_bins] for we_resample_bins_kernel.
+template <class Idx, bool LDS, int RULE, bool PLACE>
 __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cur, double *__restrict__ w_nxt,
-                               int32_t use_lds, int32_t run, unsigned char *lds, int32_t *__restrict__ binfo) {
+                               int32_t run, unsigned char *lds, int32_t *__restrict__ binfo) {
     const int32_t tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, n_waves = nthr >> 6;
     const int32_t NB = a.n_bins, M = a.m_targ, cap = a.cap;
@@ -834,7 +885,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     const int32_t *sbin = a.s_bin + base;
     const int32_t *srec = a.s_rec + base;
     RunWork<Idx> wk;
-    if (use_lds) {
+    if constexpr (LDS) {
         wk.w = reinterpret_cast<double *>(tail);
         wk.list = reinterpret_cast<int32_t *>(wk.w + cap);
         wk.tag = reinterpret_cast<uint16_t *>(wk.list + cap);
@@ -1018,7 +1069,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     }
     __syncthreads();
 
-    if (binfo) {
+    if constexpr (PLACE) {
         // bin-parallel mode: leave the bins to we_resample_bins_kernel
         int32_t *bi = binfo + (size_t)run * 3 * NB;
         for (int32_t b = tid; b < NB; b += nthr) {
@@ -1040,29 +1091,30 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     for (int32_t b = wave; b < NB; b += n_waves) {
         const int32_t nb = uni(cnt[b]);
         if (nb == 0) continue;
-        resample_bin(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
+        resample_bin<Idx, RULE>(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
     }
     __syncthreads();
     if (tid == 0) a.n_walk[run] = ostart[NB];
 }
 
-__device__ __forceinline__ void resample_run(const SimArgs &a, const double *__restrict__ w_cur,
-                                             double *__restrict__ w_nxt, int32_t use_lds, int32_t run,
-                                             unsigned char *lds, int32_t *binfo = nullptr) {
-    if (use_lds) resample_run_t<uint16_t>(a, w_cur, w_nxt, 1, run, lds, nullptr);
-    else resample_run_t<int32_t>(a, w_cur, w_nxt, 0, run, lds, binfo);
-}
+// How a run's workgroup resamples: whole, with its working arrays in LDS or in
+// device memory, or placement only (bin-parallel mode).  One kernel per mode
+// and rule: with every path in one, the compiler called the split/merge
+// routines through a stack (784 B of scratch a lane) instead of inlining them.
+enum ResampleMode { RS_LDS, RS_GLOBAL, RS_PLACE };
 
+template <int MODE, int RULE>
 __global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a, const double *__restrict__ w_cur,
-                                                          double *__restrict__ w_nxt, int32_t use_lds,
-                                                          int32_t *__restrict__ binfo) {
+                                                          double *__restrict__ w_nxt, int32_t *__restrict__ binfo) {
     extern __shared__ __align__(16) unsigned char lds[];
-    resample_run(a, w_cur, w_nxt, use_lds, blockIdx.x, lds, binfo);
+    if constexpr (MODE == RS_LDS) resample_run_t<uint16_t, true, RULE, false>(a, w_cur, w_nxt, blockIdx.x, lds, nullptr);
+    else resample_run_t<int32_t, false, RULE, MODE == RS_PLACE>(a, w_cur, w_nxt, blockIdx.x, lds, binfo);
 }
 
 // Bin-parallel split/merge after we_resample_kernel's placement: grid
 // (ceil(n_bins / 4), runs), one wave per bin, the same per-bin steps on the
 // run's arrays in device memory; bins of one run write disjoint ranges.
+template <int RULE>
 __global__ __launch_bounds__(256) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
                                                                const int32_t *__restrict__ binfo) {
     const int lane = threadIdx.x & 63;
@@ -1080,8 +1132,8 @@ __global__ __launch_bounds__(256) void we_resample_bins_kernel(SimArgs a, double
     out.wn = w_nxt + base;
     const uint32_t iter = *a.iter_dev;
     const uint64_t seed = a.seeds[run];
-    resample_bin(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
-                 (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane);
+    resample_bin<int32_t, RULE>(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
+                                (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane);
 }
 
 // New state rows from their parents: one lane per copy number.
@@ -1177,7 +1229,8 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_resample_kernel(Bat
     const int32_t i = blockIdx.y;
     const SimArgs &a = b.args[i];
     if ((int32_t)blockIdx.x >= a.n_runs) return;
-    resample_run(a, b.w_cur[i], b.w_nxt[i], b.use_lds[i], blockIdx.x, lds);
+    if (b.use_lds[i]) resample_run_t<uint16_t, true, -1, false>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, nullptr);
+    else resample_run_t<int32_t, false, -1, false>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, nullptr);
 }
 
 // Grid-strided over each member's own cells: a grid sized for the largest
@@ -1275,16 +1328,23 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
     const bool split = binfo && resample_bins_parallel(a);
     const bool use_lds = !split && resample_uses_lds(a);
     const size_t shmem = resample_lds_bytes(a, use_lds);
-    hipLaunchKernelGGL(we_resample_kernel, dim3(a.n_runs), dim3(resample_threads(a.n_runs)), shmem, st, a, w_cur, w_nxt,
-                       use_lds ? 1 : 0, split ? binfo : nullptr);
+    const bool eq = a.rs_rule == 1;
+    const dim3 gr(a.n_runs), br(resample_threads(a.n_runs));
+    if (split) {
+        // the placement takes no rule
+        hipLaunchKernelGGL((we_resample_kernel<RS_PLACE, 0>), gr, br, shmem, st, a, w_cur, w_nxt, binfo);
+        const dim3 gb((unsigned)((a.n_bins + 3) / 4), (unsigned)a.n_runs);
+        if (eq) hipLaunchKernelGGL(we_resample_bins_kernel<1>, gb, dim3(256), 0, st, a, w_nxt, binfo);
+        else hipLaunchKernelGGL(we_resample_bins_kernel<0>, gb, dim3(256), 0, st, a, w_nxt, binfo);
+    } else if (use_lds) {
+        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+        else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+    } else {
+        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+        else hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (split) {
-        hipLaunchKernelGGL(we_resample_bins_kernel, dim3((unsigned)((a.n_bins + 3) / 4), (unsigned)a.n_runs), dim3(256),
-                           0, st, a, w_nxt, binfo);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
     const int64_t total = (int64_t)a.n_runs * a.cap * a.S;
     const int32_t narrow = total + 256 < ((int64_t)1 << 31) ? 1 : 0;
     hipLaunchKernelGGL(we_gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
