@@ -46,6 +46,19 @@
 
 #include <algorithm>
 
+namespace {
+// The descriptor table in the form D, as 16-byte words.
+template <class D>
+__device__ __forceinline__ const uint4 *wave_desc(const SimArgs &a) {
+    if constexpr (std::is_same<D, RxnDesc2>::value) return reinterpret_cast<const uint4 *>(a.desc2);
+    else return reinterpret_cast<const uint4 *>(a.desc);
+}
+
+// Ints of a walker's counts in LDS: the species and the 1 of an absent
+// reactant, in whole 16-byte words.
+int32_t wave_s_pad(const SimArgs &a) { return (a.S + 4) & ~3; }
+}  // namespace
+
 // LDS-table variant: the block copies the descriptor table (16 bytes per
 // reaction, 59 KB at 3680 reactions) into LDS once -- and, with HDR, the
 // reaction headers too (another 16 bytes per reaction) -- and its waves then
@@ -63,18 +76,18 @@
 // more register and the <false> variant drops to one block per CU (measured:
 // 132 VGPRs took 8 replicas of the 3680-reaction network from 1.41 to 2.14 ms
 // per launch).
-template <bool HDR>
+template <bool HDR, class D>
 __global__ __launch_bounds__(64 * WAVE_LDS_MAX_WAVES, 4) void ssa_wave_lds_kernel(SimArgs a, int32_t *__restrict__ xs,
                                                                                  int32_t s_pad) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int32_t R = a.R;
-    RxnDesc *ldesc = reinterpret_cast<RxnDesc *>(smem);
+    D *ldesc = reinterpret_cast<D *>(smem);
     RxnInfo *linfo = reinterpret_cast<RxnInfo *>(smem + 16 * (size_t)R);
     unsigned char *wbase = smem + (HDR ? 32 : 16) * (size_t)R;
     const int nw = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double *lchunk = reinterpret_cast<double *>(wbase) + wv * 64;
     int32_t *lx = reinterpret_cast<int32_t *>(wbase + (size_t)nw * 64 * sizeof(double)) + wv * s_pad;
-    const uint4 *gd = reinterpret_cast<const uint4 *>(a.desc);
+    const uint4 *gd = wave_desc<D>(a);
     const uint4 *gh = reinterpret_cast<const uint4 *>(a.rinfo);
     uint4 *sd = reinterpret_cast<uint4 *>(ldesc);
     uint4 *sh = reinterpret_cast<uint4 *>(linfo);
@@ -83,7 +96,7 @@ __global__ __launch_bounds__(64 * WAVE_LDS_MAX_WAVES, 4) void ssa_wave_lds_kerne
         if (HDR) sh[i] = gh[i];
     }
     __syncthreads();
-    LdsTables tab;
+    LdsTables<D> tab;
     tab.d = ldesc;
     tab.h = HDR ? linfo : a.rinfo;
     tab.ids = a.dep;
@@ -119,6 +132,7 @@ __global__ __launch_bounds__(64 * WAVE_LDS_MAX_WAVES, 4) void ssa_wave_lds_kerne
 // in the event loop reads global memory.
 #define WAVE_FACT_MAX_WAVES 16
 
+template <class D>
 __global__ __launch_bounds__(64 * WAVE_FACT_MAX_WAVES) void ssa_wave_fact_kernel(SimArgs a, int32_t *__restrict__ xs,
                                                                                 int32_t s_pad) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -131,7 +145,7 @@ __global__ __launch_bounds__(64 * WAVE_FACT_MAX_WAVES) void ssa_wave_fact_kernel
     const int nw = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double *lchunk = reinterpret_cast<double *>(wbase) + wv * 64;
     int32_t *lx = reinterpret_cast<int32_t *>(wbase + (size_t)nw * 64 * sizeof(double)) + wv * s_pad;
-    const uint4 *gd = reinterpret_cast<const uint4 *>(a.desc);
+    const uint4 *gd = wave_desc<D>(a);
     for (int32_t i = threadIdx.x; i < R; i += blockDim.x) {
         ld[i] = gd[i];
         lh[i] = a.fhdr[i];
@@ -157,7 +171,7 @@ __global__ __launch_bounds__(64 * WAVE_FACT_MAX_WAVES) void ssa_wave_fact_kernel
         if ((int32_t)o < seg.y) {
             const uint32_t g = (uint32_t)seg.x + o;
             const uint32_t run = g / cap;
-            wave_walker_fact(a, tab, xs, (int32_t)run, (int32_t)(g - run * cap), iter, lchunk, lx);
+            wave_walker_fact<D>(a, tab, xs, (int32_t)run, (int32_t)(g - run * cap), iter, lchunk, lx);
         }
         const uint32_t got = atomicAdd(&a.queue[0], lane == 0 ? 1u : 0u);
         q = gridDim.x * (uint32_t)nw + (uint32_t)__shfl((int)got, 0, 64);
@@ -168,13 +182,13 @@ bool wave_kernel_fits(int32_t S, int32_t R) { return R <= 4096 && S <= 8192; }
 
 namespace {
 // Blocks of an LDS variant that stay resident per CU, for a given LDS size.
-template <bool HDR>
+template <bool HDR, class D>
 int lds_blocks_per_cu(int waves, size_t shmem) {
     static size_t last_shmem = 0;
     static int last_waves = 0, last = 1;
     if (shmem != last_shmem || waves != last_waves) {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ssa_wave_lds_kernel<HDR>, 64 * waves, shmem) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ssa_wave_lds_kernel<HDR, D>, 64 * waves, shmem) !=
                 hipSuccess || nb < 1)
             nb = 1;
         last = nb;
@@ -195,14 +209,14 @@ int device_cus() {
     return n;
 }
 
-template <bool HDR>
+template <bool HDR, class D>
 hipError_t launch_lds(const SimArgs &a, int32_t *xs, int32_t s_pad, size_t tables, size_t per_wave, int64_t walkers,
                       hipStream_t st) {
     const int nw = (int)std::min<size_t>(WAVE_LDS_MAX_WAVES, (WAVE_LDS_BYTES - tables) / per_wave);
     const size_t shmem = tables + nw * per_wave;
-    const int64_t resident = (int64_t)lds_blocks_per_cu<HDR>(nw, shmem) * device_cus();
+    const int64_t resident = (int64_t)lds_blocks_per_cu<HDR, D>(nw, shmem) * device_cus();
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(resident, (walkers + nw - 1) / nw));
-    hipLaunchKernelGGL(ssa_wave_lds_kernel<HDR>, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
+    hipLaunchKernelGGL((ssa_wave_lds_kernel<HDR, D>), dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
     return hipGetLastError();
 }
 }  // namespace
@@ -219,17 +233,18 @@ hipError_t launch_lds(const SimArgs &a, int32_t *xs, int32_t s_pad, size_t table
 bool wave_fact_fits(const SimArgs &a, size_t *tables, size_t *per_wave) {
     if (!a.fhdr || !a.inc || !a.inc_tab) return false;
     *tables = fact_tables_bytes(a.R, a.S, a.n_inc);
-    *per_wave = 64 * sizeof(double) + sizeof(int32_t) * (size_t)((a.S + 3) & ~3);
+    *per_wave = 64 * sizeof(double) + sizeof(int32_t) * (size_t)wave_s_pad(a);
     return *tables + *per_wave <= WAVE_LDS_BYTES;
 }
 
 namespace {
-int fact_blocks_per_cu(int waves, size_t shmem) {
+template <class D>
+int fact_blocks_per_cu_t(int waves, size_t shmem) {
     static size_t last_shmem = 0;
     static int last_waves = 0, last = 1;
     if (shmem != last_shmem || waves != last_waves) {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ssa_wave_fact_kernel, 64 * waves, shmem) != hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, ssa_wave_fact_kernel<D>, 64 * waves, shmem) != hipSuccess ||
             nb < 1)
             nb = 1;
         last = nb;
@@ -237,6 +252,9 @@ int fact_blocks_per_cu(int waves, size_t shmem) {
         last_waves = waves;
     }
     return last;
+}
+int fact_blocks_per_cu(const SimArgs &a, int waves, size_t shmem) {
+    return a.desc2 ? fact_blocks_per_cu_t<RxnDesc2>(waves, shmem) : fact_blocks_per_cu_t<RxnDesc>(waves, shmem);
 }
 }  // namespace
 
@@ -257,7 +275,7 @@ int fact_choice(const SimArgs &a, size_t *shmem_out) {
     const int nw = (int)std::min<size_t>(WAVE_FACT_MAX_WAVES, (WAVE_LDS_BYTES - tables) / per_wave);
     const size_t shmem = tables + nw * per_wave;
     const int64_t live = ((int64_t)a.n_runs * a.cap + 1) / 2;
-    if (nw < 1 || live > (int64_t)fact_blocks_per_cu(nw, shmem) * nw * device_cus()) return 0;
+    if (nw < 1 || live > (int64_t)fact_blocks_per_cu(a, nw, shmem) * nw * device_cus()) return 0;
     *shmem_out = shmem;
     return nw;
 }
@@ -274,7 +292,7 @@ bool lds_headers(const SimArgs &a, int32_t s_pad, size_t per_wave) {
 const char *ssa_wave_name(const SimArgs &a) {
     size_t shmem = 0;
     if (fact_choice(a, &shmem) > 0) return "ssa_wave_fact_kernel";
-    const int32_t s_pad = (a.S + 3) & ~3;
+    const int32_t s_pad = wave_s_pad(a);
     const size_t per_wave = 64 * sizeof(double) + sizeof(int32_t) * (size_t)s_pad;
     return lds_headers(a, s_pad, per_wave) ? "ssa_wave_lds_kernel<true>" : "ssa_wave_lds_kernel<false>";
 }
@@ -286,19 +304,24 @@ hipError_t launch_ssa_wave(const SimArgs &a, int32_t *xs, hipStream_t st) {
         const int nw = fact_choice(a, &shmem);
         if (nw > 0) {
             const int64_t walkers = (int64_t)a.n_runs * a.cap;
-            const int64_t resident = (int64_t)fact_blocks_per_cu(nw, shmem) * device_cus();
+            const int64_t resident = (int64_t)fact_blocks_per_cu(a, nw, shmem) * device_cus();
             const unsigned blocks =
                 (unsigned)std::max<int64_t>(1, std::min<int64_t>(resident, (walkers + nw - 1) / nw));
-            const int32_t s_pad = (a.S + 3) & ~3;
-            hipLaunchKernelGGL(ssa_wave_fact_kernel, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
+            const int32_t s_pad = wave_s_pad(a);
+            if (a.desc2)
+                hipLaunchKernelGGL(ssa_wave_fact_kernel<RxnDesc2>, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
+            else
+                hipLaunchKernelGGL(ssa_wave_fact_kernel<RxnDesc>, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
             return hipGetLastError();
         }
     }
-    const int32_t s_pad = (a.S + 3) & ~3;
+    const int32_t s_pad = wave_s_pad(a);
     const size_t per_wave = 64 * sizeof(double) + sizeof(int32_t) * (size_t)s_pad;
     const int64_t walkers = (int64_t)a.n_runs * a.cap;
     const size_t desc_bytes = 16 * (size_t)a.R;
     if (lds_headers(a, s_pad, per_wave))
-        return launch_lds<true>(a, xs, s_pad, 2 * desc_bytes, per_wave, walkers, st);
-    return launch_lds<false>(a, xs, s_pad, desc_bytes, per_wave, walkers, st);
+        return a.desc2 ? launch_lds<true, RxnDesc2>(a, xs, s_pad, 2 * desc_bytes, per_wave, walkers, st)
+                       : launch_lds<true, RxnDesc>(a, xs, s_pad, 2 * desc_bytes, per_wave, walkers, st);
+    return a.desc2 ? launch_lds<false, RxnDesc2>(a, xs, s_pad, desc_bytes, per_wave, walkers, st)
+                   : launch_lds<false, RxnDesc>(a, xs, s_pad, desc_bytes, per_wave, walkers, st);
 }

@@ -14,6 +14,8 @@
 // header of the chosen reaction, then its dependency entries (each carrying
 // the descriptor of the reaction it names) together with its changes.
 #pragma once
+#include <type_traits>
+
 #include "queue_first.h"
 #include "we_common.h"
 
@@ -112,6 +114,8 @@ __device__ __forceinline__ void add_chunk_deltas(double *lchunk, int rr, double 
 //    global memory, the dependency lists (16-bit reaction ids) from global
 //    memory and the dependents' descriptors from LDS.
 struct GlobalTables {
+    using Dep = DepEntry;
+    static constexpr bool PAIR = false;
     const RxnDesc *__restrict__ d;
     const RxnInfo *__restrict__ h;
     const DepEntry *__restrict__ e;
@@ -120,28 +124,30 @@ struct GlobalTables {
     __device__ __forceinline__ DepEntry dep(int i) const { return e[i]; }
 };
 
+// D: the descriptors' form (RxnDesc2 where the network has it).
+template <class D>
 struct LdsTables {
-    const RxnDesc *d;                  // LDS
+    struct Dep : D {
+        uint16_t r;
+    };
+    static constexpr bool PAIR = std::is_same<D, RxnDesc2>::value;
+    const D *d;                        // LDS
     const RxnInfo *h;                  // LDS or global
     const uint16_t *__restrict__ ids;  // global
-    __device__ __forceinline__ RxnDesc desc(int r) const { return d[r]; }
+    __device__ __forceinline__ D desc(int r) const { return d[r]; }
     __device__ __forceinline__ RxnInfo info(int j) const { return h[j]; }
-    __device__ __forceinline__ DepEntry dep(int i) const {
+    __device__ __forceinline__ Dep dep(int i) const {
         const int r = ids[i];
-        const RxnDesc q = d[r];
-        DepEntry o;
-        o.c = q.c;
-        o.s1 = q.s1;
-        o.s2 = q.s2;
-        o.nu1 = q.nu1;
-        o.nu2 = q.nu2;
+        Dep o;
+        static_cast<D &>(o) = d[r];
         o.r = (uint16_t)r;
         return o;
     }
 };
 
 // One walker through one interval on the calling wave; lchunk (64 doubles)
-// and lx (S ints) are this wave's LDS slices.
+// and lx (S + 1 ints: the counts, and the 1 an absent reactant reads) are this
+// wave's LDS slices.
 template <class T>
 __device__ inline void wave_walker_t(const SimArgs &a, const T &tab, int32_t *__restrict__ xs, int32_t run,
                                      int32_t k, uint32_t iter, double *lchunk, int32_t *lx) {
@@ -150,6 +156,7 @@ __device__ inline void wave_walker_t(const SimArgs &a, const T &tab, int32_t *__
     const int32_t K = (R + 63) >> 6;
     int32_t *xw = xs + ((size_t)run * a.cap + k) * S;
     for (int s = lane; s < S; s += 64) lx[s] = xw[s];
+    if (T::PAIR && lane == 0) lx[S] = 1;
     __builtin_amdgcn_wave_barrier();
 
     // chunk sums from scratch
@@ -226,7 +233,7 @@ __device__ inline void wave_walker_t(const SimArgs &a, const T &tab, int32_t *__
         if (lane < info.chg_count) pc = a.chg[info.chg_begin + lane];
         int rr[WAVE_DEP_ROUNDS];
         double old[WAVE_DEP_ROUNDS];
-        DepEntry de[WAVE_DEP_ROUNDS];
+        typename T::Dep de[WAVE_DEP_ROUNDS];
         if (nround <= WAVE_DEP_ROUNDS) {
 #pragma unroll
             for (int q = 0; q < WAVE_DEP_ROUNDS; ++q) {

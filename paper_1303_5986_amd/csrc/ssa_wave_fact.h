@@ -33,20 +33,24 @@
 
 namespace {
 
+template <class D>
 union DescBits {
-    RxnDesc d;
+    D d;
     uint4 u;
 };
 
-__device__ __forceinline__ RxnDesc desc_of(const uint4 &u) {
-    DescBits b;
+template <class D>
+__device__ __forceinline__ D desc_of(const uint4 &u) {
+    DescBits<D> b;
     b.u = u;
     return b.d;
 }
 
-__device__ __forceinline__ double prop_u4(const uint4 &u, uint32_t x1, uint32_t x2) {
-    return propensity_from(desc_of(u), x1, x2);
-}
+// Whether a reaction also takes a reactant besides the one it is listed under.
+__device__ __forceinline__ bool two_species(const RxnDesc &d) { return d.nu2 > 0; }
+// the other reactant is never one of the changed species unless it is a real
+// second species: the extra species S does not change, and a pair's is its own
+__device__ __forceinline__ bool two_species(const RxnDesc2 &) { return true; }
 
 }  // namespace
 
@@ -58,7 +62,9 @@ struct FactTables {
 };
 
 // One walker through one interval on the calling wave; lchunk (64 doubles,
-// the chunk sums) and lx (S ints) are this wave's LDS slices.
+// the chunk sums) and lx (S + 1 ints: the counts, and the 1 an absent reactant
+// reads) are this wave's LDS slices.  D: the descriptors' form.
+template <class D>
 __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab, int32_t *__restrict__ xs,
                                         int32_t run, int32_t k, uint32_t iter, double *lchunk, int32_t *lx) {
     const int lane = threadIdx.x & 63;
@@ -66,6 +72,7 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
     const int32_t K = (R + 63) >> 6;
     int32_t *xw = xs + ((size_t)run * a.cap + k) * S;
     for (int s = lane; s < S; s += 64) lx[s] = xw[s];
+    if (std::is_same<D, RxnDesc2>::value && lane == 0) lx[S] = 1;
     __builtin_amdgcn_wave_barrier();
 
     // chunk sums from scratch
@@ -75,7 +82,7 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
             const int r = c * 64 + lane;
             double v = 0.0;
             if (r < R) {
-                const RxnDesc d = desc_of(tab.d[r]);
+                const D d = desc_of<D>(tab.d[r]);
                 v = propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
             }
             const double tot = lane_value(scan_incl(v), 63);
@@ -127,7 +134,7 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
         if (rsel < R) {
             dsel = tab.d[rsel];
             hsel = tab.h[rsel];
-            const RxnDesc d = desc_of(dsel);
+            const D d = desc_of<D>(dsel);
             v = propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
         }
         const double Q = scan_incl(v);
@@ -183,7 +190,7 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
                 const int32_t off = kk == 0 ? 0 : kk == 1 ? o1 : kk == 2 ? o2 : o3;
                 const int32_t r = tab.inc[beg + idx - off];
                 dq[q] = tab.d[r];
-                const RxnDesc d = desc_of(dq[q]);
+                const D d = desc_of<D>(dq[q]);
                 x1q[q] = lx[d.s1];
                 x2q[q] = lx[d.s2];
                 kq[q] = kk;
@@ -210,13 +217,13 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
         for (int q = 0; q < FACT_DEP_ROUNDS; ++q) {
             if (q * 64 >= nd) break;
             if (chk[q] >= 0) {
-                const RxnDesc d = desc_of(dq[q]);
+                const D d = desc_of<D>(dq[q]);
                 // listed under an earlier changed species too: counted there
                 // (its other reactant is one of sp0 .. sp(k-1))
                 const int32_t kk = kq[q];
                 const int32_t spk = kk == 0 ? sp0 : kk == 1 ? sp1 : kk == 2 ? sp2 : sp3;
                 const int32_t other = d.s1 == spk ? (int32_t)d.s2 : (int32_t)d.s1;
-                const bool dup = d.nu2 > 0 && ((kk >= 1 && other == sp0) || (kk >= 2 && other == sp1) ||
+                const bool dup = two_species(d) && ((kk >= 1 && other == sp0) || (kk >= 2 && other == sp1) ||
                                                (kk >= 3 && other == sp2));
                 if (!dup) {
                     const double before = propensity_from(d, (uint32_t)x1q[q], (uint32_t)x2q[q]);

@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #define WE_COUNT_MAX_DEV 131071
 #define WE_DPACK_WORDS 8
 
@@ -30,6 +32,25 @@ struct __align__(16) RxnDesc {
     uint8_t nu1, nu2;// multiplicities (0 = absent)
     uint8_t nchg;    // number of species changed
     uint8_t order;   // nu1 + nu2
+};
+
+// The same for a network whose reactions take at most two molecules, in a form
+// that needs no case distinction: h = x1 (x2 - hom) with the counts of s1 and
+// s2, where an absent reactant is the extra species S, whose count is always
+// 1, and a pair of equal molecules takes its species twice with hom = 1 and
+// half the rate constant.  h is an integer below 2^35, and halving c is exact,
+// so c h rounds as c_j h_j does: the same propensity in 7 instructions where
+// the general form's two binomials take about 40.  Each event of a wave kernel
+// evaluates three of them per lane; what bounds those kernels is the length and
+// the issue time of that chain.  One run of the 354/3680 network 280 -> 234 us
+// per launch (factored tables), eight runs 1158 -> 957 us (descriptor tables).
+struct __align__(16) RxnDesc2 {
+    double c;        // c_j, halved for a pair of equal molecules
+    uint16_t s1, s2; // reactant species (S: none)
+    uint8_t hom;     // 1: s1 and s2 are the same species
+    uint8_t pad;
+    uint8_t nchg;    // as in RxnDesc
+    uint8_t order;
 };
 
 // A reaction's Hill-type repression (Sec. III.C): its propensity is divided
@@ -103,6 +124,7 @@ struct SimArgs {
     const uint16_t *__restrict__ dep;    //       (sorted, unique)
     const RxnInfo *__restrict__ rinfo;   // [R]
     const DepEntry *__restrict__ deps;   // dependency entries with descriptors
+    const RxnDesc2 *__restrict__ desc2;  // [R padded] (null: some reaction takes three molecules)
     const HillDesc *__restrict__ hill;   // [R padded] Hill-type rates (null: none)
     const uint2 *__restrict__ fhdr;      // [R] factored change headers (null: network too large)
     const uint32_t *__restrict__ inc_tab;// [S] incidence start | count << 16
@@ -293,9 +315,13 @@ __device__ __forceinline__ double binom_f64(double xd, uint32_t nu) {
 
 // a_j = c_j * h_j(x): h_j is an exact integer (order <= 3 keeps it below
 // 2^53), so the only rounding is the final product, as with an int64 h.
+// RxnDesc2: counts up to 2^17, so the differences and the product are exact.
 template <class D>
 __device__ __forceinline__ double propensity_from(const D &d, uint32_t x1, uint32_t x2) {
-    return d.c * (binom_f64((double)x1, d.nu1) * binom_f64((double)x2, d.nu2));
+    if constexpr (std::is_base_of<RxnDesc2, D>::value)
+        return d.c * ((double)(int32_t)x1 * (double)((int32_t)x2 - (int32_t)d.hom));
+    else
+        return d.c * (binom_f64((double)x1, d.nu1) * binom_f64((double)x2, d.nu2));
 }
 
 // ---------------------------------------------------------------- bins

@@ -28,6 +28,7 @@ struct we_network {
     std::vector<int32_t> chg_ptr, chg, dep_ptr;
     std::vector<uint16_t> dep;
     RxnDesc *d_desc = nullptr;
+    RxnDesc2 *d_desc2 = nullptr;    // null: a reaction of order three
     int32_t *d_chg_ptr = nullptr, *d_chg = nullptr, *d_dep_ptr = nullptr;
     uint16_t *d_dep = nullptr;
     RxnInfo *d_rinfo = nullptr;

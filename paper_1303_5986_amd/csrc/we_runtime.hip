@@ -235,6 +235,20 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
     desc_pad.resize(R_pad, RxnDesc{});
     dpack.resize((size_t)R_pad * WE_DPACK_WORDS, 0);
     hipError_t e = up((void **)&net->d_desc, desc_pad.data(), sizeof(RxnDesc) * R_pad);
+    if (e == hipSuccess && net->max_order <= 2) {
+        std::vector<RxnDesc2> desc2(R_pad, RxnDesc2{});
+        for (int32_t j = 0; j < R; ++j) {
+            const RxnDesc &d = net->desc[j];
+            RxnDesc2 &q = desc2[j];
+            q.hom = d.nu1 == 2 ? 1 : 0;
+            q.c = q.hom ? 0.5 * d.c : d.c;
+            q.s1 = d.nu1 ? d.s1 : (uint16_t)S;
+            q.s2 = q.hom ? d.s1 : d.nu2 ? d.s2 : (uint16_t)S;
+            q.nchg = d.nchg;
+            q.order = d.order;
+        }
+        e = up((void **)&net->d_desc2, desc2.data(), sizeof(RxnDesc2) * R_pad);
+    }
     if (e == hipSuccess) e = up((void **)&net->d_chg_ptr, net->chg_ptr.data(), 4 * (R + 1));
     if (e == hipSuccess) e = up((void **)&net->d_chg, net->chg.data(), 4 * net->chg.size());
     if (e == hipSuccess) e = up((void **)&net->d_dep_ptr, net->dep_ptr.data(), 4 * (R + 1));
@@ -284,6 +298,7 @@ extern "C" void we_destroy_network(we_network *net) {
     (void)hipFree(net->d_inc);
     (void)hipFree(net->d_hill);
     (void)hipFree(net->d_desc);
+    (void)hipFree(net->d_desc2);
     (void)hipFree(net->d_chg_ptr);
     (void)hipFree(net->d_chg);
     (void)hipFree(net->d_dep_ptr);
@@ -533,6 +548,7 @@ extern "C" we_status we_init(const we_network *net, const we_grid *g, const we_p
     a.desc = net->d_desc; a.chg_ptr = net->d_chg_ptr; a.chg = net->d_chg; a.dpack = net->d_dpack;
     a.dep_ptr = net->d_dep_ptr; a.dep = net->d_dep;
     a.rinfo = net->d_rinfo; a.deps = net->d_deps;
+    a.desc2 = net->d_desc2;
     a.hill = hill ? net->d_hill : nullptr;
     a.fhdr = net->d_fhdr;
     a.inc_tab = net->d_inc_tab;
