@@ -140,8 +140,10 @@ __global__ __launch_bounds__(64 * WAVE_FACT_MAX_WAVES) void ssa_wave_fact_kernel
     uint4 *ld = reinterpret_cast<uint4 *>(smem);
     uint2 *lh = reinterpret_cast<uint2 *>(smem + fact_off_hdr(R));
     uint32_t *ltab = reinterpret_cast<uint32_t *>(smem + fact_off_tab(R));
+    constexpr bool PAIR = std::is_same<D, RxnDesc2>::value;
     uint16_t *linc = reinterpret_cast<uint16_t *>(smem + fact_off_inc(R, S));
-    unsigned char *wbase = smem + fact_tables_bytes(R, S, a.n_inc);
+    uint32_t *linc2 = reinterpret_cast<uint32_t *>(smem + fact_off_inc(R, S));
+    unsigned char *wbase = smem + fact_tables_bytes(R, S, a.n_inc, PAIR);
     const int nw = blockDim.x >> 6, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double *lchunk = reinterpret_cast<double *>(wbase) + wv * 64;
     int32_t *lx = reinterpret_cast<int32_t *>(wbase + (size_t)nw * 64 * sizeof(double)) + wv * s_pad;
@@ -151,13 +153,17 @@ __global__ __launch_bounds__(64 * WAVE_FACT_MAX_WAVES) void ssa_wave_fact_kernel
         lh[i] = a.fhdr[i];
     }
     for (int32_t i = threadIdx.x; i < S; i += blockDim.x) ltab[i] = a.inc_tab[i];
-    for (int32_t i = threadIdx.x; i < a.n_inc; i += blockDim.x) linc[i] = a.inc[i];
+    for (int32_t i = threadIdx.x; i < a.n_inc; i += blockDim.x) {
+        if constexpr (PAIR) linc2[i] = a.inc2[i];
+        else linc[i] = a.inc[i];
+    }
     __syncthreads();
     FactTables tab;
     tab.d = ld;
     tab.h = lh;
     tab.tab = ltab;
     tab.inc = linc;
+    tab.inc2 = linc2;
     const uint32_t iter = *a.iter_dev;
     const uint32_t M = (uint32_t)a.m_targ, cap = (uint32_t)a.cap;
     const uint32_t total = a.queue[1] * M;
@@ -232,7 +238,7 @@ hipError_t launch_lds(const SimArgs &a, int32_t *xs, int32_t s_pad, size_t table
 // beside one wave's slice.
 bool wave_fact_fits(const SimArgs &a, size_t *tables, size_t *per_wave) {
     if (!a.fhdr || !a.inc || !a.inc_tab) return false;
-    *tables = fact_tables_bytes(a.R, a.S, a.n_inc);
+    *tables = fact_tables_bytes(a.R, a.S, a.n_inc, a.inc2 != nullptr);
     *per_wave = 64 * sizeof(double) + sizeof(int32_t) * (size_t)wave_s_pad(a);
     return *tables + *per_wave <= WAVE_LDS_BYTES;
 }
@@ -254,7 +260,7 @@ int fact_blocks_per_cu_t(int waves, size_t shmem) {
     return last;
 }
 int fact_blocks_per_cu(const SimArgs &a, int waves, size_t shmem) {
-    return a.desc2 ? fact_blocks_per_cu_t<RxnDesc2>(waves, shmem) : fact_blocks_per_cu_t<RxnDesc>(waves, shmem);
+    return a.inc2 ? fact_blocks_per_cu_t<RxnDesc2>(waves, shmem) : fact_blocks_per_cu_t<RxnDesc>(waves, shmem);
 }
 }  // namespace
 
@@ -308,7 +314,7 @@ hipError_t launch_ssa_wave(const SimArgs &a, int32_t *xs, hipStream_t st) {
             const unsigned blocks =
                 (unsigned)std::max<int64_t>(1, std::min<int64_t>(resident, (walkers + nw - 1) / nw));
             const int32_t s_pad = wave_s_pad(a);
-            if (a.desc2)
+            if (a.inc2)
                 hipLaunchKernelGGL(ssa_wave_fact_kernel<RxnDesc2>, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);
             else
                 hipLaunchKernelGGL(ssa_wave_fact_kernel<RxnDesc>, dim3(blocks), dim3(64 * nw), shmem, st, a, xs, s_pad);

@@ -89,7 +89,16 @@ __host__ __device__ inline int32_t change_delta(int32_t p) { return (int32_t)(in
 // taking it as a reactant start in the incidence list (bits 0-15) and how
 // many there are (bits 16-31); each species' ids ascend.  The reactions whose
 // propensity a firing changes are the union of its changed species' lists.
+// For a network of reactions of at most two molecules (RxnDesc2) an incidence
+// entry is a 32-bit word that also carries what a propensity change needs: the
+// reaction (bits 0-11), its other reactant species (bits 12-21; the extra
+// species S if none, the listed species itself for a pair of equal molecules)
+// and hom (bit 22).
 #define FACT_MAX_SPECIES 512
+#define FACT_PAIR_MAX_REACTIONS 4096
+__host__ __device__ inline uint32_t fact_pair_entry(int32_t r, int32_t other, int32_t hom) {
+    return (uint32_t)r | ((uint32_t)other << 12) | ((uint32_t)hom << 22);
+}
 #define FACT_MAX_INC 65535
 #define FACT_MAX_CHANGES 4
 __host__ __device__ inline uint32_t fact_code(int32_t s, int32_t delta) {
@@ -108,8 +117,8 @@ __host__ __device__ inline size_t fact_off_tab(int32_t R) { return fact_align16(
 __host__ __device__ inline size_t fact_off_inc(int32_t R, int32_t S) {
     return fact_align16(fact_off_tab(R) + 4 * (size_t)S);
 }
-__host__ __device__ inline size_t fact_tables_bytes(int32_t R, int32_t S, int32_t n_inc) {
-    return fact_align16(fact_off_inc(R, S) + 2 * (size_t)n_inc);
+__host__ __device__ inline size_t fact_tables_bytes(int32_t R, int32_t S, int32_t n_inc, bool pair) {
+    return fact_align16(fact_off_inc(R, S) + (pair ? 4 : 2) * (size_t)n_inc);
 }
 
 // Everything a WE kernel needs, passed by value.
@@ -129,6 +138,7 @@ struct SimArgs {
     const uint2 *__restrict__ fhdr;      // [R] factored change headers (null: network too large)
     const uint32_t *__restrict__ inc_tab;// [S] incidence start | count << 16
     const uint16_t *__restrict__ inc;    // [n_inc] species -> reactions taking it as a reactant
+    const uint32_t *__restrict__ inc2;   // [n_inc] the same as fact_pair_entry words (with desc2)
     int32_t n_inc;
     int32_t n_chg;                       // entries of chg (chg_ptr[R])
     int32_t S, R;

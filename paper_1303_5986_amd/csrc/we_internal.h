@@ -40,6 +40,7 @@ struct we_network {
     uint2 *d_fhdr = nullptr;
     uint32_t *d_inc_tab = nullptr;
     uint16_t *d_inc = nullptr;
+    uint32_t *d_inc2 = nullptr;     // null: no d_desc2, or too many reactions
     std::vector<HillDesc> hill;     // empty: no Hill-type rates
     HillDesc *d_hill = nullptr;     // [R padded to 64]
 };

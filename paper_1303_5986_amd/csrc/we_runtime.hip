@@ -260,6 +260,17 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
         e = up((void **)&net->d_fhdr, net->fhdr.data(), sizeof(uint2) * net->fhdr.size());
         if (e == hipSuccess) e = up((void **)&net->d_inc_tab, net->inc_tab.data(), 4 * net->inc_tab.size());
         if (e == hipSuccess) e = up((void **)&net->d_inc, net->inc.data(), 2 * net->inc.size());
+        if (e == hipSuccess && net->d_desc2 && R <= FACT_PAIR_MAX_REACTIONS) {
+            std::vector<uint32_t> inc2(net->inc.size(), 0u);
+            for (int32_t sp = 0; sp < S; ++sp)
+                for (uint32_t i = net->inc_tab[sp] & 0xFFFFu, n = net->inc_tab[sp] >> 16; n > 0; ++i, --n) {
+                    const RxnDesc &d = net->desc[net->inc[i]];
+                    const bool hom = d.nu1 == 2;
+                    const int32_t other = hom ? sp : d.nu2 == 0 ? S : d.s1 == sp ? d.s2 : d.s1;
+                    inc2[i] = fact_pair_entry(net->inc[i], other, hom ? 1 : 0);
+                }
+            e = up((void **)&net->d_inc2, inc2.data(), 4 * inc2.size());
+        }
     }
     if (e != hipSuccess) {
         we_destroy_network(net);
@@ -296,6 +307,7 @@ extern "C" void we_destroy_network(we_network *net) {
     (void)hipFree(net->d_fhdr);
     (void)hipFree(net->d_inc_tab);
     (void)hipFree(net->d_inc);
+    (void)hipFree(net->d_inc2);
     (void)hipFree(net->d_hill);
     (void)hipFree(net->d_desc);
     (void)hipFree(net->d_desc2);
@@ -553,6 +565,7 @@ extern "C" we_status we_init(const we_network *net, const we_grid *g, const we_p
     a.fhdr = net->d_fhdr;
     a.inc_tab = net->d_inc_tab;
     a.inc = net->d_inc;
+    a.inc2 = net->d_inc2;
     a.n_inc = (int32_t)net->inc.size();
     a.n_chg = (int32_t)net->chg.size();
     a.engine = p->engine;
