@@ -142,9 +142,18 @@ __global__ __launch_bounds__(256) void batch_wave_kernel(const SimArgs *__restri
 }
 
 // Group variant: a work item is 64 / L consecutive slots of one run, one
-// group of L lanes per slot; lx slices are s_max ints (the largest species
-// count among the members on this variant).  BR > 0: the members' lane
+// group of L lanes per slot; lx slices are s_max ints (the largest
+// group_slice among the members on this variant).  BR > 0: the members' lane
 // blocks hold at most BR reactions, kept in registers (group_walker).
+template <int L, int BR, class D>
+__device__ __forceinline__ void batch_group_item(const SimArgs &a, const D *desc, const Item &it, int32_t *xs, int32_t *lx,
+                                                 int grp) {
+    const int32_t k = it.slot + grp;
+    const bool live = k < a.cap && k < a.n_walk[it.run];
+    const GroupTables<D> tb{desc, a.chg_ptr, a.chg};
+    group_walker<L, BR, D>(a, tb, xs, it.run, k, live, *a.iter_dev, lx);
+}
+
 template <int L, int BR = 0>
 __global__ __launch_bounds__(256) void batch_group_kernel(const SimArgs *__restrict__ args,
                                                           int32_t *const *__restrict__ xptr,
@@ -161,10 +170,8 @@ __global__ __launch_bounds__(256) void batch_group_kernel(const SimArgs *__restr
         if (idx >= (uint32_t)n_items) break;
         const Item it = items[idx];
         const SimArgs &a = args[it.sim];
-        const int32_t k = it.slot + grp;
-        const bool live = k < a.cap && k < a.n_walk[it.run];
-        const GroupTables tb{a.desc, a.chg_ptr, a.chg};
-        group_walker<L, BR>(a, tb, xptr[it.sim], it.run, k, live, *a.iter_dev, lx);
+        if (a.desc2) batch_group_item<L, BR>(a, a.desc2, it, xptr[it.sim], lx, grp);
+        else batch_group_item<L, BR>(a, a.desc, it, xptr[it.sim], lx, grp);
         // every lane executes the atomic (lane 0 adds one): see batch_lane_kernel
         const uint32_t got = atomicAdd(counter, lane == 0 ? 1u : 0u);
         idx = n_static + (uint32_t)__shfl((int)got, 0, 64);
@@ -208,7 +215,7 @@ struct we_batch {
     size_t resample_shmem = 0;
     bool observe = false;
     int32_t s_pad = 4;
-    int32_t s_group = 1;              // largest species count among group-kernel members
+    int32_t s_group = 1;              // largest group_slice among group-kernel members
     int32_t iter = 0, max_iters = 0;
     hipGraphExec_t graph_exec = nullptr;
     hipStream_t capture_stream = nullptr;
@@ -521,7 +528,7 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         b->sims.push_back(s);
         b->var.push_back(variant_of(s));
         b->s_pad = std::max(b->s_pad, (S + 3) & ~3);
-        if (s->kernel == WE_KERNEL_GROUP) b->s_group = std::max(b->s_group, S);
+        if (s->kernel == WE_KERNEL_GROUP) b->s_group = std::max(b->s_group, group_slice(S));
         b->max_iters = (i == 0) ? s->max_iters : std::min(b->max_iters, s->max_iters);
     }
     if (cache_dirty) write_cache(cache_path, cache);

@@ -7,7 +7,7 @@
 // queue (the live walkers of every run, in bin segments ordered by their
 // events per walker, built by launch_work_queue) with one atomic, runs them
 // through the interval, and takes the next batch until the queue is empty.
-// Counts live in LDS (S ints per walker, 64 / L walkers per wave, four waves
+// Counts live in LDS (S + 1 ints per walker, 64 / L walkers per wave, four waves
 // per block); the descriptors and changes are copied to LDS beside them when
 // they take at most 48 KB (ssa_group_kernel<L, true>), else read through the
 // cache (<L, false>).
@@ -24,30 +24,33 @@ __host__ __device__ inline size_t group_tables_bytes(int32_t R, int32_t n_chg) {
     return (16 * (size_t)R + 4 * ((size_t)R + 1 + (size_t)n_chg) + 15) & ~(size_t)15;
 }
 
-template <int L, bool LT, int BR>
+template <int L, bool LT, int BR, class D>
 __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, int32_t *__restrict__ xs) {
     extern __shared__ __align__(16) unsigned char gsm[];
     constexpr int G = 64 / L;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int grp = lane / L;
-    GroupTables tb{a.desc, a.chg_ptr, a.chg};
+    const D *gdesc;
+    if constexpr (std::is_same<D, RxnDesc2>::value) gdesc = a.desc2;
+    else gdesc = a.desc;
+    GroupTables<D> tb{gdesc, a.chg_ptr, a.chg};
     size_t off = 0;
     if constexpr (LT) {
         const int32_t R = a.R;
         uint4 *ld = reinterpret_cast<uint4 *>(gsm);
         int32_t *lcp = reinterpret_cast<int32_t *>(gsm + 16 * (size_t)R);
         int32_t *lcg = lcp + R + 1;
-        const uint4 *gd = reinterpret_cast<const uint4 *>(a.desc);
+        const uint4 *gd = reinterpret_cast<const uint4 *>(gdesc);
         for (int32_t i = threadIdx.x; i < R; i += blockDim.x) ld[i] = gd[i];
         for (int32_t i = threadIdx.x; i <= R; i += blockDim.x) lcp[i] = a.chg_ptr[i];
         for (int32_t i = threadIdx.x; i < a.n_chg; i += blockDim.x) lcg[i] = a.chg[i];
         __syncthreads();
-        tb.desc = reinterpret_cast<const RxnDesc *>(ld);
+        tb.desc = reinterpret_cast<const D *>(ld);
         tb.chg_ptr = lcp;
         tb.chg = lcg;
         off = group_tables_bytes(R, a.n_chg);
     }
-    int32_t *lx = reinterpret_cast<int32_t *>(gsm + off) + ((size_t)wv * G + grp) * a.S;
+    int32_t *lx = reinterpret_cast<int32_t *>(gsm + off) + ((size_t)wv * G + grp) * group_slice(a.S);
     const uint32_t iter = *a.iter_dev;
     const uint32_t M = (uint32_t)a.m_targ, cap = (uint32_t)a.cap;
     const uint32_t total = a.queue[1] * M;
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, 
                 live = true;
             }
         }
-        group_walker<L, BR>(a, tb, xs, run, k, live, iter, lx);
+        group_walker<L, BR, D>(a, tb, xs, run, k, live, iter, lx);
         // every lane executes the atomic (lane 0 adds G, the others zero) and
         // lane 0's result is broadcast, so no lane leaves the wave's path
         const uint32_t got = atomicAdd(&a.queue[0], lane == 0 ? (uint32_t)G : 0u);
@@ -104,15 +107,15 @@ int group_regs(const SimArgs &a, int32_t lanes) {
     return B <= 4 ? 4 : B <= 8 ? 8 : 0;
 }
 
-template <int L, bool LT, int BR>
+template <int L, bool LT, int BR, class D>
 hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
     constexpr int G = 64 / L;
     const size_t shmem =
-        (LT ? group_tables_bytes(a.R, a.n_chg) : 0) + sizeof(int32_t) * (size_t)GROUP_WAVES * G * a.S;
+        (LT ? group_tables_bytes(a.R, a.n_chg) : 0) + sizeof(int32_t) * (size_t)GROUP_WAVES * G * group_slice(a.S);
     static size_t last_shmem = 0;
     static int per_cu = 0;
     if (per_cu == 0 || shmem != last_shmem) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ssa_group_kernel<L, LT, BR>, 64 * GROUP_WAVES,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ssa_group_kernel<L, LT, BR, D>, 64 * GROUP_WAVES,
                                                          shmem) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
@@ -121,16 +124,21 @@ hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
     const int64_t walkers = (int64_t)a.n_runs * a.cap;
     const int64_t need = (walkers + (int64_t)GROUP_WAVES * G - 1) / ((int64_t)GROUP_WAVES * G);
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)per_cu * group_cus()));
-    hipLaunchKernelGGL((ssa_group_kernel<L, LT, BR>), dim3(blocks), dim3(64 * GROUP_WAVES), shmem, st, a, xs);
+    hipLaunchKernelGGL((ssa_group_kernel<L, LT, BR, D>), dim3(blocks), dim3(64 * GROUP_WAVES), shmem, st, a, xs);
     return hipGetLastError();
+}
+
+template <int L, class D>
+hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
+    const int br = group_regs(a, L);
+    if (br == 4) return launch_group<L, true, 4, D>(a, xs, st);
+    if (br == 8) return launch_group<L, true, 8, D>(a, xs, st);
+    return group_tables_in_lds(a) ? launch_group<L, true, 0, D>(a, xs, st) : launch_group<L, false, 0, D>(a, xs, st);
 }
 
 template <int L>
 hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
-    const int br = group_regs(a, L);
-    if (br == 4) return launch_group<L, true, 4>(a, xs, st);
-    if (br == 8) return launch_group<L, true, 8>(a, xs, st);
-    return group_tables_in_lds(a) ? launch_group<L, true, 0>(a, xs, st) : launch_group<L, false, 0>(a, xs, st);
+    return a.desc2 ? launch_group<L, RxnDesc2>(a, xs, st) : launch_group<L, RxnDesc>(a, xs, st);
 }
 }  // namespace
 

@@ -33,6 +33,9 @@
 
 #include <algorithm>
 
+// Ints of a group's slice of counts.
+__host__ __device__ inline int32_t group_slice(int32_t S) { return S + 1; }
+
 // Largest group walker table: counts of 64 / L walkers per wave in LDS.
 #define GROUP_LDS_INTS_PER_WAVE 4096
 
@@ -79,20 +82,25 @@ __device__ __forceinline__ double group_scan_incl(double v) {
 
 // The network tables a group walker reads: a.desc, a.chg_ptr and a.chg, or
 // a block's LDS copy of them.
+template <class D>
 struct GroupTables {
-    const RxnDesc *desc;
+    const D *desc;
     const int32_t *chg_ptr;
     const int32_t *chg;
 };
 
 // The walkers in slots k of run `run` for the groups with live set (k may
-// differ per group); lx is this group's slice of S counts in LDS.  Every lane
-// of the wave must call it.  BR > 0 (blocks of at most BR reactions): each
+// differ per group); lx is this group's slice of S + 1 ints in LDS (the counts,
+// and the 1 that an absent reactant of a RxnDesc2 reads).  Every lane of the
+// wave must call it.  D: the descriptors' form; a lane evaluates its whole block
+// every event, so the general form's two binomials per reaction were most of
+// an event's instructions.  Toggle, 16 runs on 8 walkers per wave: 46.2 -> 42.6 us
+// per launch.  BR > 0 (blocks of at most BR reactions): each
 // lane keeps its block's descriptors in registers for the whole interval and
 // its block's propensities from step 1 for step 3, instead of reading the
 // descriptors again every event.
-template <int L, int BR = 0>
-__device__ inline void group_walker(const SimArgs &a, const GroupTables &tb, int32_t *__restrict__ xs, int32_t run,
+template <int L, int BR, class D>
+__device__ inline void group_walker(const SimArgs &a, const GroupTables<D> &tb, int32_t *__restrict__ xs, int32_t run,
                                     int32_t k, bool live, uint32_t iter, int32_t *lx) {
     const int lane = threadIdx.x & 63;
     const int gl = lane & (L - 1);
@@ -104,6 +112,7 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables &tb, int
     int32_t *xw = live ? xs + ((size_t)run * a.cap + k) * S : nullptr;
     if (live)
         for (int32_t s = gl; s < S; s += L) lx[s] = xw[s];
+    if (std::is_same<D, RxnDesc2>::value && gl == 0) lx[S] = 1;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -122,12 +131,12 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables &tb, int
     // -log(1 - u1) and u2 of the group's event (e & ~(L - 1)) + gl
     double rexp = 0.0, ru2 = 0.0;
     constexpr int NR = BR > 0 ? BR : 1;
-    RxnDesc dr[NR];
+    D dr[NR];
     double pr[NR];
     if constexpr (BR > 0) {
 #pragma unroll
         for (int b = 0; b < NR; ++b) {
-            dr[b] = RxnDesc{};
+            dr[b] = D{};
             pr[b] = 0.0;
             if (r_lo + b < r_hi) dr[b] = tb.desc[r_lo + b];
         }
@@ -145,7 +154,7 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables &tb, int
                     }
         } else if (go) {
             for (int32_t r = r_lo; r < r_hi; ++r) {
-                const RxnDesc d = tb.desc[r];
+                const D d = tb.desc[r];
                 part += propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
             }
         }
@@ -197,7 +206,7 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables &tb, int
                     }
             } else {
                 for (int32_t r = r_lo; r < r_hi; ++r) {
-                    const RxnDesc d = tb.desc[r];
+                    const D d = tb.desc[r];
                     const double ar = propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
                     if (ar > 0.0) {
                         last = r;
