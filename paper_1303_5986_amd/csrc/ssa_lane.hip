@@ -31,6 +31,40 @@
 #define LANE_REFILL_MIN 12
 #endif
 
+// A wave's share of the work queue.  Atomics on one address (or one 128-byte
+// line) take 11.4 ns each on this device, whoever asks (0.27 ns over 64 lines):
+// with a single queue head the first request of 4096 waves alone took 47 us,
+// and 64 switch runs (330,000 walkers of 3.4 events) waited on the head more
+// than they computed.  So the queue, in tiles of 64 positions, is dealt out to
+// up to 64 heads on lines of their own, block b using head b mod n (a multiple
+// of 8 heads keeps each on one XCD); a wave's first 64 positions are static.
+// Tiles alternate between the heads in queue order, so each head hands out the
+// same mix, busiest first.  The static tiles go block by block, so that the
+// busy ones spread over a CU's four SIMDs: given to wave 0 of every block first
+// they all land on one SIMD of each CU (2048 Schloegl runs 743 against 675 us).
+// No result depends on it.  Per launch, before and after: 64 switch runs 179 ->
+// 58 us, 256 tau-leaping runs 57 -> 44 us.
+#define POOL_BLOCKS_PER_HEAD 4
+struct PoolQueue {
+    uint32_t n, s;          // heads in use, this block's
+    uint32_t first;         // this wave's static first position
+    uint32_t n_first;       // positions handed out statically
+    uint32_t size;          // positions of this head's tiles (its last tile may pass the queue's end)
+    uint32_t *head;
+    __device__ __forceinline__ PoolQueue(const SimArgs &a, uint32_t total) {
+        n = min((uint32_t)a.n_heads, max(gridDim.x / POOL_BLOCKS_PER_HEAD, 1u));
+        if (n >= 8) n &= ~7u;
+        s = blockIdx.x % n;
+        const uint32_t blocks = (gridDim.x - s + n - 1) / n, tiles = (total + 63) / 64;
+        first = (blockIdx.x / n * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64u;
+        n_first = (blockDim.x >> 6) * blocks * 64u;
+        size = tiles > s ? (tiles - s + n - 1) / n * 64u : 0u;
+        head = a.heads + s * WE_HEAD_STRIDE;
+    }
+    // queue position of this head's position i
+    __device__ __forceinline__ uint32_t at(uint32_t i) const { return i < size ? ((i >> 6) * n + s) * 64u + (i & 63u) : ~0u; }
+};
+
 // Persistent lane kernel: every lane runs walkers from the work queue (see
 // work_queue.hip) until it is empty; the wave takes as many queue entries as
 // it has idle lanes with one atomic and hands them out in lane order.  Walkers
@@ -53,11 +87,12 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
     const double tau = a.tau;
     const uint32_t M = (uint32_t)a.m_targ;
     const uint32_t total = a.queue[1] * M;
+    const PoolQueue pq(a, total);
     const unsigned long long below = lane ? ((1ull << lane) - 1ull) : 0ull;
     LaneWalker w;
     int32_t x[SMAX];
     w.bad = false;
-    bool active = false, exhausted = false;
+    bool active = false, exhausted = false, first = true;
     size_t gslot = 0;
     int32_t *xr = xs;
     for (;;) {
@@ -67,11 +102,15 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
             // every lane executes the atomic (only the leader adds), so no
             // lane takes a path of its own around the wave-wide steps
             const int leader = __ffsll((long long)need) - 1;
-            const uint32_t got = atomicAdd(&a.queue[0], lane == leader ? (uint32_t)nneed : 0u);
-            const uint32_t base = (uint32_t)__shfl((int)got, leader, 64);
-            if ((uint64_t)base + (uint64_t)nneed >= total) exhausted = true;
+            uint32_t base = pq.first;
+            if (!first) {
+                const uint32_t got = atomicAdd(pq.head, lane == leader ? (uint32_t)nneed : 0u);
+                base = pq.n_first + (uint32_t)__shfl((int)got, leader, 64);
+            }
+            if ((uint64_t)(first ? pq.n_first : base + (uint32_t)nneed) >= pq.size) exhausted = true;
+            first = false;
             if (!active) {
-                const uint32_t q = base + (uint32_t)__popcll(need & below);
+                const uint32_t q = pq.at(base + (uint32_t)__popcll(need & below));
                 if (q < total) {
                     const uint32_t sg = q / M, o = q - sg * M;
                     const int2 seg = a.seg[sg];

@@ -17,6 +17,10 @@
 
 #define WE_COUNT_MAX_DEV 131071
 #define WE_DPACK_WORDS 8
+// Queue heads of the lane kernels: at most this many, one per 128-byte line
+// (atomics on words of one line are as serial as on one word).
+#define WE_MAX_HEADS 64
+#define WE_HEAD_STRIDE 32
 
 // Error bits latched in device memory.
 enum : int32_t {
@@ -207,6 +211,8 @@ struct SimArgs {
     int32_t *seg_cur;                    // [n_bins][seg_rep]
     int2 *seg;                           // [n_runs * n_bins] (first slot run*cap + j*m_targ, walkers)
     uint32_t *queue;                     // [2] next walker index, number of segments
+    uint32_t *heads;                     // [n_heads] the lane kernels' queue heads, WE_HEAD_STRIDE
+    int32_t n_heads;                     //   words apart (in s_w, which only resampling uses)
 };
 
 // ---------------------------------------------------------------- Philox

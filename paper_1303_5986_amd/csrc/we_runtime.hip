@@ -619,6 +619,11 @@ extern "C" we_status we_init(const we_network *net, const we_grid *g, const we_p
     a.seg_cur = a.seg_off + a.seg_rep * NB;
     a.seg = (int2 *)at(P_SEGLIST);
     a.queue = (uint32_t *)at(P_QUEUE);
+    // the heads share the resampling's weight scratch, which is free from the
+    // end of one resampling to the next; too small for one line: the queue's own
+    a.n_heads = (int32_t)std::min<int64_t>(WE_MAX_HEADS, (int64_t)n_runs * cap * 8 / (4 * WE_HEAD_STRIDE));
+    a.heads = a.n_heads > 0 ? (uint32_t *)a.s_w : a.queue;
+    a.n_heads = std::max(a.n_heads, 1);
     s->rs_binfo = (int32_t *)at(P_RSB);
     a.n_joint = p->n_joint;
     a.joint_bins = p->n_joint > 0 ? p->joint_bins : 1;

@@ -12,6 +12,11 @@
 // which lane or wave runs a walker.
 #include "we_common.h"
 
+// The lane kernels' queue heads (a.queue[0] itself when there is only that).
+__device__ __forceinline__ void clear_heads(const SimArgs &a, int32_t tid) {
+    if (tid < a.n_heads) a.heads[tid * WE_HEAD_STRIDE] = 0u;
+}
+
 // Segments per bin: one thread per (run, segment).
 __global__ __launch_bounds__(256) void queue_count_kernel(SimArgs a) {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -186,6 +191,7 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
         a.queue[0] = 0u;
         a.queue[1] = (uint32_t)run;
     }
+    clear_heads(a, tid);
     __syncthreads();
     acc = part[wv] + incl - acc;
 #pragma unroll
@@ -274,6 +280,7 @@ __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
         a.queue[0] = 0u;
         a.queue[1] = (uint32_t)total;
     }
+    clear_heads(a, lane);
     __syncthreads();
     // the segment list, as queue_fill_kernel lays it out
     if (b >= 0) {
