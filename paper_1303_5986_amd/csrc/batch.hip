@@ -5,12 +5,15 @@
 // bars, Sec. IV), so a batch is a set of ordinary sims sharing one stream.
 // What is batched is the propagation: instead of one SSA launch per run --
 // each too small to fill 256 CUs when a run holds a few hundred walkers --
-// every kernel variant gets ONE persistent launch whose waves pull work
-// items (run, tile) from a device counter until the list is exhausted:
-//   lane variants: a tile is 64 consecutive walker slots, one per lane;
-//   group variants: a tile is 64 / L consecutive slots, L lanes each;
-//   wave variant:  a tile is one walker slot, one wave.
-// Items of cheap and expensive runs mix freely, so uneven runs balance
+// every kernel variant gets ONE persistent launch whose workgroups pull chunks
+// (a member, a run, a range of walker slots) until the list is exhausted.  A
+// workgroup copies its chunk's reaction tables to LDS when the member changes
+// and its waves then share the chunk's slots:
+//   lane variants: 64 slots per wave at a time, one per lane;
+//   group variants: 64 / L slots, L lanes each;
+//   wave variant:  one slot, one wave.
+// Chunks hold about equal work (slots times the work of a walker of their
+// network), the networks with the most reactions first, so uneven runs balance
 // across the chip.  The bookkeeping is batched the same way: recycle/bin,
 // resample (one workgroup per run of every member), gather, observe and the
 // iteration counters are one launch each, with the member index on grid y;
@@ -41,46 +44,46 @@
 
 namespace {
 
-// V_GROUPR_L: the group kernel with L lanes per walker for members whose
-// lane blocks hold at most BATCH_GROUP_REG reactions (descriptors and
-// propensities in registers, read once per walker and interval).
+// V_GROUP_L: the group kernel with L lanes per walker, the tables in LDS;
+// V_GROUPR_L: the same for members whose lane blocks hold at most
+// BATCH_GROUP_REG reactions (descriptors and propensities in registers);
+// V_GROUPG_L: tables read through the cache, for members whose tables take
+// more than BATCH_GROUP_TABLES bytes.  The order within a group is L = 2 .. 32.
 enum Variant {
     V_LANE_1_4 = 0, V_LANE_2_8, V_LANE_8_16, V_LANE_16_32,
-    V_GROUP_2, V_GROUP_4, V_GROUP_8, V_GROUP_16, V_GROUP_32,
-    V_GROUPR_2, V_GROUPR_4, V_GROUPR_8, V_GROUPR_16, V_GROUPR_32,
-    V_WAVE, V_COUNT
+    V_GROUP, V_GROUPR = V_GROUP + 5, V_GROUPG = V_GROUPR + 5,
+    V_WAVE = V_GROUPG + 5, V_COUNT
 };
 #define BATCH_GROUP_REG 8
+#define BATCH_GROUP_TABLES (48 * 1024)
+#define BATCH_WAVES 8                       // waves per workgroup of the wave variant, at most
+#define BATCH_LDS (160 * 1024)
+// Chunk counters per variant, on 128-byte lines of their own: one counter for
+// every walker tile bound the launches (an atomic on one address takes 11.4 ns).
+// Batch of 64 networks of 8 to 3680 reactions, by chunks with tables in LDS: wave
+// leg 706 -> 242 us, the three group legs 457 -> 107 us per step.
+#define BATCH_HEADS 8
 
-// Walker slots per work item of a variant.
-int32_t tile_of(int v) {
-    switch (v) {
-    case V_GROUP_2: case V_GROUPR_2: return 32;
-    case V_GROUP_4: case V_GROUPR_4: return 16;
-    case V_GROUP_8: case V_GROUPR_8: return 8;
-    case V_GROUP_16: case V_GROUPR_16: return 4;
-    case V_GROUP_32: case V_GROUPR_32: return 2;
-    case V_WAVE: return 1;
-    default: return 64;
-    }
+// Walker slots a workgroup works on at a time.
+int32_t slots_per_round(int v, int32_t waves) {
+    if (v == V_WAVE) return waves;
+    if (v >= V_GROUP) return 4 * (32 >> ((v - V_GROUP) % 5));
+    return 256;
 }
 
-struct Item {
-    int32_t sim, run, slot;
+struct Chunk {
+    int32_t sim, run, slot, n;
 };
 
 Variant variant_of(const we_sim *s) {
     const int32_t S = s->S, R = s->net->R;
     if (s->kernel == WE_KERNEL_WAVE) return V_WAVE;
     if (s->kernel == WE_KERNEL_GROUP) {
+        const bool lds = group_tables_bytes(R, s->args.n_chg) <= BATCH_GROUP_TABLES;
         const bool reg = (R + s->group_lanes - 1) / s->group_lanes <= BATCH_GROUP_REG;
-        switch (s->group_lanes) {
-        case 2: return reg ? V_GROUPR_2 : V_GROUP_2;
-        case 4: return reg ? V_GROUPR_4 : V_GROUP_4;
-        case 8: return reg ? V_GROUPR_8 : V_GROUP_8;
-        case 16: return reg ? V_GROUPR_16 : V_GROUP_16;
-        default: return reg ? V_GROUPR_32 : V_GROUP_32;
-        }
+        int32_t l = 0;
+        while ((2 << l) < s->group_lanes) ++l;
+        return (Variant)((lds ? reg ? V_GROUPR : V_GROUP : V_GROUPG) + l);
     }
     if (S <= 1 && R <= 4) return V_LANE_1_4;
     if (S <= 2 && R <= 8) return V_LANE_2_8;
@@ -91,96 +94,130 @@ Variant variant_of(const we_sim *s) {
 
 }  // namespace
 
+// The calling workgroup's next chunk, or -1: a static first one, then from its
+// counter (block b uses counter b mod BATCH_HEADS; chunks alternate between
+// the counters in list order).  Every thread calls it; on the way it waits for
+// the workgroup, so the tables in LDS may be replaced afterwards.
+__device__ __forceinline__ int32_t next_chunk(int32_t n_chunks, bool first, uint32_t *__restrict__ counters) {
+    __shared__ uint32_t got;
+    const uint32_t H = min((uint32_t)BATCH_HEADS, gridDim.x), s = blockIdx.x % H;
+    uint32_t i = blockIdx.x / H;
+    if (!first) {
+        __syncthreads();
+        if (threadIdx.x == 0) got = atomicAdd(counters + s * WE_HEAD_STRIDE, 1u);
+        __syncthreads();
+        i = (gridDim.x - s + H - 1) / H + got;
+    }
+    i = i * H + s;
+    return i < (uint32_t)n_chunks ? (int32_t)i : -1;
+}
+
 template <int SMAX, int RMAX>
 __global__ __launch_bounds__(256) void batch_lane_kernel(const SimArgs *__restrict__ args,
                                                          int32_t *const *__restrict__ xptr,
-                                                         const Item *__restrict__ items, int32_t n_items,
-                                                         uint32_t *__restrict__ counter) {
+                                                         const Chunk *__restrict__ chunks, int32_t n_chunks,
+                                                         uint32_t *__restrict__ counters) {
     constexpr bool REG = RMAX <= LANE_REG_RMAX;
     constexpr int ROWS = REG ? 1 : RMAX * LaneRow<SMAX>::W;
     __shared__ int32_t rows[4 * ROWS];
     int32_t *wrows = rows + (threadIdx.x >> 6) * ROWS;
-    const int lane = threadIdx.x & 63;
-    const uint32_t n_static = gridDim.x * (blockDim.x >> 6);
-    uint32_t idx = first_position();
-    for (;;) {
-        if (idx >= (uint32_t)n_items) break;
-        const Item it = items[idx];
-        const SimArgs &a = args[it.sim];
+    for (bool first = true;; first = false) {
+        const int32_t c = next_chunk(n_chunks, first, counters);
+        if (c < 0) break;
+        const Chunk ch = chunks[c];
+        const SimArgs &a = args[ch.sim];
         if constexpr (!REG) lane_stage_rows<SMAX>(a, wrows);
-        const int32_t k = it.slot + lane;
-        if (k < a.n_walk[it.run]) lane_walker<SMAX, RMAX>(a, xptr[it.sim], it.run, k, *a.iter_dev, wrows);
-        // every lane executes the atomic (lane 0 adds one): no lane takes a
-        // path of its own around the wave-wide steps of the walker
-        const uint32_t got = atomicAdd(counter, lane == 0 ? 1u : 0u);
-        idx = n_static + (uint32_t)__shfl((int)got, 0, 64);
+        const int32_t hi = min(ch.slot + ch.n, a.n_walk[ch.run]);
+        for (int32_t k = ch.slot + (int32_t)threadIdx.x; k < hi; k += 256)
+            lane_walker<SMAX, RMAX>(a, xptr[ch.sim], ch.run, k, *a.iter_dev, wrows);
     }
 }
 
-__global__ __launch_bounds__(256) void batch_wave_kernel(const SimArgs *__restrict__ args,
-                                                         int32_t *const *__restrict__ xptr,
-                                                         const Item *__restrict__ items, int32_t n_items,
-                                                         uint32_t *__restrict__ counter, int32_t s_pad) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    double *lchunk = reinterpret_cast<double *>(smem) + wv * 64;
-    int32_t *lx = reinterpret_cast<int32_t *>(smem + WAVE_WALKERS_PER_BLOCK * 64 * sizeof(double)) + wv * s_pad;
-    const uint32_t n_static = gridDim.x * (blockDim.x >> 6);
-    uint32_t idx = first_position();
-    for (;;) {
-        if (idx >= (uint32_t)n_items) break;
-        const Item it = items[idx];
-        const SimArgs &a = args[it.sim];
-        if (it.slot < a.n_walk[it.run]) wave_walker(a, xptr[it.sim], it.run, it.slot, *a.iter_dev, lchunk, lx);
+// Wave variant: descriptors in LDS (in the pair form where the member's
+// network has it), reaction headers, changes and dependency lists from global
+// memory.  Members' walkers fire few events per interval, so the chunk sums
+// from scratch at its start, 64 propensities per chunk, weigh most: with the
+// descriptors read through the cache, one slot per work item, the leg of the
+// 64-network batch took 706 us.
+template <class D>
+__device__ __forceinline__ void batch_wave_chunk(const SimArgs &a, const D *gdesc, const Chunk &ch, bool stage,
+                                                 int32_t *xs, unsigned char *smem, double *lchunk, int32_t *lx) {
+    if (stage) {
+        const uint4 *gd = reinterpret_cast<const uint4 *>(gdesc);
+        uint4 *ld = reinterpret_cast<uint4 *>(smem);
+        for (int32_t i = threadIdx.x; i < a.R; i += blockDim.x) ld[i] = gd[i];
+        __syncthreads();
+    }
+    LdsTables<D> tab;
+    tab.d = reinterpret_cast<const D *>(smem);
+    tab.h = a.rinfo;
+    tab.ids = a.dep;
+    const uint32_t iter = *a.iter_dev;
+    const int32_t hi = min(ch.slot + ch.n, a.n_walk[ch.run]);
+    for (int32_t k = ch.slot + (int32_t)(threadIdx.x >> 6); k < hi; k += (int32_t)(blockDim.x >> 6)) {
+        wave_walker_t(a, tab, xs, ch.run, k, iter, lchunk, lx);
         __builtin_amdgcn_wave_barrier();
-        // every lane executes the atomic (lane 0 adds one): no lane takes a
-        // path of its own around the wave-wide steps of the walker
-        const uint32_t got = atomicAdd(counter, lane == 0 ? 1u : 0u);
-        idx = n_static + (uint32_t)__shfl((int)got, 0, 64);
     }
 }
 
-// Group variant: a work item is 64 / L consecutive slots of one run, one
-// group of L lanes per slot; lx slices are s_max ints (the largest
-// group_slice among the members on this variant).  BR > 0: the members' lane
-// blocks hold at most BR reactions, kept in registers (group_walker).
-template <int L, int BR, class D>
-__device__ __forceinline__ void batch_group_item(const SimArgs &a, const D *desc, const Item &it, int32_t *xs, int32_t *lx,
-                                                 int grp) {
-    const int32_t k = it.slot + grp;
-    const bool live = k < a.cap && k < a.n_walk[it.run];
-    const GroupTables<D> tb{desc, a.chg_ptr, a.chg};
-    group_walker<L, BR, D>(a, tb, xs, it.run, k, live, *a.iter_dev, lx);
+__global__ __launch_bounds__(64 * BATCH_WAVES, 4) void batch_wave_kernel(const SimArgs *__restrict__ args,
+                                                                       int32_t *const *__restrict__ xptr,
+                                                                       const Chunk *__restrict__ chunks, int32_t n_chunks,
+                                                                       uint32_t *__restrict__ counters, int32_t s_pad,
+                                                                       int32_t tables) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    double *lchunk = reinterpret_cast<double *>(smem + tables) + wv * 64;
+    int32_t *lx = reinterpret_cast<int32_t *>(smem + tables + (size_t)nw * 64 * sizeof(double)) + wv * s_pad;
+    int32_t staged = -1;
+    for (bool first = true;; first = false) {
+        const int32_t c = next_chunk(n_chunks, first, counters);
+        if (c < 0) break;
+        const Chunk ch = chunks[c];
+        const SimArgs &a = args[ch.sim];
+        if (a.desc2) batch_wave_chunk(a, a.desc2, ch, staged != ch.sim, xptr[ch.sim], smem, lchunk, lx);
+        else batch_wave_chunk(a, a.desc, ch, staged != ch.sim, xptr[ch.sim], smem, lchunk, lx);
+        staged = ch.sim;
+    }
 }
 
-template <int L, int BR = 0>
+// Group variant: 64 / L consecutive slots per wave, one group of L lanes per
+// slot; slices of s_max ints (the largest group_slice among the members on
+// this variant).  BR > 0: the members' lane blocks hold at most BR reactions,
+// kept in registers (group_walker).  LT: the member's tables in LDS.
+template <int L, int BR, bool LT, class D>
+__device__ __forceinline__ void batch_group_chunk(const SimArgs &a, const D *gdesc, const Chunk &ch, bool stage,
+                                                  int32_t *xs, unsigned char *smem, int32_t *lx) {
+    constexpr int G = 64 / L;
+    GroupTables<D> tb{gdesc, a.chg_ptr, a.chg};
+    if constexpr (LT) tb = group_stage(a, gdesc, smem, stage);
+    const uint32_t iter = *a.iter_dev;
+    const int32_t hi = min(ch.slot + ch.n, a.n_walk[ch.run]);
+    for (int32_t k0 = ch.slot + (int32_t)(threadIdx.x >> 6) * G; k0 < hi; k0 += 4 * G) {
+        const int32_t k = k0 + (int32_t)(threadIdx.x & 63) / L;
+        group_walker<L, BR, D>(a, tb, xs, ch.run, k, k < hi, iter, lx);
+    }
+}
+
+template <int L, int BR, bool LT>
 __global__ __launch_bounds__(256) void batch_group_kernel(const SimArgs *__restrict__ args,
                                                           int32_t *const *__restrict__ xptr,
-                                                          const Item *__restrict__ items, int32_t n_items,
-                                                          uint32_t *__restrict__ counter, int32_t s_max) {
-    extern __shared__ int32_t bglds[];
+                                                          const Chunk *__restrict__ chunks, int32_t n_chunks,
+                                                          uint32_t *__restrict__ counters, int32_t s_max, int32_t tables) {
+    extern __shared__ __align__(16) unsigned char bgsm[];
     constexpr int G = 64 / L;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int grp = lane / L;
-    int32_t *lx = bglds + ((size_t)wv * G + grp) * s_max;
-    const uint32_t n_static = gridDim.x * (blockDim.x >> 6);
-    uint32_t idx = first_position();
-    for (;;) {
-        if (idx >= (uint32_t)n_items) break;
-        const Item it = items[idx];
-        const SimArgs &a = args[it.sim];
-        if (a.desc2) batch_group_item<L, BR>(a, a.desc2, it, xptr[it.sim], lx, grp);
-        else batch_group_item<L, BR>(a, a.desc, it, xptr[it.sim], lx, grp);
-        // every lane executes the atomic (lane 0 adds one): see batch_lane_kernel
-        const uint32_t got = atomicAdd(counter, lane == 0 ? 1u : 0u);
-        idx = n_static + (uint32_t)__shfl((int)got, 0, 64);
+    int32_t *lx = reinterpret_cast<int32_t *>(bgsm + tables) +
+                  ((size_t)(threadIdx.x >> 6) * G + (threadIdx.x & 63) / L) * s_max;
+    int32_t staged = -1;
+    for (bool first = true;; first = false) {
+        const int32_t c = next_chunk(n_chunks, first, counters);
+        if (c < 0) break;
+        const Chunk ch = chunks[c];
+        const SimArgs &a = args[ch.sim];
+        if (a.desc2) batch_group_chunk<L, BR, LT>(a, a.desc2, ch, staged != ch.sim, xptr[ch.sim], bgsm, lx);
+        else batch_group_chunk<L, BR, LT>(a, a.desc, ch, staged != ch.sim, xptr[ch.sim], bgsm, lx);
+        staged = ch.sim;
     }
-}
-
-__global__ void batch_reset_kernel(uint32_t *counters, int32_t n) {
-    const int32_t i = threadIdx.x;
-    if (i < n) counters[i] = 0u;
 }
 
 struct BatchPtrs {
@@ -194,7 +231,7 @@ struct BatchPtrs {
 };
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
                                     int64_t max_cells, size_t shmem, bool observe, const CmBatchModel *models,
-                                    int32_t s_max_cm, hipStream_t st);
+                                    int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st);
 bool resample_uses_lds(const SimArgs &a);
 size_t resample_lds_bytes(const SimArgs &a, bool use_lds);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
@@ -203,9 +240,13 @@ struct we_batch {
     hipStream_t stream = nullptr;
     std::vector<we_sim *> sims;
     std::vector<Variant> var;
-    std::vector<Item> items[V_COUNT];
-    Item *d_items[V_COUNT] = {};
-    uint32_t *d_counters = nullptr;
+    // per variant: its chunks, dynamic LDS bytes (tables in front) and workgroups
+    int32_t n_chunks[V_COUNT] = {};
+    Chunk *d_chunks[V_COUNT] = {};
+    size_t shmem[V_COUNT] = {};
+    int32_t tables[V_COUNT] = {}, s_max[V_COUNT] = {}, blocks[V_COUNT] = {};
+    int32_t wave_waves = BATCH_WAVES;  // waves per workgroup of the wave variant
+    uint32_t *d_counters = nullptr;    // [V_COUNT][BATCH_HEADS], WE_HEAD_STRIDE words apart; zero between iterations
     SimArgs *d_args = nullptr;
     int32_t **d_xptr[2] = {nullptr, nullptr};
     double **d_wptr[2] = {nullptr, nullptr};
@@ -214,9 +255,8 @@ struct we_batch {
     int32_t max_runs = 0;
     size_t resample_shmem = 0;
     bool observe = false;
-    int32_t s_pad = 4;
-    int32_t s_group = 1;              // largest group_slice among group-kernel members
     int32_t iter = 0, max_iters = 0;
+    int32_t s_pad = 4;                // largest species count, padded
     hipGraphExec_t graph_exec = nullptr;
     hipStream_t capture_stream = nullptr;
     int32_t graph_iters = 0;
@@ -312,21 +352,87 @@ void write_cache(const char *path, const std::map<std::string, int> &m) {
     f << "\n}\n";
 }
 
-we_status build_items(we_batch *b) {
-    for (int v = 0; v < V_COUNT; ++v) b->items[v].clear();
-    for (size_t i = 0; i < b->sims.size(); ++i) {
-        we_sim *s = b->sims[i];
-        const Variant v = b->var[i];
-        const int32_t step = tile_of(v);
-        for (int32_t r = 0; r < s->n_runs; ++r)
-            for (int32_t k = 0; k < s->cap; k += step) b->items[v].push_back(Item{(int32_t)i, r, k});
-    }
+// Work of one walker of a member, in units of a wave's time: the chunk sums (or
+// the lane blocks) it evaluates and a constant for the rest.
+double walker_cost(int v, const we_sim *s) {
+    if (v == V_WAVE) return s->net->R / 64.0 + 16.0;
+    if (v >= V_GROUP) return (double)((s->net->R + s->group_lanes - 1) / s->group_lanes) + 8.0;
+    return s->net->R + 8.0;
+}
+
+using ChunkKernel = void (*)(const SimArgs *, int32_t *const *, const Chunk *, int32_t, uint32_t *);
+using TableKernel = void (*)(const SimArgs *, int32_t *const *, const Chunk *, int32_t, uint32_t *, int32_t, int32_t);
+
+ChunkKernel lane_kernel_of(int v) {
+    return v == V_LANE_1_4 ? batch_lane_kernel<1, 4> : v == V_LANE_2_8 ? batch_lane_kernel<2, 8>
+           : v == V_LANE_8_16 ? batch_lane_kernel<8, 16> : batch_lane_kernel<16, 32>;
+}
+
+template <int BR, bool LT>
+TableKernel group_kernel_of(int l) {
+    return l == 0 ? batch_group_kernel<2, BR, LT> : l == 1 ? batch_group_kernel<4, BR, LT>
+           : l == 2 ? batch_group_kernel<8, BR, LT> : l == 3 ? batch_group_kernel<16, BR, LT>
+                                                             : batch_group_kernel<32, BR, LT>;
+}
+
+TableKernel table_kernel_of(int v) {
+    if (v == V_WAVE) return batch_wave_kernel;
+    const int l = (v - V_GROUP) % 5;
+    return v < V_GROUPR ? group_kernel_of<0, true>(l) : v < V_GROUPG ? group_kernel_of<BATCH_GROUP_REG, true>(l)
+                                                                      : group_kernel_of<0, false>(l);
+}
+
+// The variants' LDS, workgroups and chunk lists.  About BATCH_CHUNKS chunks of
+// equal work per resident workgroup: enough to balance, few enough that the
+// tables are copied and the waves of a workgroup waited for seldom.
+#define BATCH_CHUNKS 4
+we_status build_chunks(we_batch *b) {
+    int dev = 0, cus = 1;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     for (int v = 0; v < V_COUNT; ++v) {
-        if (b->d_items[v]) { (void)hipFree(b->d_items[v]); b->d_items[v] = nullptr; }
-        if (b->items[v].empty()) continue;
-        HIP_TRY(hipMalloc(&b->d_items[v], sizeof(Item) * b->items[v].size()));
-        HIP_TRY(hipMemcpy(b->d_items[v], b->items[v].data(), sizeof(Item) * b->items[v].size(),
-                          hipMemcpyHostToDevice));
+        std::vector<int32_t> of;       // members, most reactions first
+        for (size_t i = 0; i < b->sims.size(); ++i)
+            if (b->var[i] == v) of.push_back((int32_t)i);
+        if (of.empty()) continue;
+        std::stable_sort(of.begin(), of.end(), [&](int32_t x, int32_t y) { return b->sims[x]->net->R > b->sims[y]->net->R; });
+        int threads = 256;
+        if (v >= V_GROUP) {
+            for (int32_t i : of) {
+                const we_sim *s = b->sims[i];
+                const size_t t = v == V_WAVE ? 16 * (size_t)s->net->R
+                                 : v < V_GROUPG ? group_tables_bytes(s->net->R, s->args.n_chg) : 0;
+                b->tables[v] = std::max(b->tables[v], (int32_t)((t + 15) & ~(size_t)15));
+                b->s_max[v] = std::max(b->s_max[v], v == V_WAVE ? (s->S + 4) & ~3 : group_slice(s->S));
+            }
+            if (v == V_WAVE) {
+                const size_t per = 64 * sizeof(double) + sizeof(int32_t) * (size_t)b->s_max[v];
+                b->wave_waves = (int32_t)std::min<size_t>(BATCH_WAVES, (BATCH_LDS - b->tables[v]) / per);
+                b->shmem[v] = b->tables[v] + b->wave_waves * per;
+                threads = 64 * b->wave_waves;
+            } else {
+                b->shmem[v] = b->tables[v] + sizeof(int32_t) * (size_t)slots_per_round(v, 0) * b->s_max[v];
+            }
+        }
+        const int32_t round = slots_per_round(v, b->wave_waves);
+        int per_cu = 0;
+        const void *fn = v < V_GROUP ? (const void *)lane_kernel_of(v) : (const void *)table_kernel_of(v);
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, b->shmem[v]) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        double total = 0.0;
+        for (int32_t i : of) total += walker_cost(v, b->sims[i]) * b->sims[i]->n_runs * b->sims[i]->cap;
+        const double aim = total / ((double)BATCH_CHUNKS * per_cu * cus);
+        std::vector<Chunk> ch;
+        for (int32_t i : of) {
+            const we_sim *s = b->sims[i];
+            const int32_t n = (int32_t)std::max(1.0, std::min(aim / walker_cost(v, s) / round, 1e6)) * round;
+            for (int32_t r = 0; r < s->n_runs; ++r)
+                for (int32_t k = 0; k < s->cap; k += n) ch.push_back(Chunk{i, r, k, std::min(n, s->cap - k)});
+        }
+        b->n_chunks[v] = (int32_t)ch.size();
+        b->blocks[v] = (int32_t)std::min<int64_t>(b->n_chunks[v], (int64_t)per_cu * cus);
+        HIP_TRY(hipMalloc(&b->d_chunks[v], sizeof(Chunk) * ch.size()));
+        HIP_TRY(hipMemcpy(b->d_chunks[v], ch.data(), sizeof(Chunk) * ch.size(), hipMemcpyHostToDevice));
     }
     return WE_OK;
 }
@@ -373,71 +479,16 @@ we_status launch_batch_iteration(we_batch *b, hipStream_t st, bool capture) {
         if (r != WE_OK) return r;
     }
     const int32_t parity = b->sims[0]->cur;
-    hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(64), 0, st, b->d_counters, (int32_t)V_COUNT);
-    HIP_TRY(hipGetLastError());
     int32_t *const *xp = b->d_xptr[parity];
     for (int v = 0; v < V_COUNT; ++v) {
-        const int32_t n = (int32_t)b->items[v].size();
-        if (n == 0) continue;
-        const unsigned blocks = (unsigned)std::min<int64_t>((n + 3) / 4, 2048);
-        uint32_t *cnt = b->d_counters + v;
-        switch (v) {
-        case V_LANE_1_4:
-            hipLaunchKernelGGL((batch_lane_kernel<1, 4>), dim3(blocks), dim3(256), 0, st, b->d_args, xp, b->d_items[v], n, cnt);
-            break;
-        case V_LANE_2_8:
-            hipLaunchKernelGGL((batch_lane_kernel<2, 8>), dim3(blocks), dim3(256), 0, st, b->d_args, xp, b->d_items[v], n, cnt);
-            break;
-        case V_LANE_8_16:
-            hipLaunchKernelGGL((batch_lane_kernel<8, 16>), dim3(blocks), dim3(256), 0, st, b->d_args, xp, b->d_items[v], n, cnt);
-            break;
-        case V_LANE_16_32:
-            hipLaunchKernelGGL((batch_lane_kernel<16, 32>), dim3(blocks), dim3(256), 0, st, b->d_args, xp, b->d_items[v], n, cnt);
-            break;
-        case V_GROUPR_2:
-        case V_GROUPR_4:
-        case V_GROUPR_8:
-        case V_GROUPR_16:
-        case V_GROUPR_32: {
-            const int32_t G = tile_of(v);
-            const size_t shmem = sizeof(int32_t) * 4 * (size_t)G * b->s_group;
-            if (v == V_GROUPR_2)
-                hipLaunchKernelGGL((batch_group_kernel<2, BATCH_GROUP_REG>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUPR_4)
-                hipLaunchKernelGGL((batch_group_kernel<4, BATCH_GROUP_REG>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUPR_8)
-                hipLaunchKernelGGL((batch_group_kernel<8, BATCH_GROUP_REG>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUPR_16)
-                hipLaunchKernelGGL((batch_group_kernel<16, BATCH_GROUP_REG>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else
-                hipLaunchKernelGGL((batch_group_kernel<32, BATCH_GROUP_REG>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            break;
-        }
-        case V_GROUP_2:
-        case V_GROUP_4:
-        case V_GROUP_8:
-        case V_GROUP_16:
-        case V_GROUP_32: {
-            const int32_t G = tile_of(v);
-            const size_t shmem = sizeof(int32_t) * 4 * (size_t)G * b->s_group;
-            if (v == V_GROUP_2)
-                hipLaunchKernelGGL((batch_group_kernel<2>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUP_4)
-                hipLaunchKernelGGL((batch_group_kernel<4>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUP_8)
-                hipLaunchKernelGGL((batch_group_kernel<8>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else if (v == V_GROUP_16)
-                hipLaunchKernelGGL((batch_group_kernel<16>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            else
-                hipLaunchKernelGGL((batch_group_kernel<32>), dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v], n, cnt, b->s_group);
-            break;
-        }
-        default: {
-            const size_t shmem = WAVE_WALKERS_PER_BLOCK * (64 * sizeof(double) + sizeof(int32_t) * (size_t)b->s_pad);
-            hipLaunchKernelGGL(batch_wave_kernel, dim3(blocks), dim3(256), shmem, st, b->d_args, xp, b->d_items[v],
-                               n, cnt, b->s_pad);
-        }
-        }
+        if (b->n_chunks[v] == 0) continue;
+        const dim3 grid((unsigned)b->blocks[v]);
+        uint32_t *cnt = b->d_counters + (size_t)v * BATCH_HEADS * WE_HEAD_STRIDE;
+        if (v < V_GROUP)
+            hipLaunchKernelGGL(lane_kernel_of(v), grid, dim3(256), 0, st, b->d_args, xp, b->d_chunks[v], b->n_chunks[v], cnt);
+        else
+            hipLaunchKernelGGL(table_kernel_of(v), grid, dim3(v == V_WAVE ? 64 * b->wave_waves : 256), b->shmem[v], st,
+                               b->d_args, xp, b->d_chunks[v], b->n_chunks[v], cnt, b->s_max[v], b->tables[v]);
         HIP_TRY(hipGetLastError());
     }
     // recycle/bin, committor bins where active, resample, gather, observe,
@@ -447,7 +498,7 @@ we_status launch_batch_iteration(we_batch *b, hipStream_t st, bool capture) {
                  b->d_grid_bins};
     HIP_TRY(launch_batch_bookkeeping(bp, (int32_t)b->sims.size(), b->max_slots, b->max_runs, b->max_cells,
                                      b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
-                                     b->s_max_cm, st));
+                                     b->s_max_cm, b->d_counters, V_COUNT * BATCH_HEADS, st));
     for (we_sim *s : b->sims) s->cur = 1 - s->cur;
     if (!capture)
         for (we_sim *s : b->sims) HIP_TRY(committor_record(s, st));
@@ -528,11 +579,10 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         b->sims.push_back(s);
         b->var.push_back(variant_of(s));
         b->s_pad = std::max(b->s_pad, (S + 3) & ~3);
-        if (s->kernel == WE_KERNEL_GROUP) b->s_group = std::max(b->s_group, group_slice(S));
         b->max_iters = (i == 0) ? s->max_iters : std::min(b->max_iters, s->max_iters);
     }
     if (cache_dirty) write_cache(cache_path, cache);
-    if ((size_t)WAVE_WALKERS_PER_BLOCK * (64 * sizeof(double) + 4 * (size_t)b->s_pad) > 64 * 1024) {
+    if (4 * (64 * sizeof(double) + 4 * (size_t)b->s_pad) > 64 * 1024) {
         we_batch_destroy(b);
         return we_fail(WE_EINVAL, "species count too large for the batched wave kernel");
     }
@@ -578,8 +628,10 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
     HIP_TRY(hipMalloc(&b->d_xptr[1], sizeof(int32_t *) * n));
     HIP_TRY(hipMemcpy(b->d_xptr[0], xp0.data(), sizeof(int32_t *) * n, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(b->d_xptr[1], xp1.data(), sizeof(int32_t *) * n, hipMemcpyHostToDevice));
-    HIP_TRY(hipMalloc(&b->d_counters, sizeof(uint32_t) * V_COUNT));
-    we_status r = build_items(b);
+    HIP_TRY(hipMalloc(&b->d_counters, sizeof(uint32_t) * V_COUNT * BATCH_HEADS * WE_HEAD_STRIDE));
+    HIP_TRY(hipMemset(b->d_counters, 0, sizeof(uint32_t) * V_COUNT * BATCH_HEADS * WE_HEAD_STRIDE));
+    HIP_TRY(hipDeviceSynchronize());
+    we_status r = build_chunks(b);
     if (r != WE_OK) { we_batch_destroy(b); return r; }
     *out = b;
     return WE_OK;
@@ -669,7 +721,7 @@ extern "C" void we_batch_destroy(we_batch *b) {
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     for (we_sim *s : b->sims) we_destroy(s);
-    for (int v = 0; v < V_COUNT; ++v) (void)hipFree(b->d_items[v]);
+    for (int v = 0; v < V_COUNT; ++v) (void)hipFree(b->d_chunks[v]);
     (void)hipFree(b->d_counters);
     (void)hipFree(b->d_args);
     (void)hipFree(b->d_xptr[0]);

@@ -18,12 +18,6 @@
 
 #define GROUP_WAVES 4
 
-// LDS copy of the network tables (descriptors, change offsets, changes),
-// 16-byte aligned, in front of the walkers' counts.
-__host__ __device__ inline size_t group_tables_bytes(int32_t R, int32_t n_chg) {
-    return (16 * (size_t)R + 4 * ((size_t)R + 1 + (size_t)n_chg) + 15) & ~(size_t)15;
-}
-
 template <int L, bool LT, int BR, class D>
 __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, int32_t *__restrict__ xs) {
     extern __shared__ __align__(16) unsigned char gsm[];
@@ -36,19 +30,8 @@ __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, 
     GroupTables<D> tb{gdesc, a.chg_ptr, a.chg};
     size_t off = 0;
     if constexpr (LT) {
-        const int32_t R = a.R;
-        uint4 *ld = reinterpret_cast<uint4 *>(gsm);
-        int32_t *lcp = reinterpret_cast<int32_t *>(gsm + 16 * (size_t)R);
-        int32_t *lcg = lcp + R + 1;
-        const uint4 *gd = reinterpret_cast<const uint4 *>(gdesc);
-        for (int32_t i = threadIdx.x; i < R; i += blockDim.x) ld[i] = gd[i];
-        for (int32_t i = threadIdx.x; i <= R; i += blockDim.x) lcp[i] = a.chg_ptr[i];
-        for (int32_t i = threadIdx.x; i < a.n_chg; i += blockDim.x) lcg[i] = a.chg[i];
-        __syncthreads();
-        tb.desc = reinterpret_cast<const D *>(ld);
-        tb.chg_ptr = lcp;
-        tb.chg = lcg;
-        off = group_tables_bytes(R, a.n_chg);
+        tb = group_stage(a, gdesc, gsm, true);
+        off = group_tables_bytes(a.R, a.n_chg);
     }
     int32_t *lx = reinterpret_cast<int32_t *>(gsm + off) + ((size_t)wv * G + grp) * group_slice(a.S);
     const uint32_t iter = *a.iter_dev;

@@ -89,6 +89,30 @@ struct GroupTables {
     const int32_t *chg;
 };
 
+// LDS copy of the network tables (descriptors, change offsets, changes),
+// 16-byte aligned.
+__host__ __device__ inline size_t group_tables_bytes(int32_t R, int32_t n_chg) {
+    return (16 * (size_t)R + 4 * ((size_t)R + 1 + (size_t)n_chg) + 15) & ~(size_t)15;
+}
+
+// The block's LDS copy of the tables at `lds`; copies them there first when
+// `stage` is set (every thread of the block calls it; uniform).
+template <class D>
+__device__ __forceinline__ GroupTables<D> group_stage(const SimArgs &a, const D *gdesc, unsigned char *lds, bool stage) {
+    const int32_t R = a.R;
+    uint4 *ld = reinterpret_cast<uint4 *>(lds);
+    int32_t *lcp = reinterpret_cast<int32_t *>(lds + 16 * (size_t)R);
+    int32_t *lcg = lcp + R + 1;
+    if (stage) {
+        const uint4 *gd = reinterpret_cast<const uint4 *>(gdesc);
+        for (int32_t i = threadIdx.x; i < R; i += blockDim.x) ld[i] = gd[i];
+        for (int32_t i = threadIdx.x; i <= R; i += blockDim.x) lcp[i] = a.chg_ptr[i];
+        for (int32_t i = threadIdx.x; i < a.n_chg; i += blockDim.x) lcg[i] = a.chg[i];
+        __syncthreads();
+    }
+    return GroupTables<D>{reinterpret_cast<const D *>(ld), lcp, lcg};
+}
+
 // The walkers in slots k of run `run` for the groups with live set (k may
 // differ per group); lx is this group's slice of S + 1 ints in LDS (the counts,
 // and the 1 that an absent reactant of a RxnDesc2 reads).  Every lane of the

@@ -9,17 +9,15 @@
 //  * broadcasts of one lane: v_readlane;
 //  * the dependents' propensity changes go into the per-wave chunk sums in
 //    LDS by ds_add_f64, one instruction per round of 64 dependents.
-// Per event the dependent loads from global memory are: the descriptors of
-// the chosen chunk (64 lanes, one 16-byte load each), then one packed
-// header of the chosen reaction, then its dependency entries (each carrying
-// the descriptor of the reaction it names) together with its changes.
+// Per event the dependent loads from global memory are: the chosen chunk's
+// reaction headers (unless they are in LDS), then the fired reaction's
+// dependency ids together with its changes.
 #pragma once
 #include <type_traits>
 
 #include "queue_first.h"
 #include "we_common.h"
 
-#define WAVE_WALKERS_PER_BLOCK 4
 #define WAVE_DEP_ROUNDS 2
 
 namespace {
@@ -160,22 +158,9 @@ __device__ __forceinline__ void add_chunk_deltas(double *lchunk, int rr, double 
 }  // namespace
 
 // Where the wave reads the network from.
-//  GlobalTables: descriptors, reaction headers and dependency entries (each
-//    with its reaction's descriptor inline) from global memory;
 //  LdsTables: descriptors from the block's LDS copy, headers from LDS or
 //    global memory, the dependency lists (16-bit reaction ids) from global
 //    memory and the dependents' descriptors from LDS.
-struct GlobalTables {
-    using Dep = DepEntry;
-    static constexpr bool PAIR = false;
-    const RxnDesc *__restrict__ d;
-    const RxnInfo *__restrict__ h;
-    const DepEntry *__restrict__ e;
-    __device__ __forceinline__ RxnDesc desc(int r) const { return d[r]; }
-    __device__ __forceinline__ RxnInfo info(int j) const { return h[j]; }
-    __device__ __forceinline__ DepEntry dep(int i) const { return e[i]; }
-};
-
 // D: the descriptors' form (RxnDesc2 where the network has it).
 template <class D>
 struct LdsTables {
@@ -334,13 +319,4 @@ __device__ inline void wave_walker_t(const SimArgs &a, const T &tab, int32_t *__
     __builtin_amdgcn_wave_barrier();
     for (int s = lane; s < S; s += 64) xw[s] = lx[s];
     if (lane == 0) a.ev_walker[(size_t)run * a.cap + k] = fired;
-}
-
-__device__ inline void wave_walker(const SimArgs &a, int32_t *__restrict__ xs, int32_t run, int32_t k,
-                                   uint32_t iter, double *lchunk, int32_t *lx) {
-    GlobalTables tab;
-    tab.d = a.desc;
-    tab.h = a.rinfo;
-    tab.e = a.deps;
-    wave_walker_t(a, tab, xs, run, k, iter, lchunk, lx);
 }

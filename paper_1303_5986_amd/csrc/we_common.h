@@ -70,15 +70,6 @@ struct __align__(16) RxnInfo {
     int32_t dep_begin, dep_count, chg_begin, chg_count;
 };
 
-// One reaction whose propensity changes when a given reaction fires, with
-// its own descriptor inline (so no second lookup is needed).
-struct __align__(16) DepEntry {
-    double c;
-    uint16_t s1, s2;
-    uint8_t nu1, nu2;
-    uint16_t r;
-};
-
 // Species change of a reaction, packed as (species << 16) | (delta & 0xffff).
 __host__ __device__ inline int32_t pack_change(int32_t s, int32_t d) {
     return (int32_t)(((uint32_t)s << 16) | ((uint32_t)d & 0xffffu));
@@ -136,7 +127,6 @@ struct SimArgs {
     const int32_t *__restrict__ dep_ptr; // [R+1] reactions whose propensity a reaction changes
     const uint16_t *__restrict__ dep;    //       (sorted, unique)
     const RxnInfo *__restrict__ rinfo;   // [R]
-    const DepEntry *__restrict__ deps;   // dependency entries with descriptors
     const RxnDesc2 *__restrict__ desc2;  // [R padded] (null: some reaction takes three molecules)
     const HillDesc *__restrict__ hill;   // [R padded] Hill-type rates (null: none)
     const uint2 *__restrict__ fhdr;      // [R] factored change headers (null: network too large)

@@ -32,7 +32,6 @@ struct we_network {
     int32_t *d_chg_ptr = nullptr, *d_chg = nullptr, *d_dep_ptr = nullptr;
     uint16_t *d_dep = nullptr;
     RxnInfo *d_rinfo = nullptr;
-    DepEntry *d_deps = nullptr;
     int32_t *d_dpack = nullptr;     // [R][WE_DPACK_WORDS] int8 deltas (species < 32)
     std::vector<uint2> fhdr;        // factored change headers (empty: do not fit)
     std::vector<uint32_t> inc_tab;  // per species: incidence start | count << 16

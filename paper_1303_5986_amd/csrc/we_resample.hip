@@ -1252,9 +1252,11 @@ __global__ __launch_bounds__(256) void we_batch_observe_kernel(BatchPtrs b) {
     observe_one(a, b.x_nxt[i], b.w_nxt[i], (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-__global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n) {
+// Also clears the propagation's chunk counters for the next iteration.
+__global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n, uint32_t *__restrict__ counters, int32_t n_counters) {
     const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) *b.args[i].iter_dev += 1u;
+    if (i < n_counters) counters[(size_t)i * WE_HEAD_STRIDE] = 0u;
 }
 
 // Workgroups per member in the batched gather (each strides over its member's
@@ -1263,7 +1265,7 @@ __global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n) {
 
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
                                     int64_t max_cells, size_t shmem, bool observe, const CmBatchModel *models,
-                                    int32_t s_max_cm, hipStream_t st) {
+                                    int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st) {
     const unsigned gs = (unsigned)((max_slots + 255) / 256);
     hipLaunchKernelGGL(we_batch_recycle_bin_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
     if (models) {
@@ -1275,7 +1277,8 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
     const unsigned gg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_cells + 255) / 256, BATCH_GATHER_BLOCKS));
     hipLaunchKernelGGL(we_batch_gather_kernel, dim3(gg, n_sims), dim3(256), 0, st, b);
     if (observe) hipLaunchKernelGGL(we_batch_observe_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
-    hipLaunchKernelGGL(we_batch_advance_kernel, dim3((n_sims + 63) / 64), dim3(64), 0, st, b, n_sims);
+    hipLaunchKernelGGL(we_batch_advance_kernel, dim3((std::max(n_sims, n_counters) + 63) / 64), dim3(64), 0, st, b, n_sims,
+                       counters, n_counters);
     return hipGetLastError();
 }
 

@@ -200,14 +200,9 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
         }
     }
     std::vector<RxnInfo> rinfo(R);
-    std::vector<DepEntry> deps;
     for (int32_t j = 0; j < R; ++j) {
         rinfo[j] = RxnInfo{net->dep_ptr[j], net->dep_ptr[j + 1] - net->dep_ptr[j], chg_ptr[j],
                            chg_ptr[j + 1] - chg_ptr[j]};
-        for (int32_t p = net->dep_ptr[j]; p < net->dep_ptr[j + 1]; ++p) {
-            const RxnDesc &d = net->desc[net->dep[p]];
-            deps.push_back(DepEntry{d.c, d.s1, d.s2, d.nu1, d.nu2, net->dep[p]});
-        }
     }
     // int8 delta rows for the lane kernel (species 0..31; bytes stay zero
     // for other species, and the lane kernel is not used when S > 32)
@@ -220,7 +215,6 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
                 wd |= ((uint32_t)dl & 0xFFu) << (8 * (sp % 4));
             }
         }
-    if (deps.empty()) deps.push_back(DepEntry{});
     if (net->dep.empty()) net->dep.push_back(0);
     if (net->chg.empty()) net->chg.push_back(0);
     auto up = [&](void **dst, const void *src, size_t bytes) -> hipError_t {
@@ -254,7 +248,6 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
     if (e == hipSuccess) e = up((void **)&net->d_dep_ptr, net->dep_ptr.data(), 4 * (R + 1));
     if (e == hipSuccess) e = up((void **)&net->d_dep, net->dep.data(), 2 * net->dep.size());
     if (e == hipSuccess) e = up((void **)&net->d_rinfo, rinfo.data(), sizeof(RxnInfo) * R);
-    if (e == hipSuccess) e = up((void **)&net->d_deps, deps.data(), sizeof(DepEntry) * deps.size());
     if (e == hipSuccess) e = up((void **)&net->d_dpack, dpack.data(), 4 * dpack.size());
     if (e == hipSuccess && !net->fhdr.empty()) {
         e = up((void **)&net->d_fhdr, net->fhdr.data(), sizeof(uint2) * net->fhdr.size());
@@ -316,7 +309,6 @@ extern "C" void we_destroy_network(we_network *net) {
     (void)hipFree(net->d_dep_ptr);
     (void)hipFree(net->d_dep);
     (void)hipFree(net->d_rinfo);
-    (void)hipFree(net->d_deps);
     (void)hipFree(net->d_dpack);
     delete net;
 }
@@ -559,7 +551,7 @@ extern "C" we_status we_init(const we_network *net, const we_grid *g, const we_p
     SimArgs &a = s->args;
     a.desc = net->d_desc; a.chg_ptr = net->d_chg_ptr; a.chg = net->d_chg; a.dpack = net->d_dpack;
     a.dep_ptr = net->d_dep_ptr; a.dep = net->d_dep;
-    a.rinfo = net->d_rinfo; a.deps = net->d_deps;
+    a.rinfo = net->d_rinfo;
     a.desc2 = net->d_desc2;
     a.hill = hill ? net->d_hill : nullptr;
     a.fhdr = net->d_fhdr;
