@@ -15,7 +15,8 @@
 // Chunks hold about equal work (slots times the work of a walker of their
 // network), the networks with the most reactions first, so uneven runs balance
 // across the chip.  The bookkeeping is batched the same way: recycle/bin,
-// resample (one workgroup per run of every member), gather, observe and the
+// resample (placement by one workgroup per run of every member, then one wave
+// per bin), gather, observe and the
 // iteration counters are one launch each, with the member index on grid y;
 // a member's arguments and buffers are read from device tables.  The whole
 // iteration can be captured as a HIP graph (the work counters are cleared
@@ -226,13 +227,14 @@ struct BatchPtrs {
     int32_t *const *x_nxt;
     const double *const *w_cur;
     double *const *w_nxt;
-    const int32_t *use_lds;
+    int32_t *const *binfo;
     const int32_t *grid_bins;
 };
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
-                                    int64_t max_cells, size_t shmem, bool observe, const CmBatchModel *models,
+                                    int64_t max_cells, int32_t max_bins, uint32_t m_sizes, size_t shmem, bool observe,
+                                    const CmBatchModel *models,
                                     int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st);
-bool resample_uses_lds(const SimArgs &a);
+uint32_t resample_m_size(int32_t m);
 size_t resample_lds_bytes(const SimArgs &a, bool use_lds);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
 
@@ -250,9 +252,11 @@ struct we_batch {
     SimArgs *d_args = nullptr;
     int32_t **d_xptr[2] = {nullptr, nullptr};
     double **d_wptr[2] = {nullptr, nullptr};
-    int32_t *d_use_lds = nullptr, *d_grid_bins = nullptr;
+    int32_t **d_binfo = nullptr;
+    int32_t *d_grid_bins = nullptr;
     int64_t max_slots = 0, max_cells = 0;
-    int32_t max_runs = 0;
+    int32_t max_runs = 0, max_bins = 0;
+    uint32_t m_sizes = 0;
     size_t resample_shmem = 0;
     bool observe = false;
     int32_t iter = 0, max_iters = 0;
@@ -494,10 +498,10 @@ we_status launch_batch_iteration(we_batch *b, hipStream_t st, bool capture) {
     // recycle/bin, committor bins where active, resample, gather, observe,
     // advance: one launch per step for all members
     BatchPtrs bp{b->d_args, b->d_xptr[parity], b->d_xptr[1 - parity],
-                 (const double *const *)b->d_wptr[parity], b->d_wptr[1 - parity], b->d_use_lds,
+                 (const double *const *)b->d_wptr[parity], b->d_wptr[1 - parity], b->d_binfo,
                  b->d_grid_bins};
     HIP_TRY(launch_batch_bookkeeping(bp, (int32_t)b->sims.size(), b->max_slots, b->max_runs, b->max_cells,
-                                     b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
+                                     b->max_bins, b->m_sizes, b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
                                      b->s_max_cm, b->d_counters, V_COUNT * BATCH_HEADS, st));
     for (we_sim *s : b->sims) s->cur = 1 - s->cur;
     if (!capture)
@@ -589,7 +593,8 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
     std::vector<SimArgs> args;
     std::vector<int32_t *> xp0, xp1;
     std::vector<double *> wp0, wp1;
-    std::vector<int32_t> use_lds, grid_bins;
+    std::vector<int32_t *> binfo;
+    std::vector<int32_t> grid_bins;
     int32_t runs_hi = 0;
     for (we_sim *s : b->sims) runs_hi = std::max(runs_hi, s->n_runs);
     for (we_sim *s : b->sims) {
@@ -601,10 +606,11 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         xp1.push_back(s->x[1]);
         wp0.push_back(s->w[0]);
         wp1.push_back(s->w[1]);
-        const bool ul = resample_uses_lds(s->args);
-        use_lds.push_back(ul ? 1 : 0);
+        binfo.push_back(s->rs_binfo);
         grid_bins.push_back(1);
-        b->resample_shmem = std::max(b->resample_shmem, resample_lds_bytes(args.back(), ul));
+        b->resample_shmem = std::max(b->resample_shmem, resample_lds_bytes(args.back(), false));
+        b->max_bins = std::max(b->max_bins, s->NB);
+        b->m_sizes |= resample_m_size(s->M);
         b->max_slots = std::max<int64_t>(b->max_slots, (int64_t)s->n_runs * s->cap);
         b->max_cells = std::max<int64_t>(b->max_cells, (int64_t)s->n_runs * s->cap * s->S);
         b->max_runs = std::max(b->max_runs, s->n_runs);
@@ -618,9 +624,9 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
     b->cm_host.assign(n, CmBatchModel{});
     b->grid_bins_host.assign(n, 1);
     HIP_TRY(hipMemcpy(b->d_models, b->cm_host.data(), sizeof(CmBatchModel) * n, hipMemcpyHostToDevice));
-    HIP_TRY(hipMalloc(&b->d_use_lds, sizeof(int32_t) * n));
+    HIP_TRY(hipMalloc(&b->d_binfo, sizeof(int32_t *) * n));
     HIP_TRY(hipMalloc(&b->d_grid_bins, sizeof(int32_t) * n));
-    HIP_TRY(hipMemcpy(b->d_use_lds, use_lds.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(b->d_binfo, binfo.data(), sizeof(int32_t *) * n, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(b->d_grid_bins, grid_bins.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice));
     HIP_TRY(hipMalloc(&b->d_args, sizeof(SimArgs) * n));
     HIP_TRY(hipMemcpy(b->d_args, args.data(), sizeof(SimArgs) * n, hipMemcpyHostToDevice));
@@ -728,7 +734,7 @@ extern "C" void we_batch_destroy(we_batch *b) {
     (void)hipFree(b->d_xptr[1]);
     (void)hipFree(b->d_wptr[0]);
     (void)hipFree(b->d_wptr[1]);
-    (void)hipFree(b->d_use_lds);
+    (void)hipFree(b->d_binfo);
     (void)hipFree(b->d_grid_bins);
     (void)hipFree(b->d_models);
     if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);

@@ -36,6 +36,8 @@
 //        compares the heads of the two queues (ties of equal sums ordered by
 //        a small heap): the same pairs as a full search, in O(n log n)
 //        instead of O(n^2);
+//        where one wave per bin has the LDS for it, many such merges at a time
+//        (merge_bin_rounds);
 //      output order: bins ascending, parents by ascending slot, copies of a
 //      parent consecutive -- neighbouring lanes then hold walkers of similar
 //      state for the next SSA step;
@@ -59,6 +61,7 @@
 #define RESAMPLE_GROUP_COUNT_M 32
 #define RESAMPLE_BIN_PARALLEL_RUNS 256
 #define RESAMPLE_BIN_PARALLEL_BINS 32
+#define RESAMPLE_BIG_M 128
 // Threads per run: up to 16 waves, so up to 16 bins are split/merged at
 // once.  With many runs the grid fills the chip anyway and smaller blocks
 // cost less to start, so launches with at least RESAMPLE_MANY_RUNS blocks use
@@ -179,19 +182,47 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
            (__int_as_float(__builtin_amdgcn_readlane(bits, 32)) + __int_as_float(__builtin_amdgcn_readlane(bits, 48)));
 }
 
+// Integer sum, minimum and exclusive prefix sum over the 64 lanes by DPP moves
+// (a shuffle per step is an LDS round trip of over a hundred cycles).
+template <int CTRL, int ROW_MASK, bool BOUND>
+__device__ __forceinline__ int32_t rs_dpp_i32(int32_t v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xF, BOUND);
+}
 __device__ __forceinline__ int32_t wave_min_i32(int32_t v) {
-    for (int d = 32; d > 0; d >>= 1) v = min(v, __shfl_xor(v, d, 64));
-    return v;
+    v = min(v, rs_dpp_i32<0xB1, 0xF, false>(v));
+    v = min(v, rs_dpp_i32<0x4E, 0xF, false>(v));
+    v = min(v, rs_dpp_i32<0x141, 0xF, false>(v));
+    v = min(v, rs_dpp_i32<0x140, 0xF, false>(v));
+    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+}
+__device__ __forceinline__ int32_t wave_sum_i32(int32_t v) {
+    v += rs_dpp_i32<0xB1, 0xF, false>(v);
+    v += rs_dpp_i32<0x4E, 0xF, false>(v);
+    v += rs_dpp_i32<0x141, 0xF, false>(v);
+    v += rs_dpp_i32<0x140, 0xF, false>(v);
+    return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+           (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+__device__ __forceinline__ int32_t wave_excl_scan(int32_t v, int32_t *total) {
+    int32_t x = v;
+    x += rs_dpp_i32<0x111, 0xF, true>(x);    // row_shr:1, 2, 4, 8
+    x += rs_dpp_i32<0x112, 0xF, true>(x);
+    x += rs_dpp_i32<0x114, 0xF, true>(x);
+    x += rs_dpp_i32<0x118, 0xF, true>(x);
+    x += rs_dpp_i32<0x142, 0xA, false>(x);   // row_bcast:15 into rows 1 and 3
+    x += rs_dpp_i32<0x143, 0xC, false>(x);   // row_bcast:31 into rows 2 and 3
+    *total = __builtin_amdgcn_readlane(x, 63);
+    return x - v;
 }
 
-__device__ __forceinline__ int32_t wave_excl_scan(int32_t v, int lane, int32_t *total) {
-    int32_t x = v;
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
-    *total = __shfl(x, 63, 64);
-    return x - v;
+// Sum over the 64 lanes (every lane gets it), by the steps of wave_max.
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    v += rs_dpp<0xB1>(v);
+    v += rs_dpp<0x4E>(v);
+    v += rs_dpp<0x141>(v);
+    v += rs_dpp<0x140>(v);
+    return (rs_readlane(v, 0) + rs_readlane(v, 16)) + (rs_readlane(v, 32) + rs_readlane(v, 48));
 }
 
 // Orders the LDS/global accesses of the lanes of one wave.
@@ -202,11 +233,6 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-__device__ __forceinline__ int32_t wave_sum_i32(int32_t v) {
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
 
 // Copies a walker of weight v needs so that none carries more than twice the
 // bin's ideal weight (at least one: every walker holds a place).
@@ -256,7 +282,7 @@ __device__ void split_bin(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_
     int32_t cl = 0;
     for (int32_t q = q_lo; q < q_hi; ++q) cl += (int32_t)c[q];
     int32_t tot;
-    int32_t o = o0 + wave_excl_scan(cl, lane, &tot);
+    int32_t o = o0 + wave_excl_scan(cl, &tot);
     for (int32_t q = q_lo; q < q_hi; ++q) {
         const int32_t cc = (int32_t)c[q];
         const double share = w[q] / (double)cc;
@@ -304,63 +330,132 @@ __device__ void rw_flux_bin(double *__restrict__ Frow, const RunWork<Idx> &wk, i
     }
 }
 
-// n < M with at most 64 K parents: lane L owns the contiguous parents
-// [K L, K L + K) (as split_bin's lanes do), their weights, copy counts and
-// per-copy shares in registers; the same hand-out as split_bin: the lowest
-// lane holding the wave's largest share holds the lowest tied slot, and
-// within a lane the lowest slot wins a tie.
+// The lowest slot whose entry of v equals w, given that there is one: walker
+// q of a bin held in registers lives in lane q % 64, register q / 64.
+template <int K>
+__device__ __forceinline__ int32_t lowest_slot(const double (&v)[K], double w) {
+    int32_t q = -1;
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) {
+        const unsigned long long m = __ballot(v[k] == w);
+        if (m) q = 64 * k + __ffsll((long long)m) - 1;
+    }
+    return q;
+}
+
+// The n walkers of a bin with live[k] set, weights wv, replicated up to M
+// copies and written out: one copy each, then one more at a time to the largest
+// share w/c, ties to the lowest slot.  One at a time each copy is a chain of a
+// wave maximum, ballots and a division, so two things are done at once:
+//  - what is certain.  The copies given are the M - n largest of all shares w/1,
+//    w/2, ... in that order, so for any lambda with at most M - n shares of
+//    lambda or more, every share above it is given: a walker has at least
+//    ceil(w / lambda) copies.  lambda is bisected, from W / (M - n) down (W the
+//    sum of the weights), until at most RESAMPLE_FEW copies are left.  Counts are
+//    taken at 1 -+ 2^-36 times w / lambda, which covers every rounding here and
+//    of the shares (weights of 1e-280 and more; subnormal shares round by more);
+//  - ties.  Walkers of the same largest share get their copy together, the
+//    lowest slots first if there are more of them than copies left.
+#define RESAMPLE_FEW 3
+template <int K, class Idx>
+__device__ __forceinline__ void hand_out(const RunWork<Idx> &wk, int32_t p0, int32_t M, int32_t b, int32_t o0,
+                                         const BinOut &out, const double (&wv)[K], const bool (&live)[K], int32_t n,
+                                         int lane) {
+    int32_t c[K];
+    double sh[K];                         // per-copy shares; -1: not live
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        c[k] = live[k] ? 1 : 0;
+        sh[k] = live[k] ? wv[k] : -1.0;
+    }
+    int32_t have = n;
+    if (M - n > 2 * RESAMPLE_FEW) {
+        double wl = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) wl += live[k] ? wv[k] : 0.0;
+        const double W = wave_sum_f64(wl);
+        if (W >= 1e-280) {
+            // 1 / lambda: at f_lo few enough shares, at f_hi (perhaps) too many
+            double f_lo = (double)(M - n) / W * (1.0 - 0x1.0p-35), f_hi = (double)M / W, f = f_lo;
+            for (int32_t it = 0; it < 12; ++it) {
+                int32_t up = 0, dn = 0;
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (live[k]) {
+                        const double x = wv[k] * f;
+                        up += max(1, (int32_t)ceil(x * (1.0 + 0x1.0p-36)));
+                        dn += max(1, (int32_t)ceil(x * (1.0 - 0x1.0p-36)));
+                    }
+                if (wave_sum_i32(up) <= M) {
+                    f_lo = f;
+                    have = wave_sum_i32(dn);
+                    if (M - have <= RESAMPLE_FEW) break;
+                } else {
+                    f_hi = f;
+                }
+                f = 0.5 * (f_lo + f_hi);
+            }
+            if (have > n) {
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (live[k]) {
+                        c[k] = max(1, (int32_t)ceil(wv[k] * f_lo * (1.0 - 0x1.0p-36)));
+                        sh[k] = wv[k] / (double)c[k];
+                    }
+            }
+        }
+    }
+    while (have < M) {
+        double lm = sh[0];
+#pragma unroll
+        for (int k = 1; k < K; ++k) lm = fmax(lm, sh[k]);
+        const double mx = wave_max(lm);
+        // a share that another copy may not make smaller (0, or subnormal): the
+        // lowest slot alone, which then stays in front
+        const int32_t room = mx >= 1e-280 ? M - have : 1;
+        int32_t before = 0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool tied = sh[k] == mx;
+            const unsigned long long m = __ballot(tied);
+            if (tied && before + (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0)) < room) {
+                c[k] += 1;
+                sh[k] = wv[k] / (double)c[k];
+            }
+            before += (int32_t)__popcll(m);
+        }
+        have += min(before, room);
+    }
+    int32_t o = o0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        int32_t tot;
+        int32_t ok = o + wave_excl_scan(c[k], &tot);
+        if (c[k] > 0) {
+            const int32_t kk = wk.list[p0 + 64 * k + lane];
+            for (int32_t r = 0; r < c[k]; ++r) {
+                out.orig[ok] = kk;
+                out.wn[ok] = sh[k];
+                out.obin[ok] = b;
+                ++ok;
+            }
+        }
+        o += tot;
+    }
+}
+
+// n < M with at most 64 K parents, in registers.
 template <int K, class Idx>
 __device__ void split_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
                                 const BinOut &out, int lane) {
-    double wq[K];
-    int32_t c[K];
-    double bs = -1.0;
-    int32_t bk = -1;
+    double wv[K];
+    bool live[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int32_t q = K * lane + k;
-        wq[k] = q < nb ? wk.w[p0 + q] : 0.0;
-        c[k] = 1;
-        if (q < nb) {
-            const double sh = wq[k] / 1.0;
-            if (sh > bs) { bs = sh; bk = k; }
-        }
+        live[k] = 64 * k + lane < nb;
+        wv[k] = live[k] ? wk.w[p0 + 64 * k + lane] : 0.0;
     }
-    for (int32_t e = nb; e < M; ++e) {
-        const double mx = wave_max(bs);
-        const int wl = __ffsll((long long)__ballot(bs == mx)) - 1;
-        if (lane == wl) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if (k == bk) c[k] += 1;
-            bs = -1.0;
-            bk = -1;
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if (K * lane + k < nb) {
-                    const double sh = wq[k] / (double)c[k];
-                    if (sh > bs) { bs = sh; bk = k; }
-                }
-        }
-    }
-    int32_t cl = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) cl += K * lane + k < nb ? c[k] : 0;
-    int32_t tot;
-    int32_t o = o0 + wave_excl_scan(cl, lane, &tot);
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int32_t q = K * lane + k;
-        if (q >= nb) continue;
-        const double share = wq[k] / (double)c[k];
-        const int32_t kk = wk.list[p0 + q];
-        for (int32_t r = 0; r < c[k]; ++r) {
-            out.orig[o] = kk;
-            out.wn[o] = share;
-            out.obin[o] = b;
-            ++o;
-        }
-    }
+    hand_out<K>(wk, p0, M, b, o0, out, wv, live, nb, lane);
 }
 
 // The merge queues of one bin.  Q1: the bin's walkers sorted by (weight,
@@ -466,16 +561,6 @@ __device__ void merge_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
     double wv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) wv[k] = 64 * k + lane < nb ? wk.w[p0 + 64 * k + lane] : inf;
-    // the lowest slot among the walkers of weight w, given each register's ballot
-    auto lowest = [&](const double *v, double w) {
-        int32_t q = -1;
-#pragma unroll
-        for (int k = K - 1; k >= 0; --k) {
-            const unsigned long long m = __ballot(v[k] == w);
-            if (m) q = 64 * k + __ffsll((long long)m) - 1;
-        }
-        return q;
-    };
     double ul = 0.0;
     for (int32_t m = 0; m < nb - M; ++m) {
         if ((m & 63) == 0) {   // the next 64 merge draws, one per lane
@@ -486,7 +571,7 @@ __device__ void merge_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
 #pragma unroll
         for (int k = 1; k < K; ++k) lm = fmin(lm, wv[k]);
         const double wi = wave_min(lm);
-        const int32_t qi = lowest(wv, wi);
+        const int32_t qi = lowest_slot(wv, wi);
         double wr[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) wr[k] = (64 * k + lane == qi) ? inf : wv[k];
@@ -494,7 +579,7 @@ __device__ void merge_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
 #pragma unroll
         for (int k = 1; k < K; ++k) lr = fmin(lr, wr[k]);
         const double wj = wave_min(lr);
-        const int32_t qj = lowest(wr, wj);
+        const int32_t qj = lowest_slot(wr, wj);
         const double u = rs_readlane(ul, m & 63);
         const double sum = wi + wj;
         const double p_i = wi / sum;
@@ -511,7 +596,7 @@ __device__ void merge_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
     for (int k = 0; k < K; ++k) {
         const bool live = 64 * k + lane < nb && wv[k] != inf;
         int32_t tot;
-        const int32_t ok = o + wave_excl_scan(live ? 1 : 0, lane, &tot);
+        const int32_t ok = o + wave_excl_scan(live ? 1 : 0, &tot);
         if (live) {
             out.orig[ok] = wk.list[p0 + 64 * k + lane];
             out.wn[ok] = wv[k];
@@ -558,7 +643,7 @@ __device__ void split_survivors(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
     int32_t cl = 0;
     for (int32_t q = q_lo; q < q_hi; ++q) cl += (int32_t)c[q];
     int32_t tot;
-    int32_t o = o0 + wave_excl_scan(cl, lane, &tot);
+    int32_t o = o0 + wave_excl_scan(cl, &tot);
     for (int32_t q = q_lo; q < q_hi; ++q) {
         const int32_t cc = (int32_t)c[q];
         if (cc == 0) continue;
@@ -591,16 +676,6 @@ __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t n
     double wv[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) wv[k] = 64 * k + lane < nb ? wk.w[p0 + 64 * k + lane] : inf;
-    // the lowest slot whose entry of v equals w, given that there is one
-    auto lowest = [&](const double *v, double w) {
-        int32_t q = -1;
-#pragma unroll
-        for (int k = K - 1; k >= 0; --k) {
-            const unsigned long long m = __ballot(v[k] == w);
-            if (m) q = 64 * k + __ffsll((long long)m) - 1;
-        }
-        return q;
-    };
     double Wb = 0.0;                      // the bin's weight, in slot order
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -621,7 +696,7 @@ __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t n
 #pragma unroll
         for (int k = 1; k < K; ++k) lm = fmin(lm, wv[k]);
         const double wi = wave_min(lm);
-        const int32_t qi = lowest(wv, wi);
+        const int32_t qi = lowest_slot(wv, wi);
         double wr[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) wr[k] = 64 * k + lane == qi ? inf : wv[k];
@@ -632,7 +707,7 @@ __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t n
         const double sum = wi + wj;
         const bool go = eq ? (sum <= ideal || need > M) : (n > M);
         if (!go) break;
-        const int32_t qj = lowest(wr, wj);
+        const int32_t qj = lowest_slot(wr, wj);
         if ((m & 63) == 0) {   // the next 64 merge draws, one per lane
             const U4 rr = philox4x32_10((uint32_t)(m + lane), (uint32_t)b, iter, 1u, k0, k1);
             ul = uniform53(rr.x, rr.y);
@@ -649,42 +724,10 @@ __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t n
         }
         n -= 1;
     }
-    int32_t c[K];
-    double sh[K];                         // per-copy shares; -1: not a survivor
+    bool live[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const bool live = 64 * k + lane < nb && wv[k] != inf;
-        c[k] = live ? 1 : 0;
-        sh[k] = live ? wv[k] : -1.0;
-    }
-    for (int32_t e = n; e < M; ++e) {
-        double lm = sh[0];
-#pragma unroll
-        for (int k = 1; k < K; ++k) lm = fmax(lm, sh[k]);
-        const int32_t q = lowest(sh, wave_max(lm));
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (64 * k + lane == q) {
-                c[k] += 1;
-                sh[k] = wv[k] / (double)c[k];
-            }
-    }
-    int32_t o = o0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        int32_t tot;
-        int32_t ok = o + wave_excl_scan(c[k], lane, &tot);
-        if (c[k] > 0) {
-            const int32_t kk = wk.list[p0 + 64 * k + lane];
-            for (int32_t r = 0; r < c[k]; ++r) {
-                out.orig[ok] = kk;
-                out.wn[ok] = sh[k];
-                out.obin[ok] = b;
-                ++ok;
-            }
-        }
-        o += tot;
-    }
+    for (int k = 0; k < K; ++k) live[k] = 64 * k + lane < nb && wv[k] != inf;
+    hand_out<K>(wk, p0, M, b, o0, out, wv, live, n, lane);
 }
 
 // n > M: merge the two lightest walkers (ties: lowest slot) until M remain.
@@ -797,7 +840,7 @@ __device__ void merge_bin(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_
     int32_t cl = 0;
     for (int32_t q = q_lo; q < q_hi; ++q) cl += (W[q] >= 0.0) ? 1 : 0;
     int32_t tot;
-    int32_t o = o0 + wave_excl_scan(cl, lane, &tot);
+    int32_t o = o0 + wave_excl_scan(cl, &tot);
     for (int32_t q = q_lo; q < q_hi; ++q) {
         const double wq = W[q];
         if (!(wq >= 0.0)) continue;
@@ -808,21 +851,214 @@ __device__ void merge_bin(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_
     }
 }
 
+// n > M for larger bins: the same merges, many at a time.  A is the bin sorted
+// by (weight, slot), B the merged walkers in the order they are made, sorted
+// the same way (their weights never decrease).  With s the sum of the two
+// lightest walkers, every merge made from here on weighs at least s, so all
+// walkers lighter than s are merged in pairs in their order before any of the
+// new ones: a round takes up to 64 from the front of A and of B, ranks them
+// together, and merges pairs side by side, one per lane, each with its own
+// Philox draw (merge number m0 + pair).  A round of one pair (always valid)
+// is the serial step.  Serial merging is a chain of wave minima or dependent
+// loads per merge: the 64-network batch's resample, which waits for its bins of
+// 512 walkers, 392 us that way and 158 in rounds (placement included).
+// LDS of the calling wave, n <= MERGE_ROUNDS_MAX: see MergeLds.
+#define MERGE_ROUNDS_MAX 2048
+struct MergeLds {
+    double *aw, *bw, *cw;      // [n] sorted weights, [n] merged weights, [128] a round's walkers
+    uint16_t *aq, *bq, *cq;    // their slots in the bin
+};
+__host__ __device__ inline size_t merge_lds_bytes() {
+    return (size_t)MERGE_ROUNDS_MAX * 2 * (sizeof(double) + sizeof(uint16_t)) + 128 * (sizeof(double) + sizeof(uint16_t));
+}
+__device__ __forceinline__ MergeLds merge_lds(unsigned char *p) {
+    MergeLds l;
+    l.aw = reinterpret_cast<double *>(p);
+    l.bw = l.aw + MERGE_ROUNDS_MAX;
+    l.cw = l.bw + MERGE_ROUNDS_MAX;
+    l.aq = reinterpret_cast<uint16_t *>(l.cw + 128);
+    l.bq = l.aq + MERGE_ROUNDS_MAX;
+    l.cq = l.bq + MERGE_ROUNDS_MAX;
+    return l;
+}
+
+__device__ __forceinline__ bool lighter(double w0, int32_t q0, double w1, int32_t q1) {
+    return w0 < w1 || (w0 == w1 && q0 < q1);
+}
+
+// B[t0, t) was appended to B[h, t0): puts every run of equal weights that has
+// an appended walker into slot order.  Odd-even transposition, as long as
+// something moves: runs are short unless many weights are equal.
+__device__ void sort_ties(const MergeLds &l, int32_t h, int32_t t0, int32_t t, int lane) {
+    int32_t lo = t0;                          // the run that reaches back starts here
+    const double w0 = l.bw[t0];
+    while (lo > h && l.bw[lo - 1] == w0) --lo;
+    for (int32_t still = 0, odd = 0; still < 2; odd ^= 1) {
+        bool moved = false;
+        for (int32_t c0 = lo + odd; c0 + 1 < t; c0 += 128) {
+            const int32_t i = c0 + 2 * lane;
+            if (i + 1 < t) {
+                const int32_t q0 = l.bq[i], q1 = l.bq[i + 1];
+                if (l.bw[i] == l.bw[i + 1] && q1 < q0) {
+                    l.bq[i] = (uint16_t)q1;
+                    l.bq[i + 1] = (uint16_t)q0;
+                    moved = true;
+                }
+            }
+        }
+        still = __ballot(moved) ? 0 : still + 1;
+        wave_sync();
+    }
+}
+
+__device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
+                                 const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1, const MergeLds &l, int lane) {
+    double *W = wk.w + p0;
+    for (int32_t q = lane; q < nb; q += 64) {
+        l.aw[q] = W[q];
+        l.aq[q] = (uint16_t)q;
+    }
+    wave_sync();
+    // bitonic network; mirrored first steps make positions past nb act as +inf
+    int32_t P = 1;
+    while (P < nb) P <<= 1;
+    for (int32_t size = 2; size <= P; size <<= 1)
+        for (int32_t d = size >> 1; d > 0; d >>= 1) {
+            const bool mirror = d == (size >> 1);
+            for (int32_t c = lane; c < (P >> 1); c += 64) {
+                const int32_t r = c & (d - 1), base = (c - r) << 1;
+                const int32_t i = base + r, j = mirror ? base + 2 * d - 1 - r : i + d;
+                if (j < nb) {
+                    const double wi = l.aw[i], wj = l.aw[j];
+                    const int32_t qi = l.aq[i], qj = l.aq[j];
+                    if (lighter(wj, qj, wi, qi)) {
+                        l.aw[i] = wj;
+                        l.aw[j] = wi;
+                        l.aq[i] = (uint16_t)qj;
+                        l.aq[j] = (uint16_t)qi;
+                    }
+                }
+            }
+            wave_sync();
+        }
+    const double inf = __builtin_huge_val();
+    int32_t ha = 0, hb = 0, t = 0;          // fronts of A and B, end of B
+    int32_t m0 = 0;                          // merges made
+    while (m0 < nb - M) {
+        // up to 64 walkers from the front of each
+        const int32_t ia = ha + lane, ib = hb + lane;
+        const double wa = ia < nb ? l.aw[ia] : inf, wb = ib < t ? l.bw[ib] : inf;
+        const int32_t qa = ia < nb ? (int32_t)l.aq[ia] : 0, qb = ib < t ? (int32_t)l.bq[ib] : 0;
+        // the two lightest: among the first two of each, as sums of sorted heads
+        const double a0 = rs_readlane(wa, 0), a1 = rs_readlane(wa, 1), b0 = rs_readlane(wb, 0), b1 = rs_readlane(wb, 1);
+        const double s = fmin(fmin(a0 + a1, b0 + b1), a0 + b0);
+        int32_t na = (int32_t)__popcll(__ballot(wa < s)), nbm = (int32_t)__popcll(__ballot(wb < s));
+        if (na + nbm < 2) {                  // zero weights, or a pair that rounds to its heavier walker
+            na = min(2, nb - ha);
+            nbm = min(2, t - hb);
+        }
+        // rank each walker among the na + nbm taken: walk the shorter list
+        int32_t ra = lane, rb = lane;
+        if (na <= nbm) {
+            for (int32_t j = 0; j < na; ++j) {
+                const bool less = lane < nbm && lighter(wb, qb, rs_readlane(wa, j), __builtin_amdgcn_readlane(qa, j));
+                const int32_t r = (int32_t)__popcll(__ballot(less));
+                if (lane == j) ra += r;
+                if (!less) rb += 1;
+            }
+        } else {
+            for (int32_t j = 0; j < nbm; ++j) {
+                const bool less = lane < na && lighter(wa, qa, rs_readlane(wb, j), __builtin_amdgcn_readlane(qb, j));
+                const int32_t r = (int32_t)__popcll(__ballot(less));
+                if (lane == j) rb += r;
+                if (!less) ra += 1;
+            }
+        }
+        if (lane < na) {
+            l.cw[ra] = wa;
+            l.cq[ra] = (uint16_t)qa;
+        }
+        if (lane < nbm) {
+            l.cw[rb] = wb;
+            l.cq[rb] = (uint16_t)qb;
+        }
+        wave_sync();
+        // all below s: as many pairs as there are; else (the first two of each
+        // list, ranked) only the first pair is certain
+        const bool all = __ballot((lane < na && !(wa < s)) || (lane < nbm && !(wb < s))) == 0ull;
+        // and none past the last one of a full window: further ones of that list
+        // may come before those of the other
+        int32_t sure = na + nbm;
+        if (na == 64 && ha + 64 < nb) sure = min(sure, __builtin_amdgcn_readlane(ra, 63) + 1);
+        if (nbm == 64 && hb + 64 < t) sure = min(sure, __builtin_amdgcn_readlane(rb, 63) + 1);
+        const int32_t pairs = min(all ? sure >> 1 : 1, nb - M - m0);
+        double sum = 0.0;
+        int32_t keep = 0;
+        if (lane < pairs) {
+            const double wi = l.cw[2 * lane], wj = l.cw[2 * lane + 1];
+            const int32_t qi = l.cq[2 * lane], qj = l.cq[2 * lane + 1];
+            const U4 rr = philox4x32_10((uint32_t)(m0 + lane), (uint32_t)b, iter, 1u, k0, k1);
+            const double u = uniform53(rr.x, rr.y);
+            sum = wi + wj;
+            const double p_i = wi / sum;
+            keep = (u < p_i) ? qi : qj;
+            W[keep] = sum;
+            W[keep == qi ? qj : qi] = -1.0;
+        }
+        // consumed: the walkers of rank below 2 pairs
+        ha += (int32_t)__popcll(__ballot(lane < na && ra < 2 * pairs));
+        hb += (int32_t)__popcll(__ballot(lane < nbm && rb < 2 * pairs));
+        // the new walkers behind B, sorted by weight; runs of equal weights
+        // (which may reach back into B) are put into slot order
+        if (lane < pairs) {
+            l.bw[t + lane] = sum;
+            l.bq[t + lane] = (uint16_t)keep;
+        }
+        wave_sync();
+        const int32_t t0 = t;
+        t += pairs;
+        const bool tie = lane < pairs && t0 + lane > hb && l.bw[t0 + lane - 1] == sum;
+        if (__ballot(tie)) sort_ties(l, hb, t0, t, lane);
+        m0 += pairs;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wave_sync();
+    // survivors in slot order
+    int32_t o = o0;
+    for (int32_t c0 = 0; c0 < nb; c0 += 64) {
+        const int32_t q = c0 + lane;
+        const double wq = q < nb ? W[q] : -1.0;
+        const bool live = wq >= 0.0;
+        int32_t tot;
+        const int32_t ok = o + wave_excl_scan(live ? 1 : 0, &tot);
+        if (live) {
+            out.orig[ok] = wk.list[p0 + q];
+            out.wn[ok] = wq;
+            out.obin[ok] = b;
+        }
+        o += tot;
+    }
+}
+
 }  // namespace
 
 // One bin's split/merge (and its row of the reweighting flux matrix) on the
 // calling wave: the walkers at positions [p0, p0 + nb) of wk, the output at
-// slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).
-template <class Idx, int RULE>
+// slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).  BIG: bins of
+// up to 512 walkers to split or equalize in registers, up to eight walkers per
+// lane (more than a 1024-thread workgroup has room for; else 128 and 256), and
+// of up to MERGE_ROUNDS_MAX to merge in rounds in the wave's LDS mlds.
+template <class Idx, int RULE, bool BIG>
 __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const BinOut &out, int32_t run, int32_t b,
                              int32_t nb, int32_t p0, int32_t o0, uint32_t iter, uint32_t k0, uint32_t k1,
-                             bool rw_acc, int lane) {
+                             bool rw_acc, int lane, unsigned char *mlds = nullptr) {
     const int32_t NB = a.n_bins, M = a.m_targ;
     if (rw_acc) rw_flux_bin(a.rw_F + ((size_t)run * NB + b) * NB, wk, p0, nb, lane);
     if (RULE < 0 ? a.rs_rule == 1 : RULE == 1) {
         if (nb <= 64) equalize_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
-        else if (RULE >= 0 && nb <= 128) equalize_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
-        else if (RULE >= 0 && nb <= 256) equalize_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (nb <= 128) equalize_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (nb <= 256) equalize_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (BIG && nb <= 512) equalize_bin_lanes<8>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else merge_bin<Idx, true>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
     } else if (nb == M) {
         for (int32_t q = lane; q < nb; q += 64) {
@@ -833,11 +1069,16 @@ __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const Bin
     } else if (nb < M) {
         if (nb <= 64) split_bin_lanes<1>(wk, p0, nb, M, b, o0, out, lane);
         else if (nb <= 128) split_bin_lanes<2>(wk, p0, nb, M, b, o0, out, lane);
+        else if (BIG && nb <= 256) split_bin_lanes<4>(wk, p0, nb, M, b, o0, out, lane);
+        else if (BIG && nb <= 512) split_bin_lanes<8>(wk, p0, nb, M, b, o0, out, lane);
         else split_bin(wk, p0, nb, M, b, o0, out, lane);
     } else {
         if (nb <= 64) merge_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 128) merge_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 256) merge_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if (BIG && nb <= MERGE_ROUNDS_MAX) {
+            if constexpr (BIG) merge_bin_rounds(wk, p0, nb, M, b, o0, out, iter, k0, k1, merge_lds(mlds), lane);
+        }
         else merge_bin<Idx, false>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
     }
 }
@@ -980,8 +1221,8 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
             oacc += cnt[b] > 0 ? M : 0;
         }
         int32_t tot, otot;
-        acc = wave_excl_scan(acc, lane, &tot);
-        oacc = wave_excl_scan(oacc, lane, &otot);
+        acc = wave_excl_scan(acc, &tot);
+        oacc = wave_excl_scan(oacc, &otot);
         for (int32_t b = b_lo; b < b_hi; ++b) {
             start[b] = acc;
             ostart[b] = oacc;
@@ -1091,7 +1332,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     for (int32_t b = wave; b < NB; b += n_waves) {
         const int32_t nb = uni(cnt[b]);
         if (nb == 0) continue;
-        resample_bin<Idx, RULE>(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
+        resample_bin<Idx, RULE, false>(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
     }
     __syncthreads();
     if (tid == 0) a.n_walk[run] = ostart[NB];
@@ -1114,12 +1355,12 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a
 // Bin-parallel split/merge after we_resample_kernel's placement: grid
 // (ceil(n_bins / 4), runs), one wave per bin, the same per-bin steps on the
 // run's arrays in device memory; bins of one run write disjoint ranges.
-template <int RULE>
-__global__ __launch_bounds__(256) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
-                                                               const int32_t *__restrict__ binfo) {
+template <int RULE, bool BIG>
+__device__ __forceinline__ void resample_bins_wave(const SimArgs &a, double *__restrict__ w_nxt,
+                                                   const int32_t *__restrict__ binfo, int32_t run, int32_t b,
+                                                   unsigned char *mlds) {
     const int lane = threadIdx.x & 63;
-    const int32_t run = blockIdx.y, NB = a.n_bins;
-    const int32_t b = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x >> 6);
+    const int32_t NB = a.n_bins;
     if (b >= NB) return;                       // uniform over the wave
     const int32_t *bi = binfo + (size_t)run * 3 * NB;
     const int32_t nb = uni(bi[b]);
@@ -1132,8 +1373,22 @@ __global__ __launch_bounds__(256) void we_resample_bins_kernel(SimArgs a, double
     out.wn = w_nxt + base;
     const uint32_t iter = *a.iter_dev;
     const uint64_t seed = a.seeds[run];
-    resample_bin<int32_t, RULE>(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
-                                (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane);
+    resample_bin<int32_t, RULE, BIG>(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
+                                     (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane, mlds);
+}
+
+// Waves (bins) per workgroup: one where a bin may need merge_bin_rounds' LDS.
+template <bool BIG>
+struct BinsBlock {
+    static constexpr int WAVES = BIG ? 1 : 4;
+};
+
+template <int RULE, bool BIG>
+__global__ __launch_bounds__(64 * BinsBlock<BIG>::WAVES) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
+                                                                                    const int32_t *__restrict__ binfo) {
+    extern __shared__ __align__(16) unsigned char mlds[];
+    resample_bins_wave<RULE, BIG>(a, w_nxt, binfo, blockIdx.y,
+                                  (int32_t)blockIdx.x * BinsBlock<BIG>::WAVES + (int32_t)(threadIdx.x >> 6), mlds);
 }
 
 // New state rows from their parents: one lane per copy number.
@@ -1215,7 +1470,7 @@ struct BatchPtrs {
     int32_t *const *x_nxt;
     const double *const *w_cur;
     double *const *w_nxt;
-    const int32_t *use_lds;
+    int32_t *const *binfo;
     const int32_t *grid_bins;
 };
 
@@ -1224,13 +1479,26 @@ __global__ __launch_bounds__(256) void we_batch_recycle_bin_kernel(BatchPtrs b) 
     recycle_bin_one(b.args[i], b.x_cur[i], b.grid_bins[i], (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-__global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_resample_kernel(BatchPtrs b) {
+// Placement by one workgroup per run, then one wave per bin over all members'
+// bins: with the split/merge in the run's workgroup, in LDS, the launch lasted
+// as long as the largest member's (one run of 16 bins of 512 walkers, whose
+// bins were sorted: 392 us for the batch of 64 networks).
+__global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_place_kernel(BatchPtrs b) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int32_t i = blockIdx.y;
     const SimArgs &a = b.args[i];
     if ((int32_t)blockIdx.x >= a.n_runs) return;
-    if (b.use_lds[i]) resample_run_t<uint16_t, true, -1, false>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, nullptr);
-    else resample_run_t<int32_t, false, -1, false>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, nullptr);
+    resample_run_t<int32_t, false, 0, true>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, b.binfo[i]);
+}
+
+template <bool BIG>
+__global__ __launch_bounds__(64 * BinsBlock<BIG>::WAVES) void we_batch_bins_kernel(BatchPtrs b) {
+    extern __shared__ __align__(16) unsigned char mlds[];
+    const int32_t i = blockIdx.z;
+    const SimArgs &a = b.args[i];
+    if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != BIG) return;
+    resample_bins_wave<-1, BIG>(a, b.w_nxt[i], b.binfo[i], blockIdx.x,
+                                (int32_t)blockIdx.y * BinsBlock<BIG>::WAVES + (int32_t)(threadIdx.x >> 6), mlds);
 }
 
 // Grid-strided over each member's own cells: a grid sized for the largest
@@ -1263,8 +1531,13 @@ __global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n, uint32_t *__rest
 // cells): 64 members then give 32768 workgroups, 128 per CU.
 #define BATCH_GATHER_BLOCKS 512
 
+// m_sizes: bit 0, some member has at most RESAMPLE_BIG_M walkers per bin; bit
+// 1, some member has more.
+uint32_t resample_m_size(int32_t m) { return m > RESAMPLE_BIG_M ? 2u : 1u; }
+
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
-                                    int64_t max_cells, size_t shmem, bool observe, const CmBatchModel *models,
+                                    int64_t max_cells, int32_t max_bins, uint32_t m_sizes, size_t shmem, bool observe,
+                                    const CmBatchModel *models,
                                     int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st) {
     const unsigned gs = (unsigned)((max_slots + 255) / 256);
     hipLaunchKernelGGL(we_batch_recycle_bin_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
@@ -1272,8 +1545,12 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
         const hipError_t e = committor_bin_batch(b.args, b.x_cur, models, n_sims, max_slots, s_max_cm, st);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(we_batch_resample_kernel, dim3(max_runs, n_sims),
+    hipLaunchKernelGGL(we_batch_place_kernel, dim3(max_runs, n_sims),
                        dim3(resample_threads((int64_t)max_runs * n_sims)), shmem, st, b);
+    if (m_sizes & 2u)
+        hipLaunchKernelGGL(we_batch_bins_kernel<true>, dim3(max_runs, max_bins, n_sims), dim3(64), merge_lds_bytes(), st, b);
+    if (m_sizes & 1u)
+        hipLaunchKernelGGL(we_batch_bins_kernel<false>, dim3(max_runs, (max_bins + 3) / 4, n_sims), dim3(256), 0, st, b);
     const unsigned gg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_cells + 255) / 256, BATCH_GATHER_BLOCKS));
     hipLaunchKernelGGL(we_batch_gather_kernel, dim3(gg, n_sims), dim3(256), 0, st, b);
     if (observe) hipLaunchKernelGGL(we_batch_observe_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
@@ -1336,9 +1613,14 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
     if (split) {
         // the placement takes no rule
         hipLaunchKernelGGL((we_resample_kernel<RS_PLACE, 0>), gr, br, shmem, st, a, w_cur, w_nxt, binfo);
-        const dim3 gb((unsigned)((a.n_bins + 3) / 4), (unsigned)a.n_runs);
-        if (eq) hipLaunchKernelGGL(we_resample_bins_kernel<1>, gb, dim3(256), 0, st, a, w_nxt, binfo);
-        else hipLaunchKernelGGL(we_resample_bins_kernel<0>, gb, dim3(256), 0, st, a, w_nxt, binfo);
+        // targets of at most 128 walkers leave few bins past 256, and the
+        // larger register files would cost the small bins occupancy
+        const bool big = a.m_targ > RESAMPLE_BIG_M;
+        const dim3 gb((unsigned)(big ? a.n_bins : (a.n_bins + 3) / 4), (unsigned)a.n_runs);
+        if (eq && big) hipLaunchKernelGGL((we_resample_bins_kernel<1, true>), gb, dim3(64), merge_lds_bytes(), st, a, w_nxt, binfo);
+        else if (eq) hipLaunchKernelGGL((we_resample_bins_kernel<1, false>), gb, dim3(256), 0, st, a, w_nxt, binfo);
+        else if (big) hipLaunchKernelGGL((we_resample_bins_kernel<0, true>), gb, dim3(64), merge_lds_bytes(), st, a, w_nxt, binfo);
+        else hipLaunchKernelGGL((we_resample_bins_kernel<0, false>), gb, dim3(256), 0, st, a, w_nxt, binfo);
     } else if (use_lds) {
         if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
         else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
