@@ -61,6 +61,11 @@ struct PoolQueue {
         size = tiles > s ? (tiles - s + n - 1) / n * 64u : 0u;
         head = a.heads + s * WE_HEAD_STRIDE;
     }
+    // Where the static tiles are the whole queue, a wave takes every n-th position
+    // instead (n waves to a head), one from each stretch of the queue, so that
+    // its walkers run out one by one and the last ones can be teamed up
+    // (lane_team); tiles would give it 64 walkers of one length.
+    __device__ __forceinline__ uint32_t dealt(uint32_t lane) const { return lane * (n_first / 64u) + first / 64u; }
     // queue position of this head's position i
     __device__ __forceinline__ uint32_t at(uint32_t i) const { return i < size ? ((i >> 6) * n + s) * 64u + (i & 63u) : ~0u; }
 };
@@ -72,6 +77,71 @@ struct PoolQueue {
 // grows steeply along the progress coordinate), so a fixed walker-per-lane
 // assignment would leave most lanes of a wave idle while its slowest walker
 // finishes.
+// The end of a wave's work: the queue is empty and at most 32 of its walkers
+// are left.  They are spread out, T = 2 ... 16 lanes (a team) per walker, and the
+// lanes of a team draw the random numbers of T events at once, one event each
+// (Philox, logarithm and conversions are about 70% of an event's instructions),
+// then run those events side by side, every lane on the same state.  T doubles
+// as walkers finish; the walkers take the same steps.  A launch lasts as long as
+// its busiest walker's chain of events: with the branch-free event, one Schloegl
+// run of 80 bins x 32 walkers (1158 events at most) 719 -> 304 ns per event of
+// that walker, 32 such runs 783 -> 422 ns.
+template <int SMAX, int RMAX, bool HILL>
+__device__ __forceinline__ void lane_team(const SimArgs &a, const LaneNet<SMAX, RMAX, HILL> &net, LaneWalker &w,
+                                          int32_t (&x)[SMAX], int32_t *__restrict__ xs, int32_t *xr, size_t gslot,
+                                          bool active, uint32_t iter, double tau) {
+    const int lane = threadIdx.x & 63;
+    int T = 1;
+    uint32_t g = (uint32_t)gslot;
+    for (;;) {
+        // teams left: their first lanes (lane 0 of a team is a multiple of T)
+        const unsigned long long lead = __ballot(active && (lane & (T - 1)) == 0);
+        const int n = __popcll(lead);
+        if (n == 0) return;
+        if (T < 16 && 2 * T * n <= 64) {
+            int U = 2 * T;
+            while (U < 16 && 2 * U * n <= 64) U *= 2;
+            // team j of the new teams takes the j-th walker left: its first lane
+            // hears from that walker's lane, the others from the first
+            const int rank = __popcll(lead & ((1ull << lane) - 1ull));
+            const bool is_lead = active && (lane & (T - 1)) == 0;
+            // lanes that send nothing address a lane that no team's first lane is
+            int src = __builtin_amdgcn_ds_permute(4 * (is_lead ? rank * U : 1), lane);
+            src = __shfl(src, lane & ~(U - 1), 64);
+            const bool on = lane / U < n;
+            src = on ? src : lane;
+            w.t = __shfl(w.t, src, 64);
+            w.e = (uint32_t)__shfl((int)w.e, src, 64);
+            w.fired = (uint32_t)__shfl((int)w.fired, src, 64);
+            g = (uint32_t)__shfl((int)g, src, 64);
+            w.k0 = (uint32_t)__shfl((int)w.k0, src, 64);
+            w.k1 = (uint32_t)__shfl((int)w.k1, src, 64);
+            w.slot = (uint32_t)__shfl((int)w.slot, src, 64);
+#pragma unroll
+            for (int s = 0; s < SMAX; ++s) x[s] = __shfl(x[s], src, 64);
+            active = on;
+            w.bad = false;
+            w.rs.init(w.slot, iter, w.k0, w.k1);
+            T = U;
+        }
+        const int first = lane & ~(T - 1);
+        const EventDraw mine = lane_draw(w.rs, w.e + (uint32_t)(lane - first));
+        w.e += (uint32_t)T;
+        // the next event's pair is fetched while this one runs
+        EventDraw nx{__shfl(mine.nl, first, 64), __shfl(mine.u2, first, 64)};
+        for (int i = 1; i <= T; ++i) {
+            const EventDraw d = nx;
+            nx.nl = __shfl(mine.nl, first + i, 64);
+            nx.u2 = __shfl(mine.u2, first + i, 64);
+            if (active && !lane_event(net, w, x, tau, [&]() { return d; })) {
+                if (lane == first) lane_finish(a, w, x, xs + (size_t)g * a.S, (size_t)g);
+                active = false;
+            }
+            if (!__ballot(active)) return;
+        }
+    }
+}
+
 template <int SMAX, int RMAX, bool HILL, bool LEAP>
 __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict__ xs, int32_t *wrows) {
     constexpr bool REG = RMAX <= LANE_REG_RMAX;
@@ -108,9 +178,9 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
                 base = pq.n_first + (uint32_t)__shfl((int)got, leader, 64);
             }
             if ((uint64_t)(first ? pq.n_first : base + (uint32_t)nneed) >= pq.size) exhausted = true;
-            first = false;
             if (!active) {
-                const uint32_t q = pq.at(base + (uint32_t)__popcll(need & below));
+                const uint32_t rank = (uint32_t)__popcll(need & below);
+                const uint32_t q = pq.at(!LEAP && first && pq.size <= pq.n_first ? pq.dealt(rank) : base + rank);
                 if (q < total) {
                     const uint32_t sg = q / M, o = q - sg * M;
                     const int2 seg = a.seg[sg];
@@ -126,6 +196,7 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
                     }
                 }
             }
+            first = false;
         }
         if (!__ballot(active) && exhausted) break;
         if constexpr (LEAP) {
@@ -134,7 +205,11 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
                 active = false;
             }
         } else {
-            if (active && !lane_event(net, w, x, iter, tau)) {
+            if (exhausted && nneed >= 32) {
+                lane_team<SMAX, RMAX, HILL>(a, net, w, x, xs, xr, gslot, active, iter, tau);
+                break;
+            }
+            if (active && !lane_event(net, w, x, tau, [&]() { return lane_draw(w.rs, w.e++); })) {
                 lane_finish(a, w, x, xr, gslot);
                 active = false;
             }
@@ -142,8 +217,9 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
     }
 }
 
+// Five waves per SIMD for the smallest networks, whose registers allow it.
 template <int SMAX, int RMAX>
-__global__ __launch_bounds__(256) void ssa_lane_pool_kernel(SimArgs a, int32_t *__restrict__ xs) {
+__global__ __launch_bounds__(256, SMAX == 1 ? 5 : 1) void ssa_lane_pool_kernel(SimArgs a, int32_t *__restrict__ xs) {
     constexpr int ROWS = RMAX <= LANE_REG_RMAX ? 1 : RMAX * LaneRow<SMAX>::W;
     __shared__ int32_t rows[4 * ROWS];
     lane_pool<SMAX, RMAX, false, false>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
@@ -206,7 +282,13 @@ unsigned pool_blocks(const SimArgs &a) {
         // per CU against 1.215 at 4, 1.268 at 3, 1.243 at 6 and 1.230 at 7.
         if (per_cu > LANE_POOL_PER_CU) per_cu = LANE_POOL_PER_CU;
     }
-    const int64_t need = ((int64_t)a.n_runs * a.cap + 255) / 256;
+    // Where the chip has more room than walkers: up to four times the waves, each
+    // with fewer walkers, which start as teams (one Schloegl run of 80 bins x 32
+    // walkers 433 -> 352 us); past one block per CU, whole blocks per CU, since
+    // the SIMDs with one wave more would finish last (32 such runs: 320 blocks
+    // 597, 256 482, 512 533, 1024 798 us).
+    int64_t need = ((int64_t)a.n_runs * a.cap + 255) / 256;
+    if (VARIANT != 2) need = need < n_cu ? need * std::min<int64_t>(4, n_cu / need) : (need + n_cu / 2) / n_cu * n_cu;
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)per_cu * n_cu));
 }
 

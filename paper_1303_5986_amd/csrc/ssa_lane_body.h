@@ -240,12 +240,23 @@ struct LaneWalker {
     }
 };
 
-// One event of the direct method (Sec. II.A); false once the walker's
-// interval is over (next event beyond tau, no reaction possible, or a count
-// out of range -- then w.bad is set).
-template <int SMAX, int RMAX, bool HILL>
+// The random numbers of one event: -log(1 - u1) and u2.  They depend on the
+// event's number alone, not on the walker's state.
+struct EventDraw {
+    double nl, u2;
+};
+__device__ __forceinline__ EventDraw lane_draw(const SsaStream &rs, uint32_t e) {
+    const U4 r = rs.draw(e);
+    return EventDraw{neg_log1m(uniform53(r.x, r.y)), uniform53(r.z, r.w)};
+}
+
+// One event of the direct method (Sec. II.A) with the numbers draw() returns
+// (called once the total propensity is known to be positive); false once the
+// walker's interval is over (next event beyond tau, no reaction possible, or a
+// count out of range -- then w.bad is set).
+template <int SMAX, int RMAX, bool HILL, class DrawFn>
 __device__ __forceinline__ bool lane_event(const LaneNet<SMAX, RMAX, HILL> &net, LaneWalker &w,
-                                           int32_t (&x)[SMAX], uint32_t iter, double tau) {
+                                           int32_t (&x)[SMAX], double tau, DrawFn &&draw) {
     constexpr int W = LaneRow<SMAX>::W;
     constexpr bool REG = LaneNet<SMAX, RMAX, HILL>::REG;
     constexpr bool MONO = LaneNet<SMAX, RMAX, HILL>::MONO;
@@ -265,19 +276,20 @@ __device__ __forceinline__ bool lane_event(const LaneNet<SMAX, RMAX, HILL> &net,
             a0 = a0 + prop[j];
         }
     }
-    if (!(a0 > 0.0)) return false;
-    const U4 r = w.rs.draw(w.e);
-    w.e += 1;
-    const double u1 = uniform53(r.x, r.y);
-    const double u2 = uniform53(r.z, r.w);
-    const double dt = neg_log1m(u1) * recip(a0);
-    if (w.t + dt > tau) return false;
-    w.t = w.t + dt;
-    const double target = u2 * a0;
+    // Everything below is computed without a branch, then committed under one:
+    // a walker's events are one dependent chain, and with few waves on a SIMD its
+    // latency is the time.  So the choice of the reaction runs beside the
+    // reciprocal and the waiting time instead of behind their test.  What ends
+    // or bends the normal course (the interval's end, no reaction possible, a
+    // target that rounding leaves above the whole sum, a count out of range) is
+    // sorted out after it.
+    const EventDraw d = draw();
+    const double t = w.t + d.nl * recip(a0);
+    const double target = d.u2 * a0;
     // The chosen reaction is the first j whose running sum (in reaction order)
     // exceeds the target; if rounding leaves the target above the whole sum,
     // the last reaction with a positive propensity.
-    int32_t jsel = -1;
+    int32_t jsel = REG ? -1 : 0;
     uint32_t dsel[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) dsel[q] = 0u;
@@ -306,36 +318,16 @@ __device__ __forceinline__ bool lane_event(const LaneNet<SMAX, RMAX, HILL> &net,
                 jsel = hit ? j : jsel;
             }
         }
-        if (!(c > target)) {
-#pragma unroll
-            for (int j = 0; j < RMAX; ++j)
-                if ((REG || j < net.R) && prop[j] > 0.0) jsel = j;
-            if constexpr (REG) {
-#pragma unroll
-                for (int q = 0; q < W; ++q) dsel[q] = (uint32_t)net.dpack[jsel * WE_DPACK_WORDS + q];
-            }
-        }
     } else {
         double cum = 0.0;
-        int32_t last_pos = -1;
+        bool found = false;
 #pragma unroll
         for (int j = 0; j < RMAX; ++j) {
             if (j < net.R) {
                 cum = cum + prop[j];
-                if (prop[j] > 0.0) last_pos = j;
-                const bool hit = (jsel < 0) && (cum > target);
+                const bool hit = !found && cum > target;
                 if (hit) jsel = j;
-                if constexpr (REG) {
-#pragma unroll
-                    for (int q = 0; q < W; ++q) dsel[q] = hit ? net.drow[REG ? j : 0][q] : dsel[q];
-                }
-            }
-        }
-        if (jsel < 0) {
-            jsel = last_pos;
-            if constexpr (REG) {
-#pragma unroll
-                for (int q = 0; q < W; ++q) dsel[q] = (uint32_t)net.dpack[jsel * WE_DPACK_WORDS + q];
+                found = found || hit;
             }
         }
     }
@@ -343,17 +335,46 @@ __device__ __forceinline__ bool lane_event(const LaneNet<SMAX, RMAX, HILL> &net,
 #pragma unroll
         for (int q = 0; q < W; ++q) dsel[q] = (uint32_t)net.rows[jsel * W + q];
     }
-    w.fired += 1;
+    int32_t xn[SMAX];
     int32_t any = 0;
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) {
-        x[s] += (int32_t)(dsel[s >> 2] << (24 - 8 * (s & 3))) >> 24;
-        any |= x[s];
+        xn[s] = x[s] + ((int32_t)(dsel[s >> 2] << (24 - 8 * (s & 3))) >> 24);
+        any |= xn[s];
     }
+    // (the running sums end in a0: the same additions in the same order)
+    const bool over = !(a0 > 0.0) || t > tau;
+    const bool past = !(a0 > target);
     // a count left [0, 2^17 - 1] iff a bit outside the low 17 is set
-    if (any & ~WE_COUNT_MAX_DEV) {
-        w.bad = true;
-        return false;
+    const bool odd = over || past || (any & ~WE_COUNT_MAX_DEV) != 0;
+    w.t = odd ? w.t : t;
+    w.fired += odd ? 0u : 1u;
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) x[s] = odd ? x[s] : xn[s];
+    if (__builtin_expect(odd, 0)) {
+        if (over) return false;
+        w.t = t;
+        w.fired += 1;
+        if (past) {
+            any = 0;
+#pragma unroll
+            for (int j = 0; j < RMAX; ++j)
+                if ((REG || j < net.R) && prop[j] > 0.0) jsel = j;
+#pragma unroll
+            for (int q = 0; q < W; ++q)
+                dsel[q] = REG ? (uint32_t)net.dpack[jsel * WE_DPACK_WORDS + q] : (uint32_t)net.rows[jsel * W + q];
+#pragma unroll
+            for (int s = 0; s < SMAX; ++s) {
+                xn[s] = x[s] + ((int32_t)(dsel[s >> 2] << (24 - 8 * (s & 3))) >> 24);
+                any |= xn[s];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) x[s] = xn[s];
+        if (any & ~WE_COUNT_MAX_DEV) {
+            w.bad = true;
+            return false;
+        }
     }
     return true;
 }
@@ -641,7 +662,7 @@ __device__ __forceinline__ void lane_walker(const SimArgs &a, int32_t *__restric
     LaneWalker w;
     int32_t x[SMAX];
     w.begin(x, xr, a.S, (uint32_t)k, a.seeds[run], iter);
-    while (lane_event(net, w, x, iter, a.tau)) {
+    while (lane_event(net, w, x, a.tau, [&]() { return lane_draw(w.rs, w.e++); })) {
     }
     lane_finish(a, w, x, xr, gslot);
 }
