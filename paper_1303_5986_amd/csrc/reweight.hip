@@ -26,11 +26,19 @@
 //      is scaled by 1 (exactly unchanged).  Optionally F is cleared, so that
 //      the next event sees only the intervals after this one.
 // The rate matrix lives in LDS when it fits, else in a per-run global
-// scratch.  Sums over lanes use fixed shuffle trees, so the result is
-// deterministic (graph replays equal eager runs bit for bit).
+// scratch.  What bounds an event is the latency of the elimination's steps, one
+// after another over the component's states: each step reads its row (one wave)
+// and its column (the others) at once and lists the rows with a nonzero entry,
+// and the 16 waves update those rows (rates join neighbouring bins, so most
+// rows have none).  64 runs of 465 bins take 1.6 ms per event, 32 runs of 80
+// bins 110 us; with 4 waves, each testing its share of the rows one load after
+// another, and walkers, column sums and bit masks fetched one at a time, it was
+// 7.1 ms and 141 us.  Sums over
+// lanes use fixed trees, so the result is deterministic (graph replays equal
+// eager runs bit for bit).
 #include "we_internal.h"
 
-#define RW_THREADS 256
+#define RW_THREADS 1024
 #define RW_LDS_LIMIT (128 * 1024)
 
 namespace {
@@ -47,14 +55,55 @@ __host__ __device__ inline size_t rw_small_bytes(int32_t NB) {
     return rw_align8(40 * (size_t)NB + 12 * (size_t)NB) + 16 * (size_t)NB * nw + RW_MISC_BYTES;
 }
 
+// Sum over the 64 lanes as the butterfly over lane bits 5, 4, 3, 2, 1, 0 adds it
+// (every lane gets it): lane halves and rows swapped, then rotations in a
+// 16-lane row, which reach the partner of bit 3, and, the lanes 8 apart being
+// equal by then, of bit 2.
+union RwBits {
+    double d;
+    uint32_t w[2];
+};
+template <int CTRL>
+__device__ __forceinline__ double rw_dpp(double v) {
+    RwBits in, out;
+    in.d = v;
+    out.w[0] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in.w[0], CTRL, 0xF, 0xF, false);
+    out.w[1] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)in.w[1], CTRL, 0xF, 0xF, false);
+    return out.d;
+}
 __device__ __forceinline__ double rw_wave_sum(double v) {
-    for (int d = 32; d > 0; d >>= 1) v = v + __shfl_xor(v, d, 64);
+    RwBits x, y, z;
+    x.d = v;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = __builtin_amdgcn_permlane32_swap(x.w[k], x.w[k], false, false);
+        y.w[k] = r[0];
+        z.w[k] = r[1];
+    }
+    x.d = y.d + z.d;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x.w[k], x.w[k], false, false);
+        y.w[k] = r[0];
+        z.w[k] = r[1];
+    }
+    v = y.d + z.d;
+    v = v + rw_dpp<0x128>(v);   // row_ror:8
+    v = v + rw_dpp<0x124>(v);   // row_ror:4
+    v = v + rw_dpp<0x4E>(v);    // quad_perm [2,3,0,1]
+    v = v + rw_dpp<0xB1>(v);    // quad_perm [1,0,3,2]
     return v;
 }
 
-__device__ __forceinline__ unsigned long long rw_wave_or(unsigned long long v) {
-    for (int d = 32; d > 0; d >>= 1) v |= __shfl_xor(v, d, 64);
-    return v;
+__device__ __forceinline__ uint32_t rw_wave_or(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = r[0] | r[1];
+    const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return q[0] | q[1];
 }
 
 __device__ __forceinline__ void rw_wave_sync() {
@@ -63,7 +112,7 @@ __device__ __forceinline__ void rw_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Wave 0: grows `reach` (nw words over candidate indices) along the rows of
+// One wave: grows `reach` (nw words over candidate indices) along the rows of
 // `adj` (adj[c * nw + word]: the candidates one step from c) until nothing
 // changes.  Inlined, so that every access stays an LDS access: a generic
 // pointer would turn them into flat accesses, which the wave-level sync does
@@ -81,18 +130,19 @@ __device__ __forceinline__ void rw_reach(unsigned long long *reach, const unsign
                     if (w < nw) acc[w] |= adj[(size_t)c * nw + w];
             }
         }
-        int changed = 0;
+        bool changed = false;
+        unsigned long long nr[8];
 #pragma unroll
         for (int w = 0; w < 8; ++w) {
-            if (w < nw) {
-                const unsigned long long r = reach[w];
-                const unsigned long long nr = r | rw_wave_or(acc[w]);
-                changed |= nr != r;
-                rw_wave_sync();
-                if (lane == 0) reach[w] = nr;
-                rw_wave_sync();
-            }
+            const unsigned long long r = w < nw ? reach[w] : 0ull;
+            nr[w] = r | rw_wave_or((uint32_t)acc[w]) | ((unsigned long long)rw_wave_or((uint32_t)(acc[w] >> 32)) << 32);
+            changed |= nr[w] != r;
         }
+        rw_wave_sync();
+#pragma unroll
+        for (int w = 0; w < 8; ++w)
+            if (w < nw && lane == 0) reach[w] = nr[w];
+        rw_wave_sync();
         if (!changed) break;
     }
 }
@@ -107,7 +157,12 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
     const uint32_t iter = *a.iter_dev;
     if ((iter + 1u) % (uint32_t)a.rw_period != 0u) return;
     const int32_t run = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6, n_waves = nthr >> 6;
+    // one elimination step: the state's row over its sum, the rows with a
+    // nonzero entry in its column and those entries, how many, and the row's
+    // first nonzero entry
+    __shared__ double row_m[WE_RW_MAX_BINS], col_m[WE_RW_MAX_BINS];
+    __shared__ int32_t rows_m[WE_RW_MAX_BINS], n_rows[2], row_lo;   // counts by the step's parity
     const int32_t NB = a.n_bins, NW = (NB + 63) >> 6;
     const size_t base = (size_t)run * a.cap;
     const int32_t n = a.n_walk[run];
@@ -131,27 +186,31 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
     unsigned long long *bw = fw + 8;                                              // 8 words
     double *R = RL ? reinterpret_cast<double *>(lds + rw_small_bytes(NB)) : a.rw_R + (size_t)run * NB * NB;
 
-    // 1. W_j, and where each bin's walkers start (act doubles as that table)
+    // 1. W_j, and where each bin's walkers start and end (act and pos double as
+    // these tables)
     for (int32_t j = tid; j < NB; j += nthr) {
         double acc = 0.0;
+#pragma unroll 16
         for (int32_t i = 0; i < NB; ++i) acc = acc + F[(size_t)i * NB + j];
         Wc[j] = acc;
-        act[j] = -1;
+        act[j] = 0;
+        pos[j] = 0;
         fac[j] = 1.0;
     }
     __syncthreads();
-    for (int32_t k = tid; k < n; k += nthr)
-        if (k == 0 || bins[k] != bins[k - 1]) act[bins[k]] = k;
+    for (int32_t k = tid; k < n; k += nthr) {
+        const int32_t b = bins[k], before = k > 0 ? bins[k - 1] : -1, after = k + 1 < n ? bins[k + 1] : -1;
+        if (b != before) act[b] = k;
+        if (b != after) pos[b] = k + 1;
+    }
     __syncthreads();
     for (int32_t i = tid; i < NB; i += nthr) {
         double acc = 0.0;
-        int32_t c = 0;
-        for (int32_t k = act[i]; k >= 0 && k < n && bins[k] == i; ++k) {
-            acc = acc + w[k];
-            ++c;
-        }
+        const int32_t k0 = act[i], k1 = pos[i];
+#pragma unroll 16
+        for (int32_t k = k0; k < k1; ++k) acc = acc + w[k];
         wb[i] = acc;
-        pos[i] = c;
+        pos[i] = k1 - k0;
     }
     __syncthreads();
 
@@ -195,23 +254,32 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
             pred[t] = 0ull;
         }
         __syncthreads();
-        for (size_t t = tid; t < (size_t)nc * nc; t += nthr) {
-            const int32_t to = (int32_t)(t / nc), from = (int32_t)(t - (size_t)to * nc);
-            if (to != from && F[(size_t)cand[to] * NB + cand[from]] > 0.0) {
-                atomicOr(&succ[(size_t)from * NW + (to >> 6)], 1ull << (to & 63));
-                atomicOr(&pred[(size_t)to * NW + (from >> 6)], 1ull << (from & 63));
+        for (int32_t to = wave; to < nc; to += n_waves) {
+            const double *Frow = F + (size_t)cand[to] * NB;
+            bool edge[WE_RW_MAX_BINS / 64];
+#pragma unroll
+            for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                const int32_t from = 64 * q + lane;
+                edge[q] = from < nc && to != from && Frow[cand[min(from, nc - 1)]] > 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                const unsigned long long m = __ballot(edge[q]);
+                if (edge[q]) atomicOr(&succ[(size_t)(64 * q + lane) * NW + (to >> 6)], 1ull << (to & 63));
+                if (lane == 0 && q < NW) pred[(size_t)to * NW + q] = m;
             }
         }
         __syncthreads();
-        if (wave == 0) {
+        // wave 0 forward, wave 1 backward
+        if (wave < 2) {
             const int32_t pv = misc[2];
-            for (int32_t q = lane; q < NW; q += 64) {
-                fw[q] = q == (pv >> 6) ? 1ull << (pv & 63) : 0ull;
-                bw[q] = fw[q];
-            }
+            unsigned long long *reach = fw + 8 * wave;
+            for (int32_t q = lane; q < NW; q += 64) reach[q] = q == (pv >> 6) ? 1ull << (pv & 63) : 0ull;
             rw_wave_sync();
-            rw_reach(fw, succ, nc, NW, lane);
-            rw_reach(bw, pred, nc, NW, lane);
+            rw_reach(reach, succ + (size_t)wave * NB * NW, nc, NW, lane);
+        }
+        __syncthreads();
+        if (wave == 0) {
             int32_t na = 0;
             for (int32_t c0 = 0; c0 < nc; c0 += 64) {
                 const int32_t c = c0 + lane;
@@ -226,36 +294,78 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
         const int32_t na = misc[1];
         if (na >= 2) {
             // 4. rates on the component, state reduction, back substitution
-            for (size_t t = tid; t < (size_t)na * na; t += nthr) {
-                const int32_t to = (int32_t)(t / na), from = (int32_t)(t - (size_t)to * na);
-                R[(size_t)from * na + to] =
-                    from == to ? 0.0 : F[(size_t)act[to] * NB + act[from]] / Wc[act[from]];
+            for (int32_t to = wave; to < na; to += n_waves) {
+                const double *Frow = F + (size_t)act[to] * NB;
+                double f[WE_RW_MAX_BINS / 64];
+#pragma unroll
+                for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                    const int32_t from = min(64 * q + lane, na - 1);
+                    f[q] = 64 * q < na ? Frow[act[from]] : 0.0;
+                }
+#pragma unroll
+                for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                    const int32_t from = 64 * q + lane;
+                    if (from < na) R[(size_t)from * na + to] = from == to ? 0.0 : f[q] / Wc[act[from]];
+                }
             }
+            if (tid < 2) n_rows[tid] = 0;
             __syncthreads();
             for (int32_t m = na - 1; m >= 1; --m) {
-                if (wave == 0) {
+                for (int32_t i0 = wave * 64; i0 < m; i0 += nthr) {
+                    const int32_t i = i0 + lane;
+                    const double rim = i < m ? R[(size_t)i * na + m] : 0.0;
+                    const unsigned long long nz = __ballot(rim != 0.0);
+                    int32_t at = 0;
+                    if (lane == 0 && nz) at = atomicAdd(&n_rows[m & 1], (int32_t)__popcll(nz));
+                    at = __shfl(at, 0, 64) + (int32_t)__popcll(nz & ((1ull << lane) - 1ull));
+                    if (rim != 0.0) {
+                        rows_m[at] = i;
+                        col_m[at] = rim;
+                    }
+                }
+                if (wave == n_waves - 1) {   // the last wave has no part of the column (m < 512)
+                    double v[WE_RW_MAX_BINS / 64];
                     double p = 0.0;
-                    for (int32_t j = lane; j < m; j += 64) p = p + R[(size_t)m * na + j];
+                    int32_t lo = m;
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                        const int32_t j = 64 * q + lane;
+                        v[q] = j < m ? R[(size_t)m * na + j] : 0.0;
+                    }
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                        if (64 * q + lane < m) p = p + v[q];
+                        const unsigned long long nz = __ballot(v[q] != 0.0);
+                        if (nz) lo = min(lo, 64 * q);
+                    }
                     const double s = rw_wave_sum(p);
-                    if (s > 0.0)
-                        for (int32_t j = lane; j < m; j += 64) R[(size_t)m * na + j] = R[(size_t)m * na + j] / s;
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q)
+                        if (64 * q + lane < m) row_m[64 * q + lane] = s > 0.0 ? v[q] / s : v[q];
                     if (lane == 0) {
                         sm[m] = s;
+                        row_lo = lo;
                         if (!(s > 0.0)) misc[3] = 1;
                     }
                 }
                 __syncthreads();
                 if (misc[3]) break;
-                // one row per wave: rows with r(i -> m) = 0 are skipped whole
-                // (the rates join neighbouring bins only, so most rows are, and
-                // the elimination keeps that band); each entry gets the same
-                // single update as before, so the result is unchanged
-                const int32_t n_waves = nthr >> 6;
-                for (int32_t i = wave; i < m; i += n_waves) {
-                    const double rim = R[(size_t)i * na + m];
-                    if (rim == 0.0) continue;
-                    for (int32_t j = lane; j < m; j += 64)
-                        if (j != i) R[(size_t)i * na + j] = R[(size_t)i * na + j] + rim * R[(size_t)m * na + j];
+                const int32_t nr = n_rows[m & 1], lo = row_lo;
+                if (tid == 0) n_rows[(m & 1) ^ 1] = 0;
+                for (int32_t q = wave; q < nr; q += n_waves) {
+                    const int32_t i = rows_m[q];
+                    const double rim = col_m[q];
+                    double *Ri = R + (size_t)i * na;
+                    for (int32_t j0 = lo + lane; j0 < m; j0 += 256) {
+                        double v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[u] = j0 + 64 * u < m ? Ri[j0 + 64 * u] : 0.0;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int32_t j = j0 + 64 * u;
+                            if (j < m && j != i) Ri[j] = v[u] + rim * row_m[j];
+                        }
+                    }
                 }
                 __syncthreads();
             }
@@ -263,9 +373,24 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
                 if (lane == 0) pi[0] = 1.0;
                 rw_wave_sync();
                 bool pos_ok = true;
+                // the next state's column is read while this one's sum is formed
+                double col[WE_RW_MAX_BINS / 64], nxt[WE_RW_MAX_BINS / 64];
+                auto column = [&](int32_t m, double (&c)[WE_RW_MAX_BINS / 64]) {
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) {
+                        const int32_t i = 64 * q + lane;
+                        c[q] = i < m && m < na ? R[(size_t)i * na + m] : 0.0;
+                    }
+                };
+                column(1, nxt);
                 for (int32_t m = 1; m < na; ++m) {
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q) col[q] = nxt[q];
+                    column(m + 1, nxt);
                     double p = 0.0;
-                    for (int32_t i = lane; i < m; i += 64) p = p + pi[i] * R[(size_t)i * na + m];
+#pragma unroll
+                    for (int q = 0; q < WE_RW_MAX_BINS / 64; ++q)
+                        if (64 * q + lane < m) p = p + pi[64 * q + lane] * col[q];
                     const double v = rw_wave_sum(p) / sm[m];
                     pos_ok = pos_ok && v > 0.0;
                     if (lane == 0) pi[m] = v;
