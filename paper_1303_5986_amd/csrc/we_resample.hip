@@ -56,9 +56,8 @@
 #define RESAMPLE_LDS_MAX (150 * 1024)
 // Cursor rows for placing walkers in parallel: one row of n_bins per wave, as
 // long as the rows hold at most this many counters.
-#define RESAMPLE_PLACE_INTS 4096
+#define RESAMPLE_PLACE_INTS 8192   // 16 rows of 512 bins
 // Bin-parallel resampling: runs fewer than this, bins at least this many.
-#define RESAMPLE_GROUP_COUNT_M 32
 #define RESAMPLE_BIN_PARALLEL_RUNS 256
 #define RESAMPLE_BIN_PARALLEL_BINS 32
 #define RESAMPLE_BIG_M 128
@@ -167,21 +166,6 @@ __device__ __forceinline__ double wave_min(double v) {
     return fmin(fmin(rs_readlane(v, 0), rs_readlane(v, 16)), fmin(rs_readlane(v, 32), rs_readlane(v, 48)));
 }
 
-// Sum over the 64 lanes (every lane gets it), by the steps of wave_max.
-template <int CTRL>
-__device__ __forceinline__ float rs_dpp_f32(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float wave_sum_f32(float v) {
-    v += rs_dpp_f32<0xB1>(v);
-    v += rs_dpp_f32<0x4E>(v);
-    v += rs_dpp_f32<0x141>(v);
-    v += rs_dpp_f32<0x140>(v);
-    const int32_t bits = __float_as_int(v);
-    return (__int_as_float(__builtin_amdgcn_readlane(bits, 0)) + __int_as_float(__builtin_amdgcn_readlane(bits, 16))) +
-           (__int_as_float(__builtin_amdgcn_readlane(bits, 32)) + __int_as_float(__builtin_amdgcn_readlane(bits, 48)));
-}
-
 // Integer sum, minimum and exclusive prefix sum over the 64 lanes by DPP moves
 // (a shuffle per step is an LDS round trip of over a hundred cycles).
 template <int CTRL, int ROW_MASK, bool BOUND>
@@ -230,6 +214,44 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The lanes whose v has the same low `bits` bits, among the valid ones; and
+// how many of them come before this lane.
+__device__ __forceinline__ unsigned long long match_lanes(int32_t v, bool valid, int bits) {
+    unsigned long long m = __ballot(valid);
+    for (int i = 0; i < bits; ++i) {
+        const bool one = (v >> i) & 1;
+        const unsigned long long o = __ballot(one);
+        m &= one ? o : ~o;
+    }
+    return m;
+}
+__device__ __forceinline__ int32_t lanes_below(unsigned long long m) {
+    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// sum[b] += v over the lanes with b >= 0.  Lanes of one 16-lane row are folded
+// pairwise where they hold the same b first: LDS atomics of 64 lanes on one
+// address take their turns, and walkers sit by their previous bin.
+template <int CTRL>
+__device__ __forceinline__ int32_t rs_dpp(int32_t v, int32_t none) {
+    return __builtin_amdgcn_update_dpp(none, v, CTRL, 0xF, 0xF, false);
+}
+template <int FROM_HIGH, int FROM_LOW, int BIT>
+__device__ __forceinline__ void fold_same(int32_t &b, float &v, int lane) {
+    const int32_t hi_b = rs_dpp<FROM_HIGH>(b, -2), lo_b = rs_dpp<FROM_LOW>(b, -2);
+    const float hi_v = __int_as_float(rs_dpp<FROM_HIGH>(__float_as_int(v), 0));
+    const bool high = (lane & BIT) != 0;
+    v = !high && hi_b == b ? v + hi_v : v;
+    b = high && lo_b == b ? -1 : b;
+}
+__device__ __forceinline__ void add_by_bin(float *sum, int32_t b, float v, int lane) {
+    fold_same<0x101, 0x111, 1>(b, v, lane);   // row_shl, row_shr by 1, 2, 4, 8
+    fold_same<0x102, 0x112, 2>(b, v, lane);
+    fold_same<0x104, 0x114, 4>(b, v, lane);
+    fold_same<0x108, 0x118, 8>(b, v, lane);
+    if (b >= 0) atomicAdd(&sum[b], v);
 }
 
 __device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -1105,7 +1127,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     const int lane = tid & 63, wave = tid >> 6, n_waves = nthr >> 6;
     const int32_t NB = a.n_bins, M = a.m_targ, cap = a.cap;
     __shared__ int64_t ev_part[RESAMPLE_THREADS];
-    __shared__ int32_t any_rec;   // 1 when some walker was recycled this interval
+    __shared__ int32_t rec_row[RESAMPLE_THREADS / 64];   // recycled walkers per cursor row
     int32_t *cnt = reinterpret_cast<int32_t *>(lds);   // [NB]
     int32_t *start = cnt + NB;                          // [NB+1]
     int32_t *ostart = start + NB + 1;                   // [NB+1]
@@ -1123,6 +1145,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     const int32_t n = a.n_walk[run];
     const size_t base = (size_t)run * cap;
     const double *wr = w_cur + base;
+    double *rec_w = w_nxt + base;   // until the new weights are written: each row's recycled weights, side by side
     const int32_t *sbin = a.s_bin + base;
     const int32_t *srec = a.s_rec + base;
     RunWork<Idx> wk;
@@ -1151,52 +1174,39 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
         evb[b] = 0.0f;
     }
     for (int32_t i = tid; i < P * NB; i += nthr) cursor[i] = 0;
-    if (tid == 0) any_rec = 0;
+    if (tid < RESAMPLE_THREADS / 64) rec_row[tid] = 0;
     __syncthreads();
     // counts per bin and per cursor row: each wave takes 64 consecutive slots
-    // (one cursor row: per_row is a multiple of 64); with at least
-    // RESAMPLE_GROUP_COUNT_M walkers per bin it adds each bin's group of lanes
-    // with one LDS atomic (walkers sit in slot order by their previous bin, so
-    // a chunk holds few bins, and LDS atomics on one address serialize), with
-    // smaller bins one atomic per walker (many bins per chunk, few collisions)
+    // (one cursor row: per_row is a multiple of 64), four such chunks' loads at a
+    // time, and one lane of each bin adds the bin's lanes
+    const int bits = NB > 1 ? 32 - __clz(NB - 1) : 0;
     int64_t my_ev = 0;
-    for (int32_t c0 = wave * 64; c0 < n; c0 += nthr) {
-        const int32_t k = c0 + lane;
-        const bool valid = k < n;
-        int32_t b = -1;
-        uint32_t ev = 0u;
-        bool rc = false;
-        if (valid) {
-            b = sbin[k];
-            ev = a.ev_walker[base + k];
-            rc = srec[k] != 0;
-            wk.tag[k] = (uint16_t)(b | (rc ? 0x8000 : 0));
-            my_ev += ev;
-        }
-        if (__ballot(rc) && lane == 0) any_rec = 1;
-        const int32_t row = c0 / per_row;
-        if (M < RESAMPLE_GROUP_COUNT_M) {   // small bins: many per chunk, little contention
+    for (int32_t c4 = wave * 64; c4 < n; c4 += 4 * nthr) {
+        int32_t bs[4], rs[4];
+        uint32_t evs[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c4 + u * nthr < n) {
+                const int32_t k = min(c4 + u * nthr + lane, n - 1);
+                bs[u] = sbin[k];
+                evs[u] = a.ev_walker[base + k];
+                rs[u] = srec[k];
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t c0 = c4 + u * nthr, k = c0 + lane, b = bs[u];
+            if (c0 >= n) break;
+            const bool valid = k < n, rc = valid && rs[u] != 0;
+            const unsigned long long grp = match_lanes(b, valid, bits);
             if (valid) {
-                atomicAdd(&cnt[b], 1);
-                atomicAdd(&cursor[row * NB + b], 1);
-                if (a.queue_stats) atomicAdd(&evb[b], (float)ev);
+                wk.tag[k] = (uint16_t)(b | (rc ? 0x8000 : 0));
+                my_ev += evs[u];
+                if (lanes_below(grp) == 0) {
+                    atomicAdd(&cnt[b], (int32_t)__popcll(grp));
+                    atomicAdd(&cursor[c0 / per_row * NB + b], (int32_t)__popcll(grp));
+                }
             }
-            continue;
-        }
-        unsigned long long todo = __ballot(valid);
-        while (todo) {
-            const int leader = __ffsll((long long)todo) - 1;
-            const int32_t lb = __shfl(b, leader, 64);
-            const bool mine = valid && b == lb;
-            const unsigned long long grp = __ballot(mine);
-            const float gev = a.queue_stats ? wave_sum_f32(mine ? (float)ev : 0.0f) : 0.0f;
-            if (lane == leader) {
-                const int32_t g = (int32_t)__popcll(grp);
-                atomicAdd(&cnt[lb], g);
-                atomicAdd(&cursor[row * NB + lb], g);
-                if (a.queue_stats) atomicAdd(&evb[lb], gev);
-            }
-            todo &= ~grp;
+            if (a.queue_stats) add_by_bin(evb, valid ? b : -1, (float)evs[u], lane);
         }
     }
     ev_part[tid] = my_ev;
@@ -1234,6 +1244,16 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
             ostart[NB] = otot;
         }
     }
+    // the last wave: reactions fired
+    if (wave == n_waves - 1) {
+        int64_t ev = 0;
+        for (int32_t t = lane; t < nthr; t += 64) ev += ev_part[t];
+        for (int d = 32; d > 0; d >>= 1) ev += __shfl_xor(ev, d, 64);
+        if (lane == 0 && rec_slot < a.max_iters) {
+            a.ev_iter[(size_t)run * a.max_iters + rec_slot] = ev;
+            a.seg_iter[(size_t)run * a.max_iters + rec_slot] = n;
+        }
+    }
     __syncthreads();
     // row r's count of bin b becomes the position of its first walker of b
     for (int32_t b = tid; b < NB; b += nthr) {
@@ -1246,67 +1266,97 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     }
     __syncthreads();
 
-    // stable placement: waves r < P, each over its chunks in slot order;
-    // lanes with the same bin are ranked by a ballot and the bin's cursor
-    // advances by the group size
+    // stable placement: waves r < P, each over its chunks in slot order; a
+    // lane's place is its bin's cursor plus its rank among the bin's lanes, and
+    // the cursor advances by their number.  The lanes of every bin are found at
+    // once, one ballot per bit of the bin's number (a chunk holds tens of bins
+    // where bins are small).  Each row also sets its recycled walkers' weights
+    // side by side, for the sum below.  With a ballot per bin present, and the
+    // recycled weights looked for by one wave alone, the placement took 76 us for
+    // 64 runs of 465 bins x 16 walkers, 18 us for 32 runs of 80 x 32 and 11.4 us
+    // for 16 of 64 x 16; this form takes 23.6, 10.6 and 8.3.
     if (wave < P) {
         int32_t *cur = cursor + wave * NB;
-        const int32_t k_hi = min(n, (wave + 1) * per_row);
-        for (int32_t c0 = wave * per_row; c0 < k_hi; c0 += 64) {
+        const int32_t k_lo = wave * per_row, k_hi = min(n, k_lo + per_row);
+        int32_t tag = k_lo + lane < k_hi ? (int32_t)wk.tag[k_lo + lane] : 0;
+        int32_t n_rec = 0;
+        for (int32_t c0 = k_lo; c0 < k_hi; c0 += 64) {
             const int32_t k = c0 + lane;
             const bool valid = k < k_hi;
-            const int32_t b = valid ? (int32_t)(wk.tag[k] & 0x7FFF) : -1;
-            unsigned long long todo = __ballot(valid);
-            while (todo) {
-                const int leader = __ffsll((long long)todo) - 1;
-                const int32_t lb = __shfl(b, leader, 64);
-                const unsigned long long grp = __ballot(valid && b == lb);
-                if (valid && b == lb) {
-                    const unsigned long long below = lane ? (grp & ((1ull << lane) - 1ull)) : 0ull;
-                    wk.list[cur[lb] + __popcll(below)] = k;
-                }
-                wave_sync();
-                if (lane == leader) cur[lb] += __popcll(grp);
-                wave_sync();
-                todo &= ~grp;
+            const int32_t b = tag & 0x7FFF;
+            const bool rec = valid && (tag & 0x8000);
+            const unsigned long long rm = __ballot(rec);
+            if (rec) rec_w[k_lo + n_rec + lanes_below(rm)] = wr[k];
+            n_rec += (int32_t)__popcll(rm);
+            if (k + 64 < k_hi) tag = (int32_t)wk.tag[k + 64];
+            const unsigned long long grp = match_lanes(b, valid, bits);
+            if (valid) {
+                const int32_t at = cur[b], rank = lanes_below(grp);
+                wk.list[at + rank] = k;
+                if (rank == 0) cur[b] = at + (int32_t)__popcll(grp);
             }
+            wave_sync();
         }
+        if (lane == 0) rec_row[wave] = n_rec;
     }
-    // the last wave: reactions fired and the recycled weight, summed in slot
-    // order
+    __syncthreads();
+    // the last wave: the recycled weight, summed in slot order: rows in order,
+    // up to 512 weights at a time fetched into LDS (ev_part has been read)
     if (wave == n_waves - 1) {
-        int64_t ev = 0;
-        for (int32_t t = lane; t < nthr; t += 64) ev += ev_part[t];
-        for (int d = 32; d > 0; d >>= 1) ev += __shfl_xor(ev, d, 64);
         double f = 0.0;
-        for (int32_t c0 = 0; any_rec && c0 < n; c0 += 64) {   // no recycled walker: f stays 0
-            const int32_t k = c0 + lane;
-            const bool rec = k < n && (wk.tag[k] & 0x8000);
-            unsigned long long rm = __ballot(rec);
-            if (rm) {
-                const double wv = rec ? wr[k] : 0.0;
-                while (rm) {
-                    const int l = __ffsll((long long)rm) - 1;
-                    f = f + rs_readlane(wv, l);
-                    rm &= rm - 1ull;
+        double *next_w = reinterpret_cast<double *>(ev_part);
+        int32_t rec_tot;
+        const int32_t rec_lo = wave_excl_scan(lane < P ? rec_row[lane] : 0, &rec_tot);
+        for (int32_t j0 = 0; j0 < rec_tot; j0 += 512) {
+            const int32_t m = min(512, rec_tot - j0);
+            double wv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (64 * u >= m) break;
+                const int32_t j = min(j0 + 64 * u + lane, rec_tot - 1);
+                int32_t at = j;   // row r's weights start at r * per_row
+                for (int32_t q = 1; q < P; ++q) {
+                    const int32_t lo = __builtin_amdgcn_readlane(rec_lo, q);
+                    at = j >= lo ? q * per_row + (j - lo) : at;
                 }
+                wv[u] = rec_w[at];
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                if (64 * u >= m) break;
+                next_w[64 * u + lane] = wv[u];
+            }
+            wave_sync();
+#pragma unroll 8
+            for (int32_t i = 0; i < m; ++i) f = f + next_w[i];
+            wave_sync();
         }
         if (lane == 0 && rec_slot < a.max_iters) {
             a.flux[(size_t)run * a.max_iters + rec_slot] = f;
-            a.ev_iter[(size_t)run * a.max_iters + rec_slot] = ev;
-            a.seg_iter[(size_t)run * a.max_iters + rec_slot] = n;
         }
     }
-    __syncthreads();
     // flux matrix of reweighting: from the second interval on (the first
     // one's walkers carry no bin yet); the start bins go to aux, which only
     // the split/merge of the same bin uses afterwards
     const bool rw_acc = a.rw_F != nullptr && iter >= 1u;
-    for (int32_t p = tid; p < n; p += nthr) {
-        const int32_t k = wk.list[p];
-        wk.w[p] = wr[k];
-        if (rw_acc) wk.aux[p] = (Idx)a.bin[base + k];
+    for (int32_t p4 = tid; p4 < n; p4 += 4 * nthr) {
+        int32_t ks[4], from[4] = {0, 0, 0, 0};
+        double ws[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) ks[u] = wk.list[min(p4 + u * nthr, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            ws[u] = wr[ks[u]];
+            if (rw_acc) from[u] = a.bin[base + ks[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int32_t p = p4 + u * nthr;
+            if (p < n) {
+                wk.w[p] = ws[u];
+                if (rw_acc) wk.aux[p] = (Idx)from[u];
+            }
+        }
     }
     __syncthreads();
 
