@@ -192,13 +192,13 @@ struct SimArgs {
     double *rw_F;                        // [n_runs][n_bins][n_bins] flux matrix F[i][j]
     double *rw_R;                        // [n_runs][n_bins][n_bins] solve scratch (null: in LDS)
     int32_t *rw_stat;                    // [n_runs][2] events applied, skipped
-    float *ev_bin;                       // [n_bins][seg_rep] events of the walkers that ended in each bin
-    int32_t *n_bin;                      // [n_bins][seg_rep] walkers that ended in each bin
+    float *ev_bin;                       // [seg_rep][n_bins] events of the walkers that ended in each bin
+    int32_t *n_bin;                      // [seg_rep][n_bins] walkers that ended in each bin
     int32_t seg_rep;                     // counters per bin (spread over replicas, picked by run,
                                          //   against atomic contention): min(128, 16384/n_bins, n_runs/16), >= 1
-    int32_t *occ_bin;                    // [n_bins][seg_rep] queue segments per counter
-    int32_t *seg_off;                    // [n_bins][seg_rep] first queue segment of each counter
-    int32_t *seg_cur;                    // [n_bins][seg_rep]
+    int32_t *occ_bin;                    // [seg_rep][n_bins] queue segments per counter
+    int32_t *seg_off;                    // [seg_rep][n_bins] first queue segment of each counter
+    int32_t *seg_cur;                    // [seg_rep][n_bins]
     int2 *seg;                           // [n_runs * n_bins] (first slot run*cap + j*m_targ, walkers)
     uint32_t *queue;                     // [2] next walker index, number of segments
     uint32_t *heads;                     // [n_heads] the lane kernels' queue heads, WE_HEAD_STRIDE

@@ -1127,7 +1127,10 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     const int lane = tid & 63, wave = tid >> 6, n_waves = nthr >> 6;
     const int32_t NB = a.n_bins, M = a.m_targ, cap = a.cap;
     __shared__ int64_t ev_part[RESAMPLE_THREADS];
-    __shared__ int32_t rec_row[RESAMPLE_THREADS / 64];   // recycled walkers per cursor row
+    // once the event totals are read: recycled weights to add, then the
+    // recycled walkers per cursor row
+    double *next_w = reinterpret_cast<double *>(ev_part);
+    int32_t *rec_row = reinterpret_cast<int32_t *>(ev_part + RESAMPLE_THREADS / 2);
     int32_t *cnt = reinterpret_cast<int32_t *>(lds);   // [NB]
     int32_t *start = cnt + NB;                          // [NB+1]
     int32_t *ostart = start + NB + 1;                   // [NB+1]
@@ -1174,7 +1177,6 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
         evb[b] = 0.0f;
     }
     for (int32_t i = tid; i < P * NB; i += nthr) cursor[i] = 0;
-    if (tid < RESAMPLE_THREADS / 64) rec_row[tid] = 0;
     __syncthreads();
     // counts per bin and per cursor row: each wave takes 64 consecutive slots
     // (one cursor row: per_row is a multiple of 64), four such chunks' loads at a
@@ -1216,7 +1218,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     if (a.queue_stats)
         for (int32_t b = tid; b < NB; b += nthr)
             if (cnt[b] > 0) {
-                const int32_t c = b * a.seg_rep + run % a.seg_rep;
+                const int32_t c = run % a.seg_rep * NB + b;
                 atomicAdd(&a.ev_bin[c], evb[b]);
                 atomicAdd(&a.n_bin[c], cnt[b]);
             }
@@ -1301,10 +1303,9 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     }
     __syncthreads();
     // the last wave: the recycled weight, summed in slot order: rows in order,
-    // up to 512 weights at a time fetched into LDS (ev_part has been read)
+    // up to 512 weights at a time fetched into LDS
     if (wave == n_waves - 1) {
         double f = 0.0;
-        double *next_w = reinterpret_cast<double *>(ev_part);
         int32_t rec_tot;
         const int32_t rec_lo = wave_excl_scan(lane < P ? rec_row[lane] : 0, &rec_tot);
         for (int32_t j0 = 0; j0 < rec_tot; j0 += 512) {

@@ -25,12 +25,11 @@ __global__ __launch_bounds__(256) void queue_count_kernel(SimArgs a) {
     const int64_t first = (int64_t)j * a.m_targ;
     if (first >= a.n_walk[run]) return;
     const int32_t b = min(max(a.bin[(size_t)run * a.cap + first], 0), a.n_bins - 1);
-    atomicAdd(&a.occ_bin[b * a.seg_rep + run % a.seg_rep], 1);
+    atomicAdd(&a.occ_bin[run % a.seg_rep * a.n_bins + b], 1);
 }
 
 // Bitonic sort of 64 (key, bin) pairs held one per lane, descending by key
-// and, for equal keys, by bin: the comparator of the block sort below, with
-// shuffles in place of LDS and barriers.
+// and, for equal keys, by bin.
 __device__ __forceinline__ void wave_sort_desc(float &key, int32_t &idx, int lane) {
     for (int size = 2; size <= 64; size <<= 1)
         for (int d = size >> 1; d > 0; d >>= 1) {
@@ -48,38 +47,49 @@ __device__ __forceinline__ void wave_sort_desc(float &key, int32_t &idx, int lan
         }
 }
 
-// Bin order and queue offsets: one block.  Sorts the bins by mean events
-// per walker (descending; ties: higher bin first), lays out their segments
-// in that order, and clears the statistics and the queue.  SMALL (few runs,
-// queue_small below): the same block first counts the segments into LDS
-// and afterwards lists them itself, so the three steps are one launch.
+// Bin order and queue offsets: one block.  Orders the bins by mean events per
+// walker, descending, lays out their segments in that order, and clears the
+// statistics and the queue.  SMALL (few runs, queue_small below): the same
+// block first counts the segments into LDS and afterwards lists them itself,
+// so the three steps are one launch.
+// Counters lie [replica][bin], so that a run's adds and the reads here are of
+// consecutive words.  The order needs no sort: keys are binary floats >= 0, so
+// their bits order them, and a histogram over the distance to the largest key in
+// steps of 2^-7 of a factor of two (1024 of them: down to 1/256 of the largest)
+// gives every bin its place with one LDS atomic.  Bins of one step come in any
+// order.  What bounds it is the latency of its few phases: 465 bins, 64 runs
+// took 36 us, 60 bins, 2048 runs 16.8, 80 bins, 32 runs 17.7 and 100 bins, 10 runs
+// 16 us with a bitonic sort over the block (a barrier per step, one wave per bin
+// for the sums); this form takes 5.1, 8.5, 8.2 and 6.4 us.  The counters' layout
+// also took the runs' adds in resampling (2048 runs: 61 -> 55.5 us with them).
 #define QUEUE_MAX_BINS 8192
-#define QUEUE_CHUNK 16   // counters per thread: NB * seg_rep <= 16384 over 1024 threads
 #define QUEUE_SMALL_SEGS 4096
 #define QUEUE_SMALL_BINS 1024
+#define QUEUE_STEPS 1024
+#define QUEUE_STEP_SHIFT 16
 template <bool SMALL>
 __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
     constexpr int32_t KB = SMALL ? QUEUE_SMALL_BINS : QUEUE_MAX_BINS;
-    __shared__ float key[KB];
-    __shared__ int16_t idx[KB];
-    __shared__ int32_t part[1024];
+    __shared__ uint32_t key[KB];         // mean events per walker, as bits
+    __shared__ int32_t at[KB];           // the bin's segments, then their place within its step
+    __shared__ int32_t step[QUEUE_STEPS];
+    __shared__ float part_ev[1024];      // several threads per bin: their sums
+    __shared__ int32_t part_n[1024], part_occ[1024];
+    __shared__ uint32_t key_max;
+    __shared__ int32_t wave_tot[16];
     // SMALL only: per counter, segments / first position / fill cursor, and
     // each (run, segment)'s bin (-1: no walkers)
     __shared__ int32_t s_occ[SMALL ? QUEUE_SMALL_BINS : 1];
     __shared__ int32_t s_off[SMALL ? QUEUE_SMALL_BINS : 1];
-    __shared__ int32_t s_cur[SMALL ? QUEUE_SMALL_BINS : 1];
     __shared__ int16_t s_bin[SMALL ? QUEUE_SMALL_SEGS : 1];
     const int32_t NB = a.n_bins, tid = threadIdx.x, nthr = blockDim.x;
-    int32_t P = 1;
-    while (P < NB) P <<= 1;
     const int32_t rep = a.seg_rep, NC = NB * rep;
-    const int lane = tid & 63, wv = tid >> 6, nwv = nthr >> 6;
+    const int lane = tid & 63, wv = tid >> 6;
     const int32_t n_seg = a.n_runs * NB;
+    step[tid] = 0;
+    if (tid == 0) key_max = 0u;
     if constexpr (SMALL) {
-        for (int32_t c = tid; c < NC; c += nthr) {
-            s_occ[c] = 0;
-            s_cur[c] = 0;
-        }
+        if (tid < NC) s_occ[tid] = 0;
         __syncthreads();
         for (int32_t sg = tid; sg < n_seg; sg += nthr) {
             const int32_t run = sg / NB, j = sg - run * NB;
@@ -87,124 +97,104 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
             int32_t b = -1;
             if (first < a.n_walk[run]) {
                 b = min(max(a.bin[(size_t)run * a.cap + first], 0), NB - 1);
-                atomicAdd(&s_occ[b * rep + run % rep], 1);
+                atomicAdd(&s_occ[run % rep * NB + b], 1);
             }
             s_bin[sg] = (int16_t)b;
         }
     }
-    // key of each bin: its replicas' event and walker counts summed by one
-    // wave (rep <= 128: two entries per lane at most); four bins per wave at
-    // a time, so that their loads are in flight together
-    for (int32_t b0 = wv; b0 < P; b0 += 4 * nwv) {
-        float ev[4];
-        int32_t nw[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int32_t b = b0 + u * nwv;
-            ev[u] = 0.0f;
-            nw[u] = 0;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int32_t r = lane + 64 * q;
-                if (b < NB && r < rep) {
-                    ev[u] += a.ev_bin[b * rep + r];
-                    nw[u] += a.n_bin[b * rep + r];
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            for (int d = 32; d > 0; d >>= 1) {
-                ev[u] += __shfl_xor(ev[u], d, 64);
-                nw[u] += __shfl_xor(nw[u], d, 64);
-            }
-            const int32_t b = b0 + u * nwv;
-            if (lane == 0 && b < P) {
-                key[b] = b < NB ? (nw[u] > 0 ? ev[u] / (float)nw[u] : 0.0f) : -1.0f;
-                idx[b] = (int16_t)b;
-            }
-        }
-    }
     __syncthreads();
-    if (P <= 64) {
-        // at most 64 keys: wave 0 sorts them in registers (slots past P hold
-        // a key below every real and padding key, so they sort last)
-        if (wv == 0) {
-            float k = lane < P ? key[lane] : -2.0f;
-            int32_t b = lane < P ? (int32_t)idx[lane] : 64 + lane;
-            wave_sort_desc(k, b, lane);
-            if (lane < P) {
-                key[lane] = k;
-                idx[lane] = (int16_t)b;
-            }
+    auto occ = [&](int32_t c) { return SMALL ? s_occ[SMALL ? c : 0] : a.occ_bin[c]; };
+    // G threads per bin, each over every G-th replica
+    const int32_t G = max(1, min(1024 / NB, rep));
+    uint32_t my_max = 0u;
+    for (int32_t i = tid; i < G * NB; i += nthr) {
+        const int32_t sub = i / NB, b = i - sub * NB;
+        float ev = 0.0f;
+        int32_t nw = 0, oc = 0;
+#pragma unroll 8
+        for (int32_t r = sub; r < rep; r += G) {
+            ev += a.ev_bin[r * NB + b];
+            nw += a.n_bin[r * NB + b];
+            oc += occ(r * NB + b);
         }
+        if (G > 1) {
+            part_ev[i] = ev;
+            part_n[i] = nw;
+            part_occ[i] = oc;
+        } else {
+            key[b] = __float_as_uint(nw > 0 ? ev / (float)nw : 0.0f);
+            at[b] = oc;
+            my_max = max(my_max, key[b]);
+        }
+    }
+    if (G > 1) {
         __syncthreads();
-    } else {
-        // bitonic sort, descending by (key, bin)
-        for (int32_t size = 2; size <= P; size <<= 1)
-            for (int32_t d = size >> 1; d > 0; d >>= 1) {
-                for (int32_t i = tid; i < P; i += nthr) {
-                    const int32_t j = i ^ d;
-                    if (j > i) {
-                        const bool desc = (i & size) == 0;
-                        const float ki = key[i], kj = key[j];
-                        const int32_t bi = idx[i], bj = idx[j];
-                        const bool i_first = ki > kj || (ki == kj && bi > bj);
-                        if (i_first != desc) {
-                            key[i] = kj; key[j] = ki;
-                            idx[i] = (int16_t)bj; idx[j] = (int16_t)bi;
-                        }
-                    }
-                }
-                __syncthreads();
+        if (tid < NB) {
+            float ev = 0.0f;
+            int32_t nw = 0, before = 0;
+            for (int32_t sub = 0; sub < G; ++sub) {
+                const int32_t i = sub * NB + tid, oc = part_occ[i];
+                ev += part_ev[i];
+                nw += part_n[i];
+                part_occ[i] = before;
+                before += oc;
             }
+            key[tid] = __float_as_uint(nw > 0 ? ev / (float)nw : 0.0f);
+            at[tid] = before;
+            my_max = key[tid];
+        }
     }
-    // exclusive prefix of the segment counters in sorted bin order (the
-    // replicas of a bin consecutive): per-thread chunks of that sequence,
-    // at most QUEUE_CHUNK long (NB * rep <= 16384), held in registers
-    const int32_t per = (NC + nthr - 1) / nthr;
-    const int32_t lo = min(tid * per, NC), hi = min(lo + per, NC);
-    auto counter = [&](int32_t i) { return (int32_t)idx[i / rep] * rep + i % rep; };
-    int32_t cnt[QUEUE_CHUNK];
-    int32_t acc = 0;
-#pragma unroll
-    for (int q = 0; q < QUEUE_CHUNK; ++q) {
-        cnt[q] = lo + q < hi ? (SMALL ? s_occ[counter(lo + q)] : a.occ_bin[counter(lo + q)]) : 0;
-        acc += cnt[q];
-    }
-    // block-wide exclusive scan of the chunk sums: within waves, then over
-    // the wave totals
-    int32_t incl = acc;
+    for (int d = 32; d > 0; d >>= 1) my_max = max(my_max, (uint32_t)__shfl_xor((int)my_max, d, 64));
+    if (lane == 0 && my_max > 0u) atomicMax(&key_max, my_max);
+    __syncthreads();
+    auto step_of = [&](int32_t b) {
+        return (int32_t)min((uint32_t)(QUEUE_STEPS - 1), (key_max - key[b]) >> QUEUE_STEP_SHIFT);
+    };
+    for (int32_t b = tid; b < NB; b += nthr) at[b] = atomicAdd(&step[step_of(b)], at[b]);
+    __syncthreads();
+    // first position of each step
+    const int32_t mine = step[tid];
+    int32_t incl = mine;
     for (int d = 1; d < 64; d <<= 1) {
         const int32_t y = __shfl_up(incl, d, 64);
         if (lane >= d) incl += y;
     }
-    if (lane == 63) part[wv] = incl;
+    if (lane == 63) wave_tot[wv] = incl;
     __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int32_t t = 0; t < nthr / 64; ++t) {
-            const int32_t v = part[t];
-            part[t] = run;
-            run += v;
-        }
+    for (int w = 0; w < wv; ++w) incl += wave_tot[w];
+    step[tid] = incl - mine;
+    if (tid == nthr - 1) {
         a.queue[0] = 0u;
-        a.queue[1] = (uint32_t)run;
+        a.queue[1] = (uint32_t)incl;
     }
     clear_heads(a, tid);
     __syncthreads();
-    acc = part[wv] + incl - acc;
+    for (int32_t i = tid; i < G * NB; i += nthr) {
+        const int32_t sub = i / NB, b = i - sub * NB;
+        int32_t pos = step[step_of(b)] + at[b] + (G > 1 ? part_occ[i] : 0);
+        for (int32_t r0 = sub; r0 < rep; r0 += 8 * G) {
+            int32_t oc[8];
 #pragma unroll
-    for (int q = 0; q < QUEUE_CHUNK; ++q)
-        if (lo + q < hi) {
-            if (SMALL)
-                s_off[counter(lo + q)] = acc;
-            else
-                a.seg_off[counter(lo + q)] = acc;
-            acc += cnt[q];
+            for (int u = 0; u < 8; ++u) oc[u] = r0 + u * G < rep ? occ((r0 + u * G) * NB + b) : 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int32_t r = r0 + u * G, c = r * NB + b;
+                if (r >= rep) break;
+                if (SMALL) {
+                    s_off[c] = pos;
+                } else {
+                    a.seg_off[c] = pos;
+                    a.occ_bin[c] = 0;
+                    a.seg_cur[c] = 0;
+                }
+                a.ev_bin[c] = 0.0f;
+                a.n_bin[c] = 0;
+                pos += oc[u];
+            }
         }
-    __syncthreads();
+    }
     if constexpr (SMALL) {
+        __syncthreads();
         // the segment list, as queue_fill_kernel lays it out
         for (int32_t sg = tid; sg < n_seg; sg += nthr) {
             const int32_t b = s_bin[sg];
@@ -212,27 +202,17 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
             const int32_t run = sg / NB, j = sg - run * NB;
             const int32_t n = a.n_walk[run];
             const int64_t first = (int64_t)j * a.m_targ;
-            const int32_t c = b * rep + run % rep;
-            const int32_t pos = s_off[c] + atomicAdd(&s_cur[c], 1);
+            const int32_t pos = atomicAdd(&s_off[run % rep * NB + b], 1);
             a.seg[pos] = make_int2((int32_t)((size_t)run * a.cap + first), (int32_t)min((int64_t)a.m_targ, n - first));
         }
-    }
-    for (int32_t c = tid; c < NC; c += nthr) {
-        if (!SMALL) {
-            a.occ_bin[c] = 0;
-            a.seg_cur[c] = 0;
-        }
-        a.ev_bin[c] = 0.0f;
-        a.n_bin[c] = 0;
     }
 }
 
 // Tiny case (queue_tiny: at most 64 segments and 64 counters, e.g. one run of
 // up to 64 bins): the same three steps in one wave, with no block barrier
 // in the sort -- lane b holds bin b's key, a bitonic sort over the 64 lanes
-// by shuffles (the same comparator as above, padding keys -1 last), then a
-// wave prefix over the counters in sorted order.  Gives the same segment
-// order per counter as queue_order_kernel<true>.
+// by shuffles (padding keys -1 last), then a wave prefix over the counters in
+// sorted order.
 __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
     __shared__ int32_t s_occ[64], s_off[64], s_cur[64];
     const int lane = threadIdx.x & 63;
@@ -247,7 +227,7 @@ __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
         j = lane - run * NB;
         if ((int64_t)j * a.m_targ < a.n_walk[run]) {
             b = min(max(a.bin[(size_t)run * a.cap + (size_t)j * a.m_targ], 0), NB - 1);
-            atomicAdd(&s_occ[b * rep + run % rep], 1);
+            atomicAdd(&s_occ[run % rep * NB + b], 1);
         }
     }
     // bin keys: mean events per walker over the bin's replica counters
@@ -257,8 +237,8 @@ __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
         float ev = 0.0f;
         int32_t nw = 0;
         for (int32_t r = 0; r < rep; ++r) {
-            ev += a.ev_bin[lane * rep + r];
-            nw += a.n_bin[lane * rep + r];
+            ev += a.ev_bin[r * NB + lane];
+            nw += a.n_bin[r * NB + lane];
         }
         key = nw > 0 ? ev / (float)nw : 0.0f;
     }
@@ -267,7 +247,7 @@ __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
     // exclusive prefix of the counters in sorted bin order (replicas of a
     // bin consecutive): lane i holds counter i of that sequence
     const int32_t bin_at = __shfl(idx, rep > 0 ? lane / rep : 0, 64);
-    const int32_t c = bin_at * rep + lane % rep;
+    const int32_t c = lane % rep * NB + bin_at;
     const int32_t cnt = lane < NC ? s_occ[c] : 0;
     int32_t incl = cnt;
     for (int d = 1; d < 64; d <<= 1) {
@@ -286,7 +266,7 @@ __global__ __launch_bounds__(64) void queue_order_wave_kernel(SimArgs a) {
     if (b >= 0) {
         const int32_t n = a.n_walk[run];
         const int64_t first = (int64_t)j * a.m_targ;
-        const int32_t cc = b * rep + run % rep;
+        const int32_t cc = run % rep * NB + b;
         const int32_t pos = s_off[cc] + atomicAdd(&s_cur[cc], 1);
         a.seg[pos] = make_int2((int32_t)((size_t)run * a.cap + first), (int32_t)min((int64_t)a.m_targ, n - first));
     }
@@ -306,7 +286,7 @@ __global__ __launch_bounds__(256) void queue_fill_kernel(SimArgs a) {
     if (first >= n) return;
     const size_t g = (size_t)run * a.cap + first;
     const int32_t b = min(max(a.bin[g], 0), a.n_bins - 1);
-    const int32_t c = b * a.seg_rep + run % a.seg_rep;
+    const int32_t c = run % a.seg_rep * a.n_bins + b;
     const int32_t pos = a.seg_off[c] + atomicAdd(&a.seg_cur[c], 1);
     a.seg[pos] = make_int2((int32_t)g, (int32_t)min((int64_t)a.m_targ, n - first));
 }
