@@ -1,7 +1,8 @@
 """Reweighting events over wide components: a component across the 64-state
 chunks, rows longer than one pass of an elimination step (256 entries) and as
 many bins as are taken (512), in LDS and in device memory; bins of one walker
-and of many.  The event is recomputed on the host from the flux matrix and the
+and of many.  The flux matrix itself, with bins of fewer and more than 64 walkers
+from many start bins, equals the oracle's bit for bit.  The event is recomputed on the host from the flux matrix and the
 weights of a twin that skips it: state reduction in extended precision on the
 same strongly connected component.  State reduction in FP64 has an entrywise
 relative error of order n^3 u (O'Cinneide 1993): rtol = n^3 u, n the component's
@@ -11,6 +12,7 @@ import pytest
 from scipy.sparse import csr_matrix
 from scipy.sparse.csgraph import connected_components
 
+from oracle import oracle as orc
 from paper_1303_5986_amd import workloads as wl
 
 U = 2.0 ** -53
@@ -92,3 +94,20 @@ def test_event_over_wide_components(name):
         assert np.array_equal(w[fac[b] == 1.0], w1[fac[b] == 1.0])
         np.testing.assert_allclose(w, w1 * fac[b], rtol=max(size, 2) ** 3 * U, atol=0)
         print(f"run {r}: component of {size}", flush=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nb,width,m", [(33, 8.0, 17), (64, 6.0, 64), (65, 6.0, 90), (20, 15.0, 150)])
+def test_flux_matrix_of_large_bins_is_the_oracles(nb, width, m):
+    print(f"case: flux matrix, {nb} bins of {m}", flush=True)
+    from paper_1303_5986_amd import we
+    cfg = wl.WEConfig(name="flux", net=bursts(40, 6.0, 1.0), x0=np.array([40], np.int32), bin_coef=np.array([1.0]),
+                      edges=wl.uniform_edges(0.0, nb * width, nb), m_targ=m, tau=0.6, n_iters=6,
+                      seeds=np.array([3, 4], np.uint64))
+    sim = we.sim_from_config(cfg, kernel=we.WE_KERNEL_LANE, max_iters=6, rw_period=7)
+    sim.step(6)
+    for r in range(2):
+        o = orc.OracleWE(cfg, int(cfg.seeds[r]), rw_period=7)
+        o.step(6)
+        assert np.array_equal(sim.rw_flux_matrix(r), o.rw_F), r
+        assert np.count_nonzero(o.rw_F) > 2 * nb
