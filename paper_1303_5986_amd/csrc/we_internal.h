@@ -2,6 +2,7 @@
 // libwe.so (not part of the public interface).
 #pragma once
 
+#include <mutex>
 #include <hip/hip_runtime.h>
 
 #include <string>
@@ -107,6 +108,13 @@ struct we_sim {
     hipStream_t capture_stream = nullptr;
     int32_t graph_iters = 0;
     bool capturing = false;
+    // readback (we_runtime.hip): pinned memory the device writes results to, two
+    // halves of stage_half bytes when a result is longer than one
+    std::mutex read_mu;
+    int32_t device = 0;
+    unsigned char *stage = nullptr;
+    size_t stage_half = 0;
+    hipEvent_t read_ev[2] = {nullptr, nullptr};
     // committor
     Records rec;
     Committor cm;

@@ -527,6 +527,7 @@ extern "C" we_status we_init(const we_network *net, const we_grid *g, const we_p
     const int64_t jcells = joint_cells(p);
     Layout L = make_layout(S, NB, NB2, n_runs, cap, max_iters, nh, jcells, p->rw_period > 0);
     we_sim *s = new we_sim();
+    (void)hipGetDevice(&s->device);
     s->net = net;
     s->stream = (hipStream_t)hip_stream;
     s->kernel = kernel;
@@ -713,13 +714,166 @@ extern "C" we_status we_set_ensemble(we_sim *s, int32_t run, int32_t n, const in
 }
 
 namespace {
+we_status err_status(int32_t err) {
+    if (err & WE_DERR_OVERFLOW) return fail(WE_EOVERFLOW, "a copy number left [0, WE_COUNT_MAX]");
+    if (err & WE_DERR_CAPACITY) return fail(WE_ECAPACITY, "resampling exceeded the slot reservation");
+    if (err & WE_DERR_SELECT) return fail(WE_EDEVICE, "reaction selection found no positive propensity");
+    return WE_OK;
+}
+
 we_status read_err(we_sim *s) {
     int32_t err = 0;
     HIP_TRY(hipMemcpyAsync(&err, s->args.err, 4, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
-    if (err & WE_DERR_OVERFLOW) return fail(WE_EOVERFLOW, "a copy number left [0, WE_COUNT_MAX]");
-    if (err & WE_DERR_CAPACITY) return fail(WE_ECAPACITY, "resampling exceeded the slot reservation");
-    if (err & WE_DERR_SELECT) return fail(WE_EDEVICE, "reaction selection found no positive propensity");
+    return err_status(err);
+}
+
+// Results for the host.  Read is what one call fetches: up to 5 pieces of 4-byte
+// words, each of a given length or of per_n words per walker of a run (whose
+// number the device holds).  A piece goes to dst (null: not wanted).
+#define READ_PIECES 5
+#define READ_HEAD 4   // words before the pieces: error bits, walkers, 0, 0
+struct ReadPiece {
+    const uint32_t *src;
+    uint64_t words;
+    uint32_t per_n;
+};
+struct Read {
+    const int32_t *err = nullptr, *n_dev = nullptr;
+    ReadPiece piece[READ_PIECES] = {};
+    int32_t n_pieces = 0;
+};
+struct ReadPlan {
+    Read r;
+    void *dst[READ_PIECES] = {};
+    uint64_t most = READ_HEAD;   // words at the most
+    void add(void *to, const void *src, uint64_t words, uint32_t per_n = 0, int64_t cap = 0) {
+        if (!to) return;
+        r.piece[r.n_pieces] = ReadPiece{(const uint32_t *)src, words, per_n};
+        dst[r.n_pieces++] = to;
+        most += per_n ? (uint64_t)per_n * (uint64_t)cap : words;
+    }
+};
+
+// Words [lo, lo + count) of the result, written to pinned host memory: one
+// launch and one wait per call where a copy per piece into the caller's pageable
+// memory costs a staging copy and a wait each (64 networks of a batch, five
+// pieces: 47 us a piece).
+__global__ __launch_bounds__(256) void we_read_kernel(Read r, uint32_t *__restrict__ out, uint64_t lo, uint64_t count) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= count) return;
+    const uint64_t v = lo + i;
+    const int32_t n = r.n_dev ? *r.n_dev : 0;
+    if (v < READ_HEAD) {
+        out[i] = v == 0 ? (uint32_t)*r.err : v == 1 ? (uint32_t)n : 0u;
+        return;
+    }
+    uint64_t p = v - READ_HEAD;
+#pragma unroll
+    for (int k = 0; k < READ_PIECES; ++k) {
+        if (k >= r.n_pieces) return;
+        const uint64_t w = r.piece[k].per_n ? (uint64_t)r.piece[k].per_n * (uint64_t)n : r.piece[k].words;
+        if (p < w) {
+            out[i] = r.piece[k].src[p];
+            return;
+        }
+        p -= w;
+    }
+}
+
+// The sim's pinned memory for a result of `bytes`: one piece, or two halves of
+// READ_HALF_MAX which the device and the host take in turns.
+#define READ_HALF_MAX ((size_t)1 << 20)
+bool read_stage(we_sim *s, size_t bytes) {
+    size_t half = (size_t)64 << 10;
+    while (half < bytes && half < READ_HALF_MAX) half <<= 1;
+    if (half > s->stage_half) {
+        if (s->stage) (void)hipHostFree(s->stage);
+        s->stage = nullptr;
+        s->stage_half = 0;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, half < READ_HALF_MAX ? half : 2 * half, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        s->stage = (unsigned char *)p;
+        s->stage_half = half;
+    }
+    for (hipEvent_t &e : s->read_ev)
+        if (bytes > s->stage_half && !e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+    return true;
+}
+
+// The same by plain copies: no pinned memory, or another device is current.
+we_status read_plain(we_sim *s, const ReadPlan &p, int32_t *n_out) {
+    we_status st = read_err(s);
+    if (st != WE_OK) return st;
+    int32_t n = 0;
+    if (p.r.n_dev) HIP_TRY(hipMemcpy(&n, p.r.n_dev, 4, hipMemcpyDeviceToHost));
+    if (n_out) *n_out = n;
+    for (int32_t k = 0; k < p.r.n_pieces; ++k) {
+        const ReadPiece &q = p.r.piece[k];
+        const uint64_t w = q.per_n ? (uint64_t)q.per_n * (uint64_t)n : q.words;
+        HIP_TRY(hipMemcpy(p.dst[k], q.src, 4 * w, hipMemcpyDeviceToHost));
+    }
+    return WE_OK;
+}
+
+// Waits for the sim's stream, reports latched faults and fetches the pieces.
+we_status read_back(we_sim *s, ReadPlan &p, int32_t *n_out = nullptr) {
+    std::lock_guard<std::mutex> lock(s->read_mu);
+    p.r.err = s->args.err;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev != s->device || !read_stage(s, 4 * p.most))
+        return read_plain(s, p, n_out);
+    const uint64_t half = s->stage_half / 4;
+    uint64_t total = p.most;
+    const bool one = total <= half;
+    auto launch = [&](uint64_t c) -> we_status {   // chunk c into its half
+        const uint64_t lo = c * half, count = std::min(half, total - lo);
+        hipLaunchKernelGGL(we_read_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s->stream, p.r,
+                           (uint32_t *)(s->stage + (c & 1) * s->stage_half), lo, count);
+        HIP_TRY(hipGetLastError());
+        if (!one) HIP_TRY(hipEventRecord(s->read_ev[c & 1], s->stream));
+        return WE_OK;
+    };
+    we_status st = launch(0);
+    if (st == WE_OK && !one) st = launch(1);
+    if (st != WE_OK) return st;
+    for (uint64_t c = 0; c * half < total; ++c) {
+        HIP_TRY(one ? hipStreamSynchronize(s->stream) : hipEventSynchronize(s->read_ev[c & 1]));
+        const uint32_t *got = (const uint32_t *)(s->stage + (c & 1) * s->stage_half);
+        if (c == 0) {
+            const int32_t n = (int32_t)got[1];
+            st = err_status((int32_t)got[0]);
+            if (st != WE_OK) {
+                if (!one) HIP_TRY(hipStreamSynchronize(s->stream));
+                return st;
+            }
+            if (n_out) *n_out = n;
+            total = READ_HEAD;
+            for (int32_t k = 0; k < p.r.n_pieces; ++k) {
+                ReadPiece &q = p.r.piece[k];
+                if (q.per_n) q.words = (uint64_t)q.per_n * (uint64_t)n;
+                total += q.words;
+            }
+        }
+        // the chunk's part of every piece
+        const uint64_t lo = c * half, hi = std::min(lo + half, total);
+        uint64_t at = READ_HEAD;
+        for (int32_t k = 0; k < p.r.n_pieces; ++k) {
+            const uint64_t from = std::max(lo, at), to = std::min(hi, at + p.r.piece[k].words);
+            if (from < to) std::memcpy((uint32_t *)p.dst[k] + (from - at), got + (from - lo), 4 * (to - from));
+            at += p.r.piece[k].words;
+        }
+        if ((c + 2) * half < total) {
+            st = launch(c + 2);
+            if (st != WE_OK) return st;
+        }
+    }
     return WE_OK;
 }
 }  // namespace
@@ -854,17 +1008,14 @@ extern "C" we_status we_get_walkers(we_sim *s, int32_t run, int32_t *n, int32_t 
                                     int32_t *bin, int32_t *origin) {
     if (!s) return fail(WE_EINVAL, "NULL sim");
     if (run < 0 || run >= s->n_runs) return fail(WE_EINVAL, "run out of range");
-    we_status st = read_err(s);
-    if (st != WE_OK) return st;
-    int32_t nn = 0;
-    HIP_TRY(hipMemcpy(&nn, s->args.n_walk + run, 4, hipMemcpyDeviceToHost));
     const size_t base = (size_t)run * s->cap;
-    if (n) *n = nn;
-    if (x) HIP_TRY(hipMemcpy(x, s->x[s->cur] + base * s->S, 4 * (size_t)nn * s->S, hipMemcpyDeviceToHost));
-    if (w) HIP_TRY(hipMemcpy(w, s->w[s->cur] + base, 8 * (size_t)nn, hipMemcpyDeviceToHost));
-    if (bin) HIP_TRY(hipMemcpy(bin, s->args.bin + base, 4 * (size_t)nn, hipMemcpyDeviceToHost));
-    if (origin) HIP_TRY(hipMemcpy(origin, s->args.origin + base, 4 * (size_t)nn, hipMemcpyDeviceToHost));
-    return WE_OK;
+    ReadPlan p;
+    p.r.n_dev = s->args.n_walk + run;
+    p.add(w, s->w[s->cur] + base, 0, 2, s->cap);
+    p.add(bin, s->args.bin + base, 0, 1, s->cap);
+    p.add(origin, s->args.origin + base, 0, 1, s->cap);
+    p.add(x, s->x[s->cur] + base * s->S, 0, (uint32_t)s->S, s->cap);
+    return read_back(s, p, n);
 }
 
 extern "C" we_status we_histogram(we_sim *s, int32_t run, int32_t species, int32_t lo, int32_t hi,
@@ -887,9 +1038,10 @@ extern "C" we_status we_histogram(we_sim *s, int32_t run, int32_t species, int32
 extern "C" we_status we_histogram_accum(we_sim *s, double *out, int32_t *n_iters) {
     if (!s || !out) return fail(WE_EINVAL, "NULL argument");
     if (s->args.nh <= 0) return fail(WE_ESTATE, "no histogram was requested at init");
-    we_status st = read_err(s);
+    ReadPlan p;
+    p.add(out, s->args.hist, 2 * (uint64_t)s->n_runs * s->args.nh);
+    we_status st = read_back(s, p);
     if (st != WE_OK) return st;
-    HIP_TRY(hipMemcpy(out, s->args.hist, 8 * (size_t)s->n_runs * s->args.nh, hipMemcpyDeviceToHost));
     if (n_iters) *n_iters = s->hist_iters;
     return WE_OK;
 }
@@ -897,22 +1049,18 @@ extern "C" we_status we_histogram_accum(we_sim *s, double *out, int32_t *n_iters
 extern "C" we_status we_joint_histogram(we_sim *s, double *out) {
     if (!s || !out) return fail(WE_EINVAL, "NULL argument");
     if (s->args.n_joint <= 0) return fail(WE_ESTATE, "no joint histogram was requested at init");
-    we_status st = read_err(s);
-    if (st != WE_OK) return st;
-    HIP_TRY(hipMemcpy(out, s->args.jhist, 8 * (size_t)s->n_runs * s->args.jcells, hipMemcpyDeviceToHost));
-    return WE_OK;
+    ReadPlan p;
+    p.add(out, s->args.jhist, 2 * (uint64_t)s->n_runs * s->args.jcells);
+    return read_back(s, p);
 }
 
 extern "C" we_status we_flux(we_sim *s, int32_t run, int32_t first, int32_t count, double *out) {
     if (!s || (!out && count > 0)) return fail(WE_EINVAL, "NULL argument");
     if (run < 0 || run >= s->n_runs || first < 0 || count < 0 || first + count > s->iter)
         return fail(WE_EINVAL, "flux range out of bounds");
-    we_status st = read_err(s);
-    if (st != WE_OK) return st;
-    if (count > 0)
-        HIP_TRY(hipMemcpy(out, s->args.flux + (size_t)run * s->max_iters + first, 8 * (size_t)count,
-                          hipMemcpyDeviceToHost));
-    return WE_OK;
+    ReadPlan p;
+    if (count > 0) p.add(out, s->args.flux + (size_t)run * s->max_iters + first, 2 * (uint64_t)count);
+    return read_back(s, p);
 }
 
 extern "C" we_status we_mfpt(we_sim *s, int32_t discard, double *mfpt, double *flux_mean,
@@ -1081,6 +1229,9 @@ extern "C" void we_destroy(we_sim *s) {
     if (!s) return;
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     else (void)hipDeviceSynchronize();
+    if (s->stage) (void)hipHostFree(s->stage);
+    for (hipEvent_t e : s->read_ev)
+        if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_pool) (void)hipEventDestroy(e);
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     committor_free(s);
