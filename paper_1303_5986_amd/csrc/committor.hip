@@ -277,8 +277,18 @@ struct Scratch {
 // Forward and backward of one sample per wave, one hidden unit per lane;
 // the sample is either drawn from the dataset with Philox (counter
 // (b, step, 1, 2)) or given directly.  Every dot product runs over its inputs
-// in ascending order, on the lane that owns the output.
-inline size_t cm_fwd_bwd_lds(int32_t n_in) { return 4 * sizeof(float) * ((size_t)n_in + 3 * CM_H); }
+// in ascending order, on the lane that owns the output.  The workgroup stages W2
+// in LDS, rows CM_W2_PITCH words apart: forward every lane reads its own row (four
+// words at a time, on banks of their own), backward its column; the four
+// samples' results leave side by side.  What bounds it now is one chain: the
+// fetch of the sample (1.6 us of 4.7), three dots of 64 dependent terms, two
+// tanh and the sigmoid.  A batch of 1024 takes 7.0 us, launch included; with the
+// rows of W2 read from memory (64 lines a load) and results stored one word per
+// line 8.0.
+#define CM_W2_PITCH (CM_H + 4)
+#define CM_W1_AHEAD 8
+__device__ __forceinline__ float4 cm_four(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+inline size_t cm_fwd_bwd_lds(int32_t n_in) { return 4 * sizeof(float) * ((size_t)((n_in + 3) & ~3) + 4 * CM_H); }
 
 __global__ __launch_bounds__(256) void cm_fwd_bwd_kernel(const float *__restrict__ params, const float *__restrict__ feat,
                                                          int32_t n_in, int32_t B, int32_t step,
@@ -288,89 +298,217 @@ __global__ __launch_bounds__(256) void cm_fwd_bwd_kernel(const float *__restrict
                                                          const int32_t *__restrict__ rx,
                                                          const int32_t *__restrict__ direct_x,
                                                          const float *__restrict__ direct_y, Scratch sc) {
-    extern __shared__ float cm_lds[];
+    extern __shared__ __align__(16) float cm_lds4[];
+    __shared__ __align__(16) float w2[CM_H * CM_W2_PITCH];
+    __shared__ __align__(16) float w3[CM_H];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int32_t b = (int32_t)blockIdx.x * 4 + wv;
-    if (b >= B) return;   // uniform over the wave
-    float *lphi = cm_lds + (size_t)wv * (n_in + 3 * CM_H);
-    float *lh1 = lphi + n_in, *lh2 = lh1 + CM_H, *lg2 = lh2 + CM_H;
+    const bool on = b < B;   // uniform over the wave
+    const int32_t n_pad = (n_in + 3) & ~3;   // the hidden layers' slices on 16 bytes
+    float *lphi = cm_lds4 + (size_t)wv * (n_pad + 4 * CM_H);
+    float *lh1 = lphi + n_pad, *lh2 = lh1 + CM_H, *lg2 = lh2 + CM_H, *lg1 = lg2 + CM_H;
     const ParamView P = cm_view(params, n_in);
-    const int32_t *xr;
-    float y;
-    if (direct_x) {
-        xr = direct_x + (size_t)b * n_in;
-        y = direct_y[b];
-    } else {
-        const U4 r = philox4x32_10((uint32_t)b, (uint32_t)step, 1u, 2u, k0, k1);
-        int32_t pick = (int32_t)(uniform53(r.x, r.y) * (double)n_ds);
-        if (pick >= n_ds) pick = n_ds - 1;
-        xr = rx + ds_idx[pick] * n_in;
-        y = ds_y[pick];
-    }
-    for (int32_t k = lane; k < n_in; k += 64) {
-        const float f = feature(xr[k], feat, k, n_in);
-        lphi[k] = f;
-        sc.phi[(size_t)k * B + b] = f;
-    }
-    cm_wave_sync();
     const int j = lane;   // this lane's hidden unit in both layers
-    float z1 = P.b1[j];
-    for (int32_t k = 0; k < n_in; ++k) z1 = fmaf(P.W1[j * n_in + k], lphi[k], z1);
-    const float h1 = tanhf(z1);
-    lh1[j] = h1;
-    sc.h1[(size_t)j * B + b] = h1;
-    cm_wave_sync();
-    float z2 = P.b2[j];
-    for (int i = 0; i < CM_H; ++i) z2 = fmaf(P.W2[j * CM_H + i], lh1[i], z2);
-    const float h2 = tanhf(z2);
-    lh2[j] = h2;
-    sc.h2[(size_t)j * B + b] = h2;
-    cm_wave_sync();
-    float z3 = P.b3[0];
-    for (int i = 0; i < CM_H; ++i) z3 = fmaf(P.W3[i], lh2[i], z3);
-    const float q = 1.0f / (1.0f + expf(-z3));
-    const float g3 = (q - y) / (float)B;
-    if (lane == 0) {
-        // binary cross-entropy with a soft label, in the stable form
-        sc.loss[b] = fmaxf(z3, 0.0f) - z3 * y + log1pf(expf(-fabsf(z3)));
-        sc.g3[b] = g3;
+    // every parameter is fetched before the first is used
+    const float b1j = P.b1[j], b2j = P.b2[j], w3j = P.W3[j], b3 = P.b3[0];
+    float w1j[CM_W1_AHEAD], stage[CM_H * CM_H / 256];
+#pragma unroll
+    for (int u = 0; u < CM_W1_AHEAD; ++u) w1j[u] = P.W1[j * n_in + min(u, n_in - 1)];
+#pragma unroll
+    for (int u = 0; u < CM_H * CM_H / 256; ++u) stage[u] = P.W2[u * 256 + threadIdx.x];
+    float y = 0.0f, h1 = 0.0f;
+    if (on) {
+        const int32_t *xr;
+        if (direct_x) {
+            xr = direct_x + (size_t)b * n_in;
+            y = direct_y[b];
+        } else {
+            const U4 r = philox4x32_10((uint32_t)b, (uint32_t)step, 1u, 2u, k0, k1);
+            int32_t pick = (int32_t)(uniform53(r.x, r.y) * (double)n_ds);
+            if (pick >= n_ds) pick = n_ds - 1;
+            xr = rx + ds_idx[pick] * n_in;
+            y = ds_y[pick];
+        }
+        for (int32_t k = lane; k < n_in; k += 64) {
+            const float f = feature(xr[k], feat, k, n_in);
+            lphi[k] = f;
+        }
+        cm_wave_sync();
+        float z1 = b1j;
+#pragma unroll
+        for (int u = 0; u < CM_W1_AHEAD; ++u)
+            if (u < n_in) z1 = fmaf(w1j[u], lphi[u], z1);
+#pragma unroll 8
+        for (int32_t k = CM_W1_AHEAD; k < n_in; ++k) z1 = fmaf(P.W1[j * n_in + k], lphi[k], z1);
+        h1 = tanhf(z1);
+        lh1[j] = h1;
     }
-    const float g2 = g3 * P.W3[j] * (1.0f - h2 * h2);
-    lg2[j] = g2;
-    sc.g2[(size_t)j * B + b] = g2;
-    cm_wave_sync();
-    float acc = 0.0f;
-    for (int i = 0; i < CM_H; ++i) acc = fmaf(P.W2[i * CM_H + j], lg2[i], acc);
-    sc.g1[(size_t)j * B + b] = acc * (1.0f - h1 * h1);
+#pragma unroll
+    for (int u = 0; u < CM_H * CM_H / 256; ++u) {
+        const int t = u * 256 + threadIdx.x;
+        w2[t / CM_H * CM_W2_PITCH + t % CM_H] = stage[u];
+    }
+    if (wv == 0) w3[j] = w3j;
+    __syncthreads();
+    if (on) {
+        float z2 = b2j;
+        {
+            float4 w[CM_H / 4], h[CM_H / 4];
+#pragma unroll
+            for (int i = 0; i < CM_H / 4; ++i) {
+                w[i] = cm_four(&w2[j * CM_W2_PITCH + 4 * i]);
+                h[i] = cm_four(lh1 + 4 * i);
+            }
+#pragma unroll
+            for (int i = 0; i < CM_H / 4; ++i) {
+                z2 = fmaf(w[i].x, h[i].x, z2);
+                z2 = fmaf(w[i].y, h[i].y, z2);
+                z2 = fmaf(w[i].z, h[i].z, z2);
+                z2 = fmaf(w[i].w, h[i].w, z2);
+            }
+        }
+        const float h2 = tanhf(z2);
+        lh2[j] = h2;
+        cm_wave_sync();
+        float z3 = b3, col[CM_H];
+        {
+            float4 w[CM_H / 4], h[CM_H / 4];
+#pragma unroll
+            for (int i = 0; i < CM_H / 4; ++i) {
+                w[i] = cm_four(&w3[4 * i]);
+                h[i] = cm_four(lh2 + 4 * i);
+            }
+#pragma unroll
+            for (int i = 0; i < CM_H; ++i) col[i] = w2[i * CM_W2_PITCH + j];   // for the backward pass
+#pragma unroll
+            for (int i = 0; i < CM_H / 4; ++i) {
+                z3 = fmaf(w[i].x, h[i].x, z3);
+                z3 = fmaf(w[i].y, h[i].y, z3);
+                z3 = fmaf(w[i].z, h[i].z, z3);
+                z3 = fmaf(w[i].w, h[i].w, z3);
+            }
+        }
+        const float q = 1.0f / (1.0f + expf(-z3));
+        const float g3 = (q - y) / (float)B;
+        if (lane == 0) {
+            // binary cross-entropy with a soft label, in the stable form
+            sc.loss[b] = fmaxf(z3, 0.0f) - z3 * y + log1pf(expf(-fabsf(z3)));
+            sc.g3[b] = g3;
+        }
+        const float g2 = g3 * w3j * (1.0f - h2 * h2);
+        lg2[j] = g2;
+        cm_wave_sync();
+        float acc = 0.0f;
+#pragma unroll
+        for (int i = 0; i < CM_H / 4; ++i) {
+            const float4 g = cm_four(lg2 + 4 * i);
+            acc = fmaf(col[4 * i], g.x, acc);
+            acc = fmaf(col[4 * i + 1], g.y, acc);
+            acc = fmaf(col[4 * i + 2], g.z, acc);
+            acc = fmaf(col[4 * i + 3], g.w, acc);
+        }
+        lg1[j] = acc * (1.0f - h1 * h1);
+    }
+    __syncthreads();
+    // the four samples' values side by side: a quarter of the memory requests
+    const int32_t s = threadIdx.x & 3, bs = (int32_t)blockIdx.x * 4 + s;
+    if (bs >= B) return;
+    const float *from = cm_lds4 + (size_t)s * (n_pad + 4 * CM_H);
+    for (int32_t k = threadIdx.x >> 2; k < n_in; k += 64) sc.phi[(size_t)k * B + bs] = from[k];
+    const size_t at = (size_t)(threadIdx.x >> 2) * B + bs;
+    from += n_pad + (threadIdx.x >> 2);
+    sc.h1[at] = from[0];
+    sc.h2[at] = from[CM_H];
+    sc.g2[at] = from[2 * CM_H];
+    sc.g1[at] = from[3 * CM_H];
 }
 
-// One wave per parameter (and one for the mean loss): lane l sums samples
-// l, l+64, l+128, ... in that order, then a fixed butterfly adds the 64 lane
-// sums -- coalesced loads, and the same order on every run.
+// Sum over the wave as the butterfly over lane bits 5, 4, 3, 2, 1, 0 adds it:
+// halves and rows swapped, then rotations in a 16-lane row (lanes 8 apart are
+// equal when the one by 4 comes).
+template <int CTRL>
+__device__ __forceinline__ float cm_dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float cm_wave_sum(float v) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v += cm_dpp<0x128>(v);
+    v += cm_dpp<0x124>(v);
+    v += cm_dpp<0x4E>(v);
+    v += cm_dpp<0xB1>(v);
+    return v;
+}
+
+// Gradients: lane l sums samples l, l+64, l+128, ... in that order, then a fixed
+// butterfly adds the 64 lane sums -- coalesced loads, and the same order on every
+// run.  One wave takes up to CM_GRAD_COLS parameters of one row, which share the
+// row's factor u (their own factors v), with the bias of the row (the sum of
+// u) at the row's first; a wave more for the mean loss.  What bounds it is the
+// latency of the loads: eight samples' are in flight at once.  One parameter per
+// wave and two loads at a time: 7.2 us for a batch of 1024, this way 4.8.
+#define CM_GRAD_COLS 4
+#define CM_GRAD_AHEAD 8
+__host__ __device__ inline int32_t cm_grad_waves(int32_t n_in) {
+    return CM_H * ((n_in + CM_GRAD_COLS - 1) / CM_GRAD_COLS) + CM_H * (CM_H / CM_GRAD_COLS) + CM_H / CM_GRAD_COLS + 1;
+}
 __global__ __launch_bounds__(256) void cm_grad_kernel(int32_t n_in, int32_t B, Scratch sc, float *__restrict__ grad,
                                                       float *__restrict__ loss_out) {
     const int32_t i = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int32_t np = cm_n_params(n_in);
-    if (i > np || (i == np && !loss_out)) return;   // uniform over the wave
     const int32_t nW1 = CM_H * n_in, nW2 = CM_H * CM_H;
     const int32_t b1 = nW1, w2 = b1 + CM_H, b2 = w2 + nW2, w3 = b2 + CM_H, b3 = w3 + CM_H;
+    const int32_t g1c = (n_in + CM_GRAD_COLS - 1) / CM_GRAD_COLS, g2c = CM_H / CM_GRAD_COLS;
+    const int32_t t2 = CM_H * g1c, t3 = t2 + CM_H * g2c, t4 = t3 + g2c;
+    if (i > t4 || (i == t4 && !loss_out)) return;   // uniform over the wave
+    // the row's factor, its columns' factors, where the columns' and the row's own sums go
     const float *u, *v = nullptr;
-    if (i == np) { u = sc.loss; }
-    else if (i < b1) { u = sc.g1 + (size_t)(i / n_in) * B; v = sc.phi + (size_t)(i % n_in) * B; }
-    else if (i < w2) { u = sc.g1 + (size_t)(i - b1) * B; }
-    else if (i < b2) { const int32_t r = i - w2; u = sc.g2 + (size_t)(r / CM_H) * B; v = sc.h1 + (size_t)(r % CM_H) * B; }
-    else if (i < w3) { u = sc.g2 + (size_t)(i - b2) * B; }
-    else if (i < b3) { u = sc.g3; v = sc.h2 + (size_t)(i - w3) * B; }
-    else { u = sc.g3; }
-    float acc = 0.0f;
-    if (v) for (int32_t b = lane; b < B; b += 64) acc = fmaf(u[b], v[b], acc);
-    else for (int32_t b = lane; b < B; b += 64) acc += u[b];
-    for (int d = 32; d > 0; d >>= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) {
-        if (i == np) *loss_out = acc / (float)B;
-        else grad[i] = acc;
+    float *to = nullptr, *to_bias = nullptr;
+    int32_t cols = 0;
+    if (i < t2) {
+        const int32_t r = i / g1c, c = i % g1c * CM_GRAD_COLS;
+        u = sc.g1 + (size_t)r * B; v = sc.phi + (size_t)c * B; cols = min(CM_GRAD_COLS, n_in - c);
+        to = grad + r * n_in + c; to_bias = c == 0 ? grad + b1 + r : nullptr;
+    } else if (i < t3) {
+        const int32_t r = (i - t2) / g2c, c = (i - t2) % g2c * CM_GRAD_COLS;
+        u = sc.g2 + (size_t)r * B; v = sc.h1 + (size_t)c * B; cols = CM_GRAD_COLS;
+        to = grad + w2 + r * CM_H + c; to_bias = c == 0 ? grad + b2 + r : nullptr;
+    } else if (i < t4) {
+        const int32_t c = (i - t3) * CM_GRAD_COLS;
+        u = sc.g3; v = sc.h2 + (size_t)c * B; cols = CM_GRAD_COLS;
+        to = grad + w3 + c; to_bias = c == 0 ? grad + b3 : nullptr;
+    } else {
+        u = sc.loss; to_bias = loss_out;
     }
+    float acc[CM_GRAD_COLS], sum = 0.0f;
+#pragma unroll
+    for (int c = 0; c < CM_GRAD_COLS; ++c) acc[c] = 0.0f;
+    for (int32_t b0 = lane; b0 < B; b0 += 64 * CM_GRAD_AHEAD) {
+        float ub[CM_GRAD_AHEAD], vb[CM_GRAD_COLS][CM_GRAD_AHEAD];
+#pragma unroll
+        for (int a = 0; a < CM_GRAD_AHEAD; ++a) {
+            const int32_t b = min(b0 + 64 * a, B - 1);
+            ub[a] = u[b];
+#pragma unroll
+            for (int c = 0; c < CM_GRAD_COLS; ++c) vb[c][a] = c < cols ? v[(size_t)c * B + b] : 0.0f;
+        }
+#pragma unroll
+        for (int a = 0; a < CM_GRAD_AHEAD; ++a) {
+            const bool in = b0 + 64 * a < B;
+            sum = in ? sum + ub[a] : sum;
+#pragma unroll
+            for (int c = 0; c < CM_GRAD_COLS; ++c) acc[c] = in ? fmaf(ub[a], vb[c][a], acc[c]) : acc[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CM_GRAD_COLS; ++c) {
+        const float g = cm_wave_sum(acc[c]);
+        if (lane == 0 && c < cols) to[c] = g;
+    }
+    sum = cm_wave_sum(sum);
+    if (lane == 0 && to_bias) *to_bias = i == t4 ? sum / (float)B : sum;
 }
 
 __global__ void cm_adam_kernel(int32_t np, float *__restrict__ p, float *__restrict__ m, float *__restrict__ v,
@@ -806,7 +944,7 @@ extern "C" we_status we_train_committor(we_sim *s, const we_train_params *tp, fl
                            step, k0, k1, n_ds, ds_idx.as<int64_t>(), ds_y.as<float>(), R.d_x,
                            (const int32_t *)nullptr, (const float *)nullptr, sb.view());
         HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL(cm_grad_kernel, dim3((C.n_params + 1 + 3) / 4), dim3(256), 0, s->stream, n_in, B,
+        hipLaunchKernelGGL(cm_grad_kernel, dim3((cm_grad_waves(n_in) + 3) / 4), dim3(256), 0, s->stream, n_in, B,
                            sb.view(), C.d_grad, dloss.as<float>() + step);
         HIP_TRY(hipGetLastError());
         hipLaunchKernelGGL(cm_adam_kernel, dim3((C.n_params + 255) / 256), dim3(256), 0, s->stream, C.n_params,
@@ -908,7 +1046,7 @@ extern "C" we_status we_mlp_loss_grad(int32_t n_in, const float *params, const f
                        df.as<float>(), n_in, batch, 0, 0u, 0u, 0, (const int64_t *)nullptr, (const float *)nullptr,
                        (const int32_t *)nullptr, dx.as<int32_t>(), dy.as<float>(), sb.view());
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(cm_grad_kernel, dim3((np + 1 + 3) / 4), dim3(256), 0, nullptr, n_in, batch, sb.view(),
+    hipLaunchKernelGGL(cm_grad_kernel, dim3((cm_grad_waves(n_in) + 3) / 4), dim3(256), 0, nullptr, n_in, batch, sb.view(),
                        dg.as<float>(), dl.as<float>());
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipDeviceSynchronize());
@@ -969,12 +1107,11 @@ extern "C" we_status we_mlp_loss_grad_noalloc(int32_t n_in, const float *params,
     sc.g3 = sc.g2 + CM_H * B;
     sc.loss = sc.g3 + B;
     hipStream_t st_h = static_cast<hipStream_t>(hip_stream);
-    const int32_t np = cm_n_params(n_in);
     hipLaunchKernelGGL(cm_fwd_bwd_kernel, dim3((batch + 3) / 4), dim3(256), cm_fwd_bwd_lds(n_in), st_h, params, feat,
                        n_in, batch, 0, 0u, 0u, 0, (const int64_t *)nullptr, (const float *)nullptr,
                        (const int32_t *)nullptr, x, y, sc);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(cm_grad_kernel, dim3((np + 1 + 3) / 4), dim3(256), 0, st_h, n_in, batch, sc, grad, loss);
+    hipLaunchKernelGGL(cm_grad_kernel, dim3((cm_grad_waves(n_in) + 3) / 4), dim3(256), 0, st_h, n_in, batch, sc, grad, loss);
     HIP_TRY(hipGetLastError());
     return WE_OK;
 }
