@@ -625,84 +625,152 @@ __global__ void cm_transpose_kernel(const float *__restrict__ params, int32_t n_
 }
 
 // The same z as mlp_z (every dot product over the same terms in the same
-// order, on the lane that owns its output), one walker per wave, one hidden
-// unit per lane; wt is cm_transpose_kernel's output; lphi/lh1/lh2 are the
-// wave's LDS slices (n_in, 64, 64 floats).
-__device__ float mlp_z_wave(const ParamView &P, const float *__restrict__ wt, const float *feat, const int32_t *xr,
-                            int32_t n_in, float *lphi, float *lh1, float *lh2) {
+// order, on the lane that owns its output), CM_WALKERS walkers per wave, one
+// hidden unit per lane; wt is cm_transpose_kernel's output; l is the wave's LDS
+// (cm_bin_floats).  Lane i gives the counts x, and gets the z, of walker
+// i % CM_WALKERS.  The walkers share
+// every fetched weight and the chain of the last dot product, whose 64 terms
+// every lane would add for one walker all the same; with one walker per wave the
+// binning of 16 toggle runs of 64 bins x 16 took 19 us, this way 8.8.
+#define CM_WALKERS 4
+#define CM_H_PITCH (CM_H + 4)   // the walkers' hidden layers on banks of their own
+__host__ __device__ inline int32_t cm_phi_pitch(int32_t n_in) { return (n_in + 3) & ~3; }
+__host__ __device__ inline size_t cm_bin_floats(int32_t n_in) {
+    return CM_WALKERS * ((size_t)cm_phi_pitch(n_in) + 2 * CM_H_PITCH);
+}
+__device__ __forceinline__ float mlp_z_wave(const ParamView &P, const float *__restrict__ wt, const float *feat,
+                                            const int32_t *__restrict__ x, int32_t n_in, float *l) {
     const int lane = threadIdx.x & 63;
+    const int32_t pitch = cm_phi_pitch(n_in);
     const float *W1t = wt, *W2t = wt + CM_H * n_in;
-    for (int32_t k = lane; k < n_in; k += 64) lphi[k] = feature(xr[k], feat, k, n_in);
+    float *phi = l, *h1 = l + CM_WALKERS * pitch, *h2 = h1 + CM_WALKERS * CM_H_PITCH;
+    const int32_t w = lane % CM_WALKERS;
+    for (int32_t k = lane / CM_WALKERS; k < n_in; k += 64 / CM_WALKERS)
+        phi[w * pitch + k] = feature(x[k], feat, k, n_in);
     cm_wave_sync();
-    float z1 = P.b1[lane];
-    for (int32_t k = 0; k < n_in; ++k) z1 = fmaf(W1t[k * CM_H + lane], lphi[k], z1);
-    lh1[lane] = tanhf(z1);
+    float z[CM_WALKERS];
+#pragma unroll
+    for (int c = 0; c < CM_WALKERS; ++c) z[c] = P.b1[lane];
+#pragma unroll 4
+    for (int32_t k = 0; k < n_in; ++k) {
+        const float v = W1t[k * CM_H + lane];
+#pragma unroll
+        for (int c = 0; c < CM_WALKERS; ++c) z[c] = fmaf(v, phi[c * pitch + k], z[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < CM_WALKERS; ++c) h1[c * CM_H_PITCH + lane] = tanhf(z[c]);
     cm_wave_sync();
-    float z2 = P.b2[lane];
-    for (int j = 0; j < CM_H; ++j) z2 = fmaf(W2t[j * CM_H + lane], lh1[j], z2);
-    lh2[lane] = tanhf(z2);
+#pragma unroll
+    for (int c = 0; c < CM_WALKERS; ++c) z[c] = P.b2[lane];
+#pragma unroll 1
+    for (int j0 = 0; j0 < CM_H; j0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = W2t[(j0 + u) * CM_H + lane];
+#pragma unroll
+        for (int u = 0; u < 16; u += 4)
+#pragma unroll
+            for (int c = 0; c < CM_WALKERS; ++c) {
+                const float4 h = cm_four(&h1[c * CM_H_PITCH + j0 + u]);
+                z[c] = fmaf(v[u], h.x, z[c]);
+                z[c] = fmaf(v[u + 1], h.y, z[c]);
+                z[c] = fmaf(v[u + 2], h.z, z[c]);
+                z[c] = fmaf(v[u + 3], h.w, z[c]);
+            }
+    }
+#pragma unroll
+    for (int c = 0; c < CM_WALKERS; ++c) h2[c * CM_H_PITCH + lane] = tanhf(z[c]);
     cm_wave_sync();
     float z3 = P.b3[0];
-    for (int i = 0; i < CM_H; ++i) z3 = fmaf(P.W3[i], lh2[i], z3);
+#pragma unroll 4
+    for (int i = 0; i < CM_H; i += 4) {
+        const float4 h = cm_four(&h2[w * CM_H_PITCH + i]);
+        z3 = fmaf(P.W3[i], h.x, z3);
+        z3 = fmaf(P.W3[i + 1], h.y, z3);
+        z3 = fmaf(P.W3[i + 2], h.z, z3);
+        z3 = fmaf(P.W3[i + 3], h.w, z3);
+    }
     cm_wave_sync();
     return z3;
 }
 
-// Learned bins after recycling: one wave per walker slot.
+// The learned bins of walkers k0 .. k0 + CM_WALKERS - 1 of a run.  Up to
+// CM_COUNT_BINS bins the edges at or below z are counted, 64 at a time: bin_index
+// without its chain of dependent fetches (the edges increase strictly).
+#define CM_COUNT_BINS 256
+__device__ __forceinline__ void cm_bin_walkers(const SimArgs &a, const int32_t *__restrict__ x_cur, const ParamView &P,
+                                               const float *__restrict__ wt, const float *__restrict__ feat,
+                                               const double *__restrict__ qedges, int32_t run, int32_t k0, float *l) {
+    const int lane = threadIdx.x & 63;
+    const int32_t n = a.n_walk[run];
+    if (k0 >= n) return;   // uniform over the wave
+    const size_t base = (size_t)run * a.cap;
+    const int32_t *x = x_cur + (base + min(k0 + lane % CM_WALKERS, n - 1)) * a.S;
+    const double z = (double)mlp_z_wave(P, wt, feat, x, a.S, l);
+    int32_t b = 0;
+    if (a.n_bins <= CM_COUNT_BINS) {
+        for (int32_t e0 = 1; e0 < a.n_bins; e0 += 64) {
+            const bool is = e0 + lane < a.n_bins;
+            const double edge = is ? qedges[e0 + lane] : 0.0;
+#pragma unroll
+            for (int c = 0; c < CM_WALKERS; ++c) {
+                const double zc = __shfl(z, c, 64);
+                const int32_t m = (int32_t)__popcll(__ballot(is && zc >= edge));
+                b += lane == c ? m : 0;
+            }
+        }
+    } else if (lane < CM_WALKERS) {
+        b = bin_index(qedges, a.n_bins, z);
+    }
+    if (lane < CM_WALKERS && k0 + lane < n) a.s_bin[base + k0 + lane] = b;
+}
+
+// Learned bins after recycling: one wave per CM_WALKERS walker slots of a run.
 __global__ __launch_bounds__(256) void cm_bin_kernel(SimArgs a, const int32_t *__restrict__ x_cur,
                                                      const float *__restrict__ params, const float *__restrict__ wt,
                                                      const float *__restrict__ feat,
                                                      const double *__restrict__ qedges) {
-    extern __shared__ float cm_lds[];
+    extern __shared__ __align__(16) float cm_lds4[];
     const int wv = threadIdx.x >> 6;
+    const int32_t per_run = (a.cap + CM_WALKERS - 1) / CM_WALKERS;
     const int64_t gid = (int64_t)blockIdx.x * 4 + wv;
-    const int32_t run = (int32_t)(gid / a.cap);
-    const int32_t k = (int32_t)(gid - (int64_t)run * a.cap);
+    const int32_t run = (int32_t)(gid / per_run);
     if (run >= a.n_runs) return;          // uniform over the wave
-    if (k >= a.n_walk[run]) return;
-    const size_t idx = (size_t)run * a.cap + k;
-    float *lphi = cm_lds + (size_t)wv * (a.S + 2 * CM_H);
-    const ParamView P = cm_view(params, a.S);
-    const float z = mlp_z_wave(P, wt, feat, x_cur + idx * a.S, a.S, lphi, lphi + a.S, lphi + a.S + CM_H);
-    if ((threadIdx.x & 63) == 0) a.s_bin[idx] = bin_index(qedges, a.n_bins, (double)z);
+    cm_bin_walkers(a, x_cur, cm_view(params, a.S), wt, feat, qedges, run,
+                   (int32_t)(gid - (int64_t)run * per_run) * CM_WALKERS, cm_lds4 + wv * cm_bin_floats(a.S));
 }
 
 hipError_t committor_bin(we_sim *s, int32_t *x_cur, hipStream_t st) {
-    const int64_t total = (int64_t)s->n_runs * s->cap;
-    const size_t lds = 4 * sizeof(float) * ((size_t)s->S + 2 * CM_H);
+    const int64_t total = (int64_t)s->n_runs * ((s->cap + CM_WALKERS - 1) / CM_WALKERS);
+    const size_t lds = 4 * sizeof(float) * cm_bin_floats(s->S);
     hipLaunchKernelGGL(cm_bin_kernel, dim3((unsigned)((total + 3) / 4)), dim3(256), lds, st, s->args, x_cur,
                        s->cm.d_params, s->cm.d_wt, s->cm.d_feat, s->cm.d_qedges);
     return hipGetLastError();
 }
 
 // Learned bins of every batch member whose committor is active, after the
-// batched recycle/bin: grid (CM_BATCH_BLOCKS, members), one wave per walker
-// slot as in cm_bin_kernel, each wave striding over its member's slots (a
-// grid sized for the largest member would spend most of its workgroups on
-// members with no slots left for them); members without a model (params
-// NULL) return at once.
+// batched recycle/bin: grid (CM_BATCH_BLOCKS, members), waves as in
+// cm_bin_kernel, each striding over its member's slots (a grid sized for the
+// largest member would spend most of its workgroups on members with no slots
+// left for them); members without a model (params NULL) return at once.
 #define CM_BATCH_BLOCKS 256
 __global__ __launch_bounds__(256) void cm_batch_bin_kernel(const SimArgs *__restrict__ args,
                                                            int32_t *const *__restrict__ x_cur,
                                                            const CmBatchModel *__restrict__ models,
                                                            int32_t s_lds) {
-    extern __shared__ float cm_lds[];
+    extern __shared__ __align__(16) float cm_lds4[];
     const int32_t i = blockIdx.y;
     const CmBatchModel m = models[i];
     if (!m.params) return;
     const SimArgs &a = args[i];
     const int wv = threadIdx.x >> 6;
-    float *lphi = cm_lds + (size_t)wv * (s_lds + 2 * CM_H);
     const ParamView P = cm_view(m.params, a.S);
-    const int64_t slots = (int64_t)a.n_runs * a.cap;
-    for (int64_t gid = (int64_t)blockIdx.x * 4 + wv; gid < slots; gid += (int64_t)gridDim.x * 4) {
-        const int32_t run = (int32_t)(gid / a.cap);   // uniform over the wave
-        const int32_t k = (int32_t)(gid - (int64_t)run * a.cap);
-        if (k >= a.n_walk[run]) continue;
-        const size_t idx = (size_t)run * a.cap + k;
-        const float z =
-            mlp_z_wave(P, m.wt, m.feat, x_cur[i] + idx * a.S, a.S, lphi, lphi + s_lds, lphi + s_lds + CM_H);
-        if ((threadIdx.x & 63) == 0) a.s_bin[idx] = bin_index(m.qedges, a.n_bins, (double)z);
+    const int32_t per_run = (a.cap + CM_WALKERS - 1) / CM_WALKERS;
+    const int64_t groups = (int64_t)a.n_runs * per_run;
+    for (int64_t gid = (int64_t)blockIdx.x * 4 + wv; gid < groups; gid += (int64_t)gridDim.x * 4) {
+        const int32_t run = (int32_t)(gid / per_run);   // uniform over the wave
+        cm_bin_walkers(a, x_cur[i], P, m.wt, m.feat, m.qedges, run, (int32_t)(gid - (int64_t)run * per_run) * CM_WALKERS,
+                       cm_lds4 + wv * cm_bin_floats(s_lds));
     }
 }
 
@@ -719,7 +787,7 @@ CmBatchModel committor_batch_model(const we_sim *s) {
 
 hipError_t committor_bin_batch(const SimArgs *d_args, int32_t *const *d_x, const CmBatchModel *d_models,
                                int32_t n_sims, int64_t max_slots, int32_t s_max, hipStream_t st) {
-    const size_t lds = 4 * sizeof(float) * ((size_t)s_max + 2 * CM_H);
+    const size_t lds = 4 * sizeof(float) * cm_bin_floats(s_max);
     const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_slots + 3) / 4, CM_BATCH_BLOCKS));
     hipLaunchKernelGGL(cm_batch_bin_kernel, dim3(gx, (unsigned)n_sims), dim3(256), lds, st, d_args, d_x, d_models,
                        s_max);
