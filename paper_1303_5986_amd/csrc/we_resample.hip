@@ -678,7 +678,8 @@ __device__ void split_survivors(const RunWork<Idx> &wk, int32_t p0, int32_t nb, 
 // what bounds it is their latency: in registers a merge takes two wave minima
 // (about a thousand cycles) where merge_bin's queues wait on several dependent
 // loads of the bin's arrays.  Ten futile-cycle runs of 101 bins x 100 walkers:
-// 428 -> 252 us per interval with bins of 65 to 256 walkers on this path.
+// 428 -> 252 us per interval with bins of 65 to 256 walkers on this path, which
+// the bin-parallel launch now merges in rounds.
 template <int K, class Idx>
 __device__ void equalize_bin_lanes(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b,
                                    int32_t o0, const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1,
@@ -872,24 +873,31 @@ __device__ void merge_bin(const RunWork<Idx> &wk, int32_t p0, int32_t nb, int32_
 // Philox draw (merge number m0 + pair).  A round of one pair (always valid)
 // is the serial step.  Serial merging is a chain of wave minima or dependent
 // loads per merge: the 64-network batch's resample, which waits for its bins of
-// 512 walkers, 392 us that way and 158 in rounds (placement included).
-// LDS of the calling wave, n <= MERGE_ROUNDS_MAX: see MergeLds.
+// 512 walkers, 392 us that way and 158 in rounds (placement included).  A round
+// costs about two serial merges, and where weights span many decades it may hold
+// one pair, so the count-only rule takes rounds past 256 walkers only (16 toggle
+// runs of 64 bins x 16: 10.2 us serial, 16.4 in rounds from 12 merges on); the
+// weight-equalizing rule, which merges on while two weights are far below the
+// ideal, from 65 (see equalize_bin_rounds).
+// CAP: the most walkers the wave's LDS holds (0: none), a multiple of 8.
 #define MERGE_ROUNDS_MAX 2048
 struct MergeLds {
     double *aw, *bw, *cw;      // [n] sorted weights, [n] merged weights, [128] a round's walkers
     uint16_t *aq, *bq, *cq;    // their slots in the bin
 };
-__host__ __device__ inline size_t merge_lds_bytes() {
-    return (size_t)MERGE_ROUNDS_MAX * 2 * (sizeof(double) + sizeof(uint16_t)) + 128 * (sizeof(double) + sizeof(uint16_t));
+template <int CAP>
+__host__ __device__ constexpr size_t merge_lds_bytes() {
+    return CAP ? (size_t)CAP * 2 * (sizeof(double) + sizeof(uint16_t)) + 128 * (sizeof(double) + sizeof(uint16_t)) : 0;
 }
+template <int CAP>
 __device__ __forceinline__ MergeLds merge_lds(unsigned char *p) {
     MergeLds l;
     l.aw = reinterpret_cast<double *>(p);
-    l.bw = l.aw + MERGE_ROUNDS_MAX;
-    l.cw = l.bw + MERGE_ROUNDS_MAX;
+    l.bw = l.aw + CAP;
+    l.cw = l.bw + CAP;
     l.aq = reinterpret_cast<uint16_t *>(l.cw + 128);
-    l.bq = l.aq + MERGE_ROUNDS_MAX;
-    l.cq = l.bq + MERGE_ROUNDS_MAX;
+    l.bq = l.aq + CAP;
+    l.cq = l.bq + CAP;
     return l;
 }
 
@@ -922,14 +930,32 @@ __device__ void sort_ties(const MergeLds &l, int32_t h, int32_t t0, int32_t t, i
     }
 }
 
-__device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
-                                 const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1, const MergeLds &l, int lane) {
-    double *W = wk.w + p0;
+// EQ: the weight-equalizing rule's merges (equalize_bin_lanes' condition; how many
+// of a round's pairs it lets through is a scan over what each changes `need` by).
+// W ends with the survivors' weights, merged-away walkers -1; -> survivors.
+template <bool EQ>
+__device__ int32_t merge_rounds(double *W, int32_t nb, int32_t M, int32_t b, uint32_t iter, uint32_t k0, uint32_t k1,
+                                const MergeLds &l, int lane) {
     for (int32_t q = lane; q < nb; q += 64) {
         l.aw[q] = W[q];
         l.aq[q] = (uint16_t)q;
     }
     wave_sync();
+    bool eq = false;
+    double ideal = 0.0, two_ideal = 0.0;
+    int32_t need = 0;
+    if constexpr (EQ) {
+        double Wb = 0.0;                  // the bin's weight, in slot order
+#pragma unroll 8
+        for (int32_t q = 0; q < nb; ++q) Wb = Wb + l.aw[q];
+        eq = Wb > 0.0;
+        ideal = Wb / (double)M;
+        two_ideal = ideal + ideal;
+        if (eq)
+            for (int32_t q = lane; q < nb; q += 64) need += need_copies(l.aw[q], two_ideal);
+        need = wave_sum_i32(need);
+    }
+    int32_t n = nb;
     // bitonic network; mirrored first steps make positions past nb act as +inf
     int32_t P = 1;
     while (P < nb) P <<= 1;
@@ -955,7 +981,7 @@ __device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t
     const double inf = __builtin_huge_val();
     int32_t ha = 0, hb = 0, t = 0;          // fronts of A and B, end of B
     int32_t m0 = 0;                          // merges made
-    while (m0 < nb - M) {
+    while (EQ ? n > 1 : n > M) {
         // up to 64 walkers from the front of each
         const int32_t ia = ha + lane, ib = hb + lane;
         const double wa = ia < nb ? l.aw[ia] : inf, wb = ib < t ? l.bw[ib] : inf;
@@ -1002,20 +1028,36 @@ __device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t
         int32_t sure = na + nbm;
         if (na == 64 && ha + 64 < nb) sure = min(sure, __builtin_amdgcn_readlane(ra, 63) + 1);
         if (nbm == 64 && hb + 64 < t) sure = min(sure, __builtin_amdgcn_readlane(rb, 63) + 1);
-        const int32_t pairs = min(all ? sure >> 1 : 1, nb - M - m0);
-        double sum = 0.0;
+        int32_t pairs = min(all ? sure >> 1 : 1, EQ ? n - 1 : n - M);
+        const int32_t offered = pairs;
+        double wi = 0.0, wj = 0.0, sum = 0.0;
+        if (lane < offered) {
+            wi = l.cw[2 * lane];
+            wj = l.cw[2 * lane + 1];
+            sum = wi + wj;
+        }
+        if constexpr (EQ) {
+            int32_t more = 0, tot;        // what the lane's merge adds to need
+            if (eq && lane < offered)
+                more = need_copies(sum, two_ideal) - need_copies(wi, two_ideal) - need_copies(wj, two_ideal);
+            const int32_t at = need + wave_excl_scan(more, &tot);
+            const bool go = eq ? (sum <= ideal || at > M) : (n - lane > M);
+            const unsigned long long stop = __ballot(lane < offered && !go);
+            if (stop) pairs = __ffsll((long long)stop) - 1;
+            need = pairs < offered ? __builtin_amdgcn_readlane(at, pairs) : need + tot;
+        }
         int32_t keep = 0;
         if (lane < pairs) {
-            const double wi = l.cw[2 * lane], wj = l.cw[2 * lane + 1];
             const int32_t qi = l.cq[2 * lane], qj = l.cq[2 * lane + 1];
             const U4 rr = philox4x32_10((uint32_t)(m0 + lane), (uint32_t)b, iter, 1u, k0, k1);
             const double u = uniform53(rr.x, rr.y);
-            sum = wi + wj;
             const double p_i = wi / sum;
             keep = (u < p_i) ? qi : qj;
             W[keep] = sum;
             W[keep == qi ? qj : qi] = -1.0;
         }
+        n -= pairs;
+        if (EQ && pairs < offered) break;
         // consumed: the walkers of rank below 2 pairs
         ha += (int32_t)__popcll(__ballot(lane < na && ra < 2 * pairs));
         hb += (int32_t)__popcll(__ballot(lane < nbm && rb < 2 * pairs));
@@ -1034,6 +1076,15 @@ __device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     wave_sync();
+    return n;
+}
+
+template <int CAP>
+__device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
+                                 const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1, unsigned char *lds,
+                                 int lane) {
+    const double *W = wk.w + p0;
+    merge_rounds<false>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
     // survivors in slot order
     int32_t o = o0;
     for (int32_t c0 = 0; c0 < nb; c0 += 64) {
@@ -1051,25 +1102,49 @@ __device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t
     }
 }
 
+// equalize_bin_lanes with its merges in rounds.  Ten futile-cycle runs of 101 bins
+// x 100 walkers wait for one bin of 190 walkers and 138 merges: 85 us merged one
+// by one, 38 in rounds.
+template <int K, int CAP>
+__device__ __forceinline__ void equalize_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M,
+                                                    int32_t b, int32_t o0, const BinOut &out, uint32_t iter,
+                                                    uint32_t k0, uint32_t k1, unsigned char *lds, int lane) {
+    const int32_t n = merge_rounds<true>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
+    double wv[K];
+    bool live[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        wv[k] = 64 * k + lane < nb ? wk.w[p0 + 64 * k + lane] : -1.0;
+        live[k] = wv[k] >= 0.0;
+    }
+    hand_out<K>(wk, p0, M, b, o0, out, wv, live, n, lane);
+}
+
 }  // namespace
 
 // One bin's split/merge (and its row of the reweighting flux matrix) on the
 // calling wave: the walkers at positions [p0, p0 + nb) of wk, the output at
-// slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).  BIG: bins of
-// up to 512 walkers to split or equalize in registers, up to eight walkers per
-// lane (more than a 1024-thread workgroup has room for; else 128 and 256), and
-// of up to MERGE_ROUNDS_MAX to merge in rounds in the wave's LDS mlds.
-template <class Idx, int RULE, bool BIG>
+// slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).  CAP: walkers
+// the wave's LDS lds holds for merges in rounds.  With MERGE_ROUNDS_MAX the bins
+// to split or equalize in registers reach 512 walkers, eight per lane (more than
+// a 1024-thread workgroup has room for; else 128 and 256).
+template <class Idx, int RULE, int CAP>
 __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const BinOut &out, int32_t run, int32_t b,
                              int32_t nb, int32_t p0, int32_t o0, uint32_t iter, uint32_t k0, uint32_t k1,
-                             bool rw_acc, int lane, unsigned char *mlds = nullptr) {
+                             bool rw_acc, int lane, unsigned char *lds = nullptr) {
+    constexpr bool BIG = CAP >= MERGE_ROUNDS_MAX;
     const int32_t NB = a.n_bins, M = a.m_targ;
     if (rw_acc) rw_flux_bin(a.rw_F + ((size_t)run * NB + b) * NB, wk, p0, nb, NB > 1 ? 32 - __clz(NB - 1) : 0, lane);
     if (RULE < 0 ? a.rs_rule == 1 : RULE == 1) {
         if (nb <= 64) equalize_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        else if constexpr (CAP > 0) {
+            if (CAP >= 128 && nb <= 128) equalize_bin_rounds<2, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
+            else if (CAP >= 256 && nb <= 256) equalize_bin_rounds<4, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
+            else if (BIG && nb <= 512) equalize_bin_rounds<8, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
+            else merge_bin<Idx, true>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
+        }
         else if (nb <= 128) equalize_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 256) equalize_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
-        else if (BIG && nb <= 512) equalize_bin_lanes<8>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else merge_bin<Idx, true>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
     } else if (nb == M) {
         for (int32_t q = lane; q < nb; q += 64) {
@@ -1088,7 +1163,7 @@ __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const Bin
         else if (nb <= 128) merge_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 256) merge_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (BIG && nb <= MERGE_ROUNDS_MAX) {
-            if constexpr (BIG) merge_bin_rounds(wk, p0, nb, M, b, o0, out, iter, k0, k1, merge_lds(mlds), lane);
+            if constexpr (BIG) merge_bin_rounds<CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
         }
         else merge_bin<Idx, false>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
     }
@@ -1372,7 +1447,7 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
     for (int32_t b = wave; b < NB; b += n_waves) {
         const int32_t nb = uni(cnt[b]);
         if (nb == 0) continue;
-        resample_bin<Idx, RULE, false>(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
+        resample_bin<Idx, RULE, 0>(a, wk, out, run, b, nb, uni(start[b]), uni(ostart[b]), iter, k0, k1, rw_acc, lane);
     }
     __syncthreads();
     if (tid == 0) a.n_walk[run] = ostart[NB];
@@ -1395,7 +1470,7 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a
 // Bin-parallel split/merge after we_resample_kernel's placement: grid
 // (ceil(n_bins / 4), runs), one wave per bin, the same per-bin steps on the
 // run's arrays in device memory; bins of one run write disjoint ranges.
-template <int RULE, bool BIG>
+template <int RULE, int CAP>
 __device__ __forceinline__ void resample_bins_wave(const SimArgs &a, double *__restrict__ w_nxt,
                                                    const int32_t *__restrict__ binfo, int32_t run, int32_t b,
                                                    unsigned char *mlds) {
@@ -1413,22 +1488,31 @@ __device__ __forceinline__ void resample_bins_wave(const SimArgs &a, double *__r
     out.wn = w_nxt + base;
     const uint32_t iter = *a.iter_dev;
     const uint64_t seed = a.seeds[run];
-    resample_bin<int32_t, RULE, BIG>(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
+    resample_bin<int32_t, RULE, CAP>(a, wk, out, run, b, nb, uni(bi[NB + b]), uni(bi[2 * NB + b]), iter, (uint32_t)seed,
                                      (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane, mlds);
 }
 
-// Waves (bins) per workgroup: one where a bin may need merge_bin_rounds' LDS.
-template <bool BIG>
+// Waves (bins) per workgroup.
+template <int CAP>
 struct BinsBlock {
-    static constexpr int WAVES = BIG ? 1 : 4;
+    static constexpr int WAVES = CAP >= MERGE_ROUNDS_MAX ? 1 : 4;
+    static constexpr size_t LDS = WAVES * merge_lds_bytes<CAP>();
 };
 
-template <int RULE, bool BIG>
-__global__ __launch_bounds__(64 * BinsBlock<BIG>::WAVES) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
+template <int RULE, int CAP>
+__global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
                                                                                     const int32_t *__restrict__ binfo) {
     extern __shared__ __align__(16) unsigned char mlds[];
-    resample_bins_wave<RULE, BIG>(a, w_nxt, binfo, blockIdx.y,
-                                  (int32_t)blockIdx.x * BinsBlock<BIG>::WAVES + (int32_t)(threadIdx.x >> 6), mlds);
+    const int32_t wave = (int32_t)(threadIdx.x >> 6);
+    resample_bins_wave<RULE, CAP>(a, w_nxt, binfo, blockIdx.y, (int32_t)blockIdx.x * BinsBlock<CAP>::WAVES + wave,
+                                  mlds + wave * merge_lds_bytes<CAP>());
+}
+
+template <int RULE, int CAP>
+void launch_bins(const SimArgs &a, double *w_nxt, const int32_t *binfo, hipStream_t st) {
+    constexpr int W = BinsBlock<CAP>::WAVES;
+    hipLaunchKernelGGL((we_resample_bins_kernel<RULE, CAP>), dim3((unsigned)((a.n_bins + W - 1) / W), (unsigned)a.n_runs),
+                       dim3(64 * W), BinsBlock<CAP>::LDS, st, a, w_nxt, binfo);
 }
 
 // New state rows from their parents: one lane per copy number.
@@ -1531,14 +1615,15 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_place_kernel(BatchP
     resample_run_t<int32_t, false, 0, true>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, b.binfo[i]);
 }
 
-template <bool BIG>
-__global__ __launch_bounds__(64 * BinsBlock<BIG>::WAVES) void we_batch_bins_kernel(BatchPtrs b) {
+template <int CAP>
+__global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_batch_bins_kernel(BatchPtrs b) {
     extern __shared__ __align__(16) unsigned char mlds[];
     const int32_t i = blockIdx.z;
     const SimArgs &a = b.args[i];
-    if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != BIG) return;
-    resample_bins_wave<-1, BIG>(a, b.w_nxt[i], b.binfo[i], blockIdx.x,
-                                (int32_t)blockIdx.y * BinsBlock<BIG>::WAVES + (int32_t)(threadIdx.x >> 6), mlds);
+    if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != (CAP >= MERGE_ROUNDS_MAX)) return;
+    const int32_t wave = (int32_t)(threadIdx.x >> 6);
+    resample_bins_wave<-1, CAP>(a, b.w_nxt[i], b.binfo[i], blockIdx.x, (int32_t)blockIdx.y * BinsBlock<CAP>::WAVES + wave,
+                                mlds + wave * merge_lds_bytes<CAP>());
 }
 
 // Grid-strided over each member's own cells: a grid sized for the largest
@@ -1588,9 +1673,11 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
     hipLaunchKernelGGL(we_batch_place_kernel, dim3(max_runs, n_sims),
                        dim3(resample_threads((int64_t)max_runs * n_sims)), shmem, st, b);
     if (m_sizes & 2u)
-        hipLaunchKernelGGL(we_batch_bins_kernel<true>, dim3(max_runs, max_bins, n_sims), dim3(64), merge_lds_bytes(), st, b);
+        hipLaunchKernelGGL(we_batch_bins_kernel<MERGE_ROUNDS_MAX>, dim3(max_runs, max_bins, n_sims), dim3(64),
+                           BinsBlock<MERGE_ROUNDS_MAX>::LDS, st, b);
     if (m_sizes & 1u)
-        hipLaunchKernelGGL(we_batch_bins_kernel<false>, dim3(max_runs, (max_bins + 3) / 4, n_sims), dim3(256), 0, st, b);
+        hipLaunchKernelGGL(we_batch_bins_kernel<256>, dim3(max_runs, (max_bins + 3) / 4, n_sims), dim3(256),
+                           BinsBlock<256>::LDS, st, b);
     const unsigned gg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_cells + 255) / 256, BATCH_GATHER_BLOCKS));
     hipLaunchKernelGGL(we_batch_gather_kernel, dim3(gg, n_sims), dim3(256), 0, st, b);
     if (observe) hipLaunchKernelGGL(we_batch_observe_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
@@ -1656,11 +1743,10 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
         // targets of at most 128 walkers leave few bins past 256, and the
         // larger register files would cost the small bins occupancy
         const bool big = a.m_targ > RESAMPLE_BIG_M;
-        const dim3 gb((unsigned)(big ? a.n_bins : (a.n_bins + 3) / 4), (unsigned)a.n_runs);
-        if (eq && big) hipLaunchKernelGGL((we_resample_bins_kernel<1, true>), gb, dim3(64), merge_lds_bytes(), st, a, w_nxt, binfo);
-        else if (eq) hipLaunchKernelGGL((we_resample_bins_kernel<1, false>), gb, dim3(256), 0, st, a, w_nxt, binfo);
-        else if (big) hipLaunchKernelGGL((we_resample_bins_kernel<0, true>), gb, dim3(64), merge_lds_bytes(), st, a, w_nxt, binfo);
-        else hipLaunchKernelGGL((we_resample_bins_kernel<0, false>), gb, dim3(256), 0, st, a, w_nxt, binfo);
+        if (eq && big) launch_bins<1, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
+        else if (eq) launch_bins<1, 256>(a, w_nxt, binfo, st);
+        else if (big) launch_bins<0, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
+        else launch_bins<0, 0>(a, w_nxt, binfo, st);
     } else if (use_lds) {
         if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
         else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
