@@ -1730,8 +1730,7 @@ bool resample_bins_parallel(const SimArgs &a) {
            a.n_bins >= waves;
 }
 
-hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur, int32_t *x_nxt,
-                           double *w_nxt, int32_t *binfo, hipStream_t st) {
+hipError_t launch_resample(const SimArgs &a, const double *w_cur, double *w_nxt, int32_t *binfo, hipStream_t st) {
     const bool split = binfo && resample_bins_parallel(a);
     const bool use_lds = !split && resample_uses_lds(a);
     const size_t shmem = resample_lds_bytes(a, use_lds);
@@ -1754,12 +1753,6 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
         if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
         else hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t total = (int64_t)a.n_runs * a.cap * a.S;
-    const int32_t narrow = total + 256 < ((int64_t)1 << 31) ? 1 : 0;
-    hipLaunchKernelGGL(we_gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       a, x_cur, x_nxt, narrow);
     return hipGetLastError();
 }
 
@@ -1780,7 +1773,15 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
 #define OBS_JOINT_LOG2 9
 #define OBS_JOINT_SLOTS (1 << OBS_JOINT_LOG2)
 #define OBS_JOINT_PROBES 16
-__global__ __launch_bounds__(256) void we_observe_lds_kernel(SimArgs a, const int32_t *__restrict__ xs,
+// FRESH: the state rows are still the parents' (x_cur): each thread copies its
+// walkers' rows to xs first, in place of the gather's launch.  What bounds both
+// is the launch; a row of up to OBS_ROW_MAX counts fits one thread (longer ones
+// want a lane per count).  Gather and observation of 16 runs of 64 bins x 16, 8
+// species: 5.6 us, as two launches 4.4 and 4.1 and the gap between them.
+#define OBS_ROW_MAX 16
+template <bool FRESH>
+__global__ __launch_bounds__(256) void we_observe_lds_kernel(SimArgs a, const int32_t *__restrict__ x_cur,
+                                                             int32_t *__restrict__ xs,
                                                              const double *__restrict__ ws, int32_t per) {
     extern __shared__ __align__(16) unsigned char obs_lds[];
     double *h = reinterpret_cast<double *>(obs_lds);
@@ -1806,12 +1807,22 @@ __global__ __launch_bounds__(256) void we_observe_lds_kernel(SimArgs a, const in
     for (int32_t k = k0 + tid; k < k1; k += blockDim.x) {
         const size_t idx = base + k;
         const double wv = ws[idx];
-        const int32_t v = xs[idx * a.S + a.hist_species] - a.hist_lo;
+        const int32_t *row = FRESH ? x_cur + (base + (size_t)a.origin[idx]) * a.S : xs + idx * a.S;
+        if constexpr (FRESH) {
+            int32_t c[OBS_ROW_MAX];
+#pragma unroll
+            for (int sp = 0; sp < OBS_ROW_MAX; ++sp)
+                if (sp < a.S) c[sp] = row[sp];
+#pragma unroll
+            for (int sp = 0; sp < OBS_ROW_MAX; ++sp)
+                if (sp < a.S) xs[idx * a.S + sp] = c[sp];
+        }
+        const int32_t v = row[a.hist_species] - a.hist_lo;
         if (v >= 0 && v < a.nh) atomicAdd(&h[v], wv);
         if (a.n_joint > 0) {
             int32_t cell = 0, mul = 1;
             for (int d = 0; d < a.n_joint; ++d) {
-                const int32_t c = min(xs[idx * a.S + a.joint_species[d]] / a.joint_width, a.joint_bins - 1);
+                const int32_t c = min(row[a.joint_species[d]] / a.joint_width, a.joint_bins - 1);
                 cell += c * mul;
                 mul *= a.joint_bins;
             }
@@ -1836,21 +1847,35 @@ __global__ __launch_bounds__(256) void we_observe_lds_kernel(SimArgs a, const in
         if (jkey[v] >= 0) atomicAdd(&jrow[jkey[v]], jval[v]);
 }
 
-// Histograms and the end of the iteration; *advanced tells whether the iteration
-// counter was advanced (else the caller launches the advance kernel).
-hipError_t launch_observe(const SimArgs &a, const int32_t *xs, const double *ws, hipStream_t st, bool *advanced) {
+// New state rows (x_nxt), histograms and the end of the iteration; *advanced tells
+// whether the iteration counter was advanced (else the caller launches the
+// advance kernel).
+hipError_t launch_gather_observe(const SimArgs &a, const int32_t *x_cur, int32_t *x_nxt, const double *ws,
+                                 hipStream_t st, bool *advanced) {
     *advanced = false;
-    if (a.nh > 0 && a.nh <= OBS_LDS_BINS) {
+    const bool in_lds = a.nh > 0 && a.nh <= OBS_LDS_BINS;
+    const bool fresh = in_lds && a.S <= OBS_ROW_MAX;
+    if (!fresh) {
+        const int64_t total = (int64_t)a.n_runs * a.cap * a.S;
+        const int32_t narrow = total + 256 < ((int64_t)1 << 31) ? 1 : 0;
+        hipLaunchKernelGGL(we_gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
+                           a, x_cur, x_nxt, narrow);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (a.nh <= 0 && a.n_joint <= 0) return hipSuccess;
+    if (in_lds) {
         const int32_t per = a.n_runs < OBS_FEW_RUNS ? OBS_WALKERS_FEW : OBS_WALKERS;
         const dim3 grid((unsigned)a.n_runs, (unsigned)((a.cap + per - 1) / per));
-        hipLaunchKernelGGL(we_observe_lds_kernel, grid, dim3(256), (size_t)a.nh * sizeof(double), st, a, xs, ws,
-                           per);
+        const size_t lds = (size_t)a.nh * sizeof(double);
+        if (fresh) hipLaunchKernelGGL(we_observe_lds_kernel<true>, grid, dim3(256), lds, st, a, x_cur, x_nxt, ws, per);
+        else hipLaunchKernelGGL(we_observe_lds_kernel<false>, grid, dim3(256), lds, st, a, x_cur, x_nxt, ws, per);
         *advanced = true;
         return hipGetLastError();
     }
     const int64_t total = (int64_t)a.n_runs * a.cap;
     hipLaunchKernelGGL(we_observe_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       a, xs, ws);
+                       a, x_nxt, ws);
     return hipGetLastError();
 }
 

@@ -30,11 +30,10 @@ hipError_t launch_ssa_wave(const SimArgs &a, int32_t *xs, hipStream_t st);
 bool wave_kernel_fits(int32_t S, int32_t R);
 hipError_t launch_recycle_bin(const SimArgs &a, int32_t *x_cur, bool grid_bins, hipStream_t st);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
-hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur, int32_t *x_nxt,
-                           double *w_nxt, int32_t *binfo, hipStream_t st);
+hipError_t launch_resample(const SimArgs &a, const double *w_cur, double *w_nxt, int32_t *binfo, hipStream_t st);
 hipError_t launch_advance(const SimArgs &a, hipStream_t st);
-hipError_t launch_observe(const SimArgs &a, const int32_t *xs, const double *ws, hipStream_t st,
-                          bool *advanced);
+hipError_t launch_gather_observe(const SimArgs &a, const int32_t *x_cur, int32_t *x_nxt, const double *ws,
+                                 hipStream_t st, bool *advanced);
 
 namespace {
 thread_local std::string g_err;
@@ -893,7 +892,7 @@ we_status we_sim_bookkeeping(we_sim *s, hipStream_t st, hipEvent_t *ev) {
         e = committor_bin(s, s->x[c], st);
         if (e != hipSuccess) return hip_fail(e, "committor bin launch");
     }
-    e = launch_resample(a, s->x[c], s->w[c], s->x[nx], s->w[nx], s->rs_binfo, st);
+    e = launch_resample(a, s->w[c], s->w[nx], s->rs_binfo, st);
     if (e != hipSuccess) return hip_fail(e, "resample launch");
     if (a.rw_period > 0) {
         e = launch_reweight(a, s->w[nx], st);
@@ -901,10 +900,8 @@ we_status we_sim_bookkeeping(we_sim *s, hipStream_t st, hipEvent_t *ev) {
     }
     if (ev) HIP_TRY(hipEventRecord(ev[1], st));
     bool advanced = false;
-    if (a.nh > 0 || a.n_joint > 0) {
-        e = launch_observe(a, s->x[nx], s->w[nx], st, &advanced);
-        if (e != hipSuccess) return hip_fail(e, "observe launch");
-    }
+    e = launch_gather_observe(a, s->x[c], s->x[nx], s->w[nx], st, &advanced);
+    if (e != hipSuccess) return hip_fail(e, "gather/observe launch");
     if (!advanced) {
         e = launch_advance(a, st);
         if (e != hipSuccess) return hip_fail(e, "advance launch");
