@@ -61,6 +61,8 @@
 #define RESAMPLE_BIN_PARALLEL_RUNS 256
 #define RESAMPLE_BIN_PARALLEL_BINS 32
 #define RESAMPLE_BIG_M 128
+// Recycling and binning in the run's workgroup: rows of at most this many counts.
+#define RESAMPLE_ROW_MAX 4
 // Threads per run: up to 16 waves, so up to 16 bins are split/merged at
 // once.  With many runs the grid fills the chip anyway and smaller blocks
 // cost less to start, so launches with at least RESAMPLE_MANY_RUNS blocks use
@@ -1184,9 +1186,12 @@ __device__ __forceinline__ RunWork<int32_t> global_work(const SimArgs &a, size_t
 // (Idx int32).  PLACE (device arrays only): stop after placement and staging,
 // and leave each bin's count, first position and first output slot in
 // binfo[run][3][n_bins] for we_resample_bins_kernel.
+// x_cur (LDS, at most one walker per thread; null: already done): recycle and bin
+// the run's walkers first.
 template <class Idx, bool LDS, int RULE, bool PLACE>
-__device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cur, double *__restrict__ w_nxt,
-                               int32_t run, unsigned char *lds, int32_t *__restrict__ binfo) {
+__device__ void resample_run_t(const SimArgs &a, int32_t *__restrict__ x_cur, const double *__restrict__ w_cur,
+                               double *__restrict__ w_nxt, int32_t run, unsigned char *lds,
+                               int32_t *__restrict__ binfo) {
     const int32_t tid = threadIdx.x, nthr = blockDim.x;
     const int lane = tid & 63, wave = tid >> 6, n_waves = nthr >> 6;
     const int32_t NB = a.n_bins, M = a.m_targ, cap = a.cap;
@@ -1241,6 +1246,8 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
         evb[b] = 0.0f;
     }
     for (int32_t i = tid; i < P * NB; i += nthr) cursor[i] = 0;
+    if constexpr (LDS)
+        if (x_cur && tid < n) recycle_bin_one(a, x_cur, 1, (int64_t)run * cap + tid);   // counted by this thread below
     __syncthreads();
     // counts per bin and per cursor row: each wave takes 64 consecutive slots
     // (one cursor row: per_row is a multiple of 64), four such chunks' loads at a
@@ -1460,11 +1467,11 @@ __device__ void resample_run_t(const SimArgs &a, const double *__restrict__ w_cu
 enum ResampleMode { RS_LDS, RS_GLOBAL, RS_PLACE };
 
 template <int MODE, int RULE>
-__global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a, const double *__restrict__ w_cur,
+__global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a, int32_t *__restrict__ x_cur, const double *__restrict__ w_cur,
                                                           double *__restrict__ w_nxt, int32_t *__restrict__ binfo) {
     extern __shared__ __align__(16) unsigned char lds[];
-    if constexpr (MODE == RS_LDS) resample_run_t<uint16_t, true, RULE, false>(a, w_cur, w_nxt, blockIdx.x, lds, nullptr);
-    else resample_run_t<int32_t, false, RULE, MODE == RS_PLACE>(a, w_cur, w_nxt, blockIdx.x, lds, binfo);
+    if constexpr (MODE == RS_LDS) resample_run_t<uint16_t, true, RULE, false>(a, x_cur, w_cur, w_nxt, blockIdx.x, lds, nullptr);
+    else resample_run_t<int32_t, false, RULE, MODE == RS_PLACE>(a, x_cur, w_cur, w_nxt, blockIdx.x, lds, binfo);
 }
 
 // Bin-parallel split/merge after we_resample_kernel's placement: grid
@@ -1612,7 +1619,7 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_place_kernel(BatchP
     const int32_t i = blockIdx.y;
     const SimArgs &a = b.args[i];
     if ((int32_t)blockIdx.x >= a.n_runs) return;
-    resample_run_t<int32_t, false, 0, true>(a, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, b.binfo[i]);
+    resample_run_t<int32_t, false, 0, true>(a, nullptr, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, b.binfo[i]);
 }
 
 template <int CAP>
@@ -1730,15 +1737,29 @@ bool resample_bins_parallel(const SimArgs &a) {
            a.n_bins >= waves;
 }
 
-hipError_t launch_resample(const SimArgs &a, const double *w_cur, double *w_nxt, int32_t *binfo, hipStream_t st) {
-    const bool split = binfo && resample_bins_parallel(a);
+// Recycling and binning by the run's workgroup saves a launch, and costs its
+// chain of fetches (row, coefficients, a search of the edges) once per walker of a
+// thread.  It pays for short rows and one walker per thread: one birth-death run,
+// 20 intervals 545 -> 499 us, 256 tau-leaping runs of 40 bins x 16, 50 intervals
+// 4.32 -> 4.22 ms.  With two walkers per thread it is even (2048 Schloegl runs:
+// 55.4 + 8.4 us -> 63.9), with 8 species or 2.5 walkers per thread it loses (16 toggle
+// runs 8.2 + 4.9 us -> 16.1, 32 Schloegl runs of 80 x 32 10.4 + 4.8 -> 16.8).
+bool resample_recycles(const SimArgs &a) {
+    return !resample_bins_parallel(a) && resample_uses_lds(a) && a.S <= RESAMPLE_ROW_MAX &&
+           a.cap <= (int32_t)resample_threads(a.n_runs);
+}
+
+// x_cur: null, or the rows to recycle and bin first (resample_recycles).
+hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur, double *w_nxt, int32_t *binfo,
+                           hipStream_t st) {
+    const bool split = resample_bins_parallel(a);
     const bool use_lds = !split && resample_uses_lds(a);
     const size_t shmem = resample_lds_bytes(a, use_lds);
     const bool eq = a.rs_rule == 1;
     const dim3 gr(a.n_runs), br(resample_threads(a.n_runs));
     if (split) {
         // the placement takes no rule
-        hipLaunchKernelGGL((we_resample_kernel<RS_PLACE, 0>), gr, br, shmem, st, a, w_cur, w_nxt, binfo);
+        hipLaunchKernelGGL((we_resample_kernel<RS_PLACE, 0>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, binfo);
         // targets of at most 128 walkers leave few bins past 256, and the
         // larger register files would cost the small bins occupancy
         const bool big = a.m_targ > RESAMPLE_BIG_M;
@@ -1747,11 +1768,11 @@ hipError_t launch_resample(const SimArgs &a, const double *w_cur, double *w_nxt,
         else if (big) launch_bins<0, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
         else launch_bins<0, 0>(a, w_nxt, binfo, st);
     } else if (use_lds) {
-        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
-        else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
+        else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
     } else {
-        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 1>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
-        else hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 0>), gr, br, shmem, st, a, w_cur, w_nxt, nullptr);
+        if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 1>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
+        else hipLaunchKernelGGL((we_resample_kernel<RS_GLOBAL, 0>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
     }
     return hipGetLastError();
 }

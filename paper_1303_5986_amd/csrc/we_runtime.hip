@@ -30,7 +30,9 @@ hipError_t launch_ssa_wave(const SimArgs &a, int32_t *xs, hipStream_t st);
 bool wave_kernel_fits(int32_t S, int32_t R);
 hipError_t launch_recycle_bin(const SimArgs &a, int32_t *x_cur, bool grid_bins, hipStream_t st);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
-hipError_t launch_resample(const SimArgs &a, const double *w_cur, double *w_nxt, int32_t *binfo, hipStream_t st);
+bool resample_recycles(const SimArgs &a);
+hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur, double *w_nxt, int32_t *binfo,
+                           hipStream_t st);
 hipError_t launch_advance(const SimArgs &a, hipStream_t st);
 hipError_t launch_gather_observe(const SimArgs &a, const int32_t *x_cur, int32_t *x_nxt, const double *ws,
                                  hipStream_t st, bool *advanced);
@@ -886,13 +888,15 @@ we_status we_read_err(we_sim *s) { return read_err(s); }
 we_status we_sim_bookkeeping(we_sim *s, hipStream_t st, hipEvent_t *ev) {
     SimArgs &a = s->args;
     const int32_t c = s->cur, nx = 1 - c;
-    hipError_t e = launch_recycle_bin(a, s->x[c], !s->cm.active, st);
+    const bool in_resample = !s->cm.active && resample_recycles(a);
+    hipError_t e = hipSuccess;
+    if (!in_resample) e = launch_recycle_bin(a, s->x[c], !s->cm.active, st);
     if (e != hipSuccess) return hip_fail(e, "recycle/bin launch");
     if (s->cm.active) {
         e = committor_bin(s, s->x[c], st);
         if (e != hipSuccess) return hip_fail(e, "committor bin launch");
     }
-    e = launch_resample(a, s->w[c], s->w[nx], s->rs_binfo, st);
+    e = launch_resample(a, in_resample ? s->x[c] : nullptr, s->w[c], s->w[nx], s->rs_binfo, st);
     if (e != hipSuccess) return hip_fail(e, "resample launch");
     if (a.rw_period > 0) {
         e = launch_reweight(a, s->w[nx], st);

@@ -1,7 +1,8 @@
 """Placement of walkers by bin: one bin, numbers of bins around powers of two
 (a ballot per bit of the bin's number), more bins than cursor rows for all
 waves, more walkers than a pass of the recycled sum takes (512), and few walkers
-in a last chunk; with the bins merged in the run's workgroup and by bin, for
+in a last chunk; recycled and binned beforehand or by the run's workgroup (one walker
+per thread at most); with the bins merged in the run's workgroup and by bin, for
 both rules.  Everything against the CPU oracle, bit for bit."""
 import dataclasses
 
@@ -23,6 +24,10 @@ CASES = {
     "1100 bins, 7 rows": (1100, 1.0, 5, 1, 1, 101),
     "6000 bins, one row": (6000, 1.0, 3, 1, 0, 99),
     "many runs": (17, 10.0, 12, 520, 0, 95),
+    "a walker per thread": (16, 8.0, 64, 2, 0, 95),
+    "some threads two": (16, 8.0, 65, 2, 1, 95),
+    "many runs, a walker per thread": (16, 8.0, 16, 512, 1, 95),
+    "many runs, some threads two": (16, 8.0, 17, 512, 0, 95),
 }
 
 
