@@ -910,7 +910,7 @@ __device__ __forceinline__ bool lighter(double w0, int32_t q0, double w1, int32_
 // B[t0, t) was appended to B[h, t0): puts every run of equal weights that has
 // an appended walker into slot order.  Odd-even transposition, as long as
 // something moves: runs are short unless many weights are equal.
-__device__ void sort_ties(const MergeLds &l, int32_t h, int32_t t0, int32_t t, int lane) {
+__device__ __forceinline__ void sort_ties(const MergeLds &l, int32_t h, int32_t t0, int32_t t, int lane) {
     int32_t lo = t0;                          // the run that reaches back starts here
     const double w0 = l.bw[t0];
     while (lo > h && l.bw[lo - 1] == w0) --lo;
@@ -935,8 +935,8 @@ __device__ void sort_ties(const MergeLds &l, int32_t h, int32_t t0, int32_t t, i
 // EQ: the weight-equalizing rule's merges (equalize_bin_lanes' condition; how many
 // of a round's pairs it lets through is a scan over what each changes `need` by).
 // W ends with the survivors' weights, merged-away walkers -1; -> survivors.
-template <bool EQ>
-__device__ int32_t merge_rounds(double *W, int32_t nb, int32_t M, int32_t b, uint32_t iter, uint32_t k0, uint32_t k1,
+template <bool EQ, int CAP>
+__device__ __forceinline__ int32_t merge_rounds(double *W, int32_t nb, int32_t M, int32_t b, uint32_t iter, uint32_t k0, uint32_t k1,
                                 const MergeLds &l, int lane) {
     for (int32_t q = lane; q < nb; q += 64) {
         l.aw[q] = W[q];
@@ -958,25 +958,39 @@ __device__ int32_t merge_rounds(double *W, int32_t nb, int32_t M, int32_t b, uin
         need = wave_sum_i32(need);
     }
     int32_t n = nb;
-    // bitonic network; mirrored first steps make positions past nb act as +inf
+    // bitonic network; mirrored first steps make positions past nb act as +inf.
+    // AHEAD pairs of a lane are read before the first is written: the largest bins
+    // of a 64-network batch (700 walkers) 123 -> 111 us, ten futile-cycle runs of
+    // 101 bins x 100 38 -> 35.6.  A wave alone on its SIMD, it is bound by issue now.
+    constexpr int AHEAD = CAP >= MERGE_ROUNDS_MAX ? 8 : 2;
     int32_t P = 1;
     while (P < nb) P <<= 1;
     for (int32_t size = 2; size <= P; size <<= 1)
         for (int32_t d = size >> 1; d > 0; d >>= 1) {
             const bool mirror = d == (size >> 1);
-            for (int32_t c = lane; c < (P >> 1); c += 64) {
-                const int32_t r = c & (d - 1), base = (c - r) << 1;
-                const int32_t i = base + r, j = mirror ? base + 2 * d - 1 - r : i + d;
-                if (j < nb) {
-                    const double wi = l.aw[i], wj = l.aw[j];
-                    const int32_t qi = l.aq[i], qj = l.aq[j];
-                    if (lighter(wj, qj, wi, qi)) {
-                        l.aw[i] = wj;
-                        l.aw[j] = wi;
-                        l.aq[i] = (uint16_t)qj;
-                        l.aq[j] = (uint16_t)qi;
-                    }
+            for (int32_t c0 = 0; c0 < (P >> 1); c0 += 64 * AHEAD) {
+                double wi[AHEAD], wj[AHEAD];
+                int32_t qi[AHEAD], qj[AHEAD], at[AHEAD], to[AHEAD];
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u) {
+                    const int32_t c = c0 + 64 * u + lane;
+                    const int32_t r = c & (d - 1), base = (c - r) << 1;
+                    at[u] = base + r;
+                    to[u] = mirror ? base + 2 * d - 1 - r : base + r + d;
+                    if (to[u] >= nb) at[u] = to[u] = nb - 1;   // nothing to exchange with
+                    wi[u] = l.aw[at[u]];
+                    wj[u] = l.aw[to[u]];
+                    qi[u] = l.aq[at[u]];
+                    qj[u] = l.aq[to[u]];
                 }
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+                    if (lighter(wj[u], qj[u], wi[u], qi[u])) {
+                        l.aw[at[u]] = wj[u];
+                        l.aw[to[u]] = wi[u];
+                        l.aq[at[u]] = (uint16_t)qj[u];
+                        l.aq[to[u]] = (uint16_t)qi[u];
+                    }
             }
             wave_sync();
         }
@@ -1082,11 +1096,11 @@ __device__ int32_t merge_rounds(double *W, int32_t nb, int32_t M, int32_t b, uin
 }
 
 template <int CAP>
-__device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
+__device__ __forceinline__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M, int32_t b, int32_t o0,
                                  const BinOut &out, uint32_t iter, uint32_t k0, uint32_t k1, unsigned char *lds,
                                  int lane) {
     const double *W = wk.w + p0;
-    merge_rounds<false>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
+    merge_rounds<false, CAP>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
     // survivors in slot order
     int32_t o = o0;
     for (int32_t c0 = 0; c0 < nb; c0 += 64) {
@@ -1106,12 +1120,12 @@ __device__ void merge_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t
 
 // equalize_bin_lanes with its merges in rounds.  Ten futile-cycle runs of 101 bins
 // x 100 walkers wait for one bin of 190 walkers and 138 merges: 85 us merged one
-// by one, 38 in rounds.
+// by one, 35.6 in rounds.
 template <int K, int CAP>
 __device__ __forceinline__ void equalize_bin_rounds(const RunWork<int32_t> &wk, int32_t p0, int32_t nb, int32_t M,
                                                     int32_t b, int32_t o0, const BinOut &out, uint32_t iter,
                                                     uint32_t k0, uint32_t k1, unsigned char *lds, int lane) {
-    const int32_t n = merge_rounds<true>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
+    const int32_t n = merge_rounds<true, CAP>(wk.w + p0, nb, M, b, iter, k0, k1, merge_lds<CAP>(lds), lane);
     double wv[K];
     bool live[K];
 #pragma unroll
