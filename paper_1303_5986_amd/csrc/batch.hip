@@ -200,8 +200,10 @@ __device__ __forceinline__ void batch_group_chunk(const SimArgs &a, const D *gde
     }
 }
 
+// BR > 0: three waves a SIMD (167 registers; left to itself the compiler takes 174
+// and the longest of these launches goes from 50.4 to 53.7 us).
 template <int L, int BR, bool LT>
-__global__ __launch_bounds__(256) void batch_group_kernel(const SimArgs *__restrict__ args,
+__global__ __launch_bounds__(256, BR > 0 ? 3 : 1) void batch_group_kernel(const SimArgs *__restrict__ args,
                                                           int32_t *const *__restrict__ xptr,
                                                           const Chunk *__restrict__ chunks, int32_t n_chunks,
                                                           uint32_t *__restrict__ counters, int32_t s_max, int32_t tables) {

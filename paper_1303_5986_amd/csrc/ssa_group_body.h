@@ -80,6 +80,34 @@ __device__ __forceinline__ double group_scan_incl(double v) {
     return v;
 }
 
+// The value of a group's last lane on all its lanes: row broadcasts (two banks of
+// four lanes each for groups of 8), a quad permutation, or lane reads.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double group_bcast(double old, double v) {
+    GroupF64 in, was, out;
+    in.d = v;
+    was.d = old;
+    out.w[0] = __builtin_amdgcn_update_dpp(was.w[0], in.w[0], CTRL, 0xF, BANKS, false);
+    out.w[1] = __builtin_amdgcn_update_dpp(was.w[1], in.w[1], CTRL, 0xF, BANKS, false);
+    return out.d;
+}
+template <int L>
+__device__ __forceinline__ double group_last(double v) {
+    if constexpr (L == 2) return group_bcast<0xF5, 0xF>(v, v);                              // quad_perm [1,1,3,3]
+    else if constexpr (L == 4) return group_bcast<0xFF, 0xF>(v, v);                         // quad_perm [3,3,3,3]
+    else if constexpr (L == 8) return group_bcast<0x15F, 0xC>(group_bcast<0x157, 0x3>(v, v), v);   // row_newbcast:7, 15
+    else if constexpr (L == 16) return group_bcast<0x15F, 0xF>(v, v);                       // row_newbcast:15
+    else {
+        GroupF64 in, lo, hi;
+        in.d = v;
+        for (int i = 0; i < 2; ++i) {
+            lo.w[i] = __builtin_amdgcn_readlane(in.w[i], 31);
+            hi.w[i] = __builtin_amdgcn_readlane(in.w[i], 63);
+        }
+        return (threadIdx.x & 32) ? hi.d : lo.d;
+    }
+}
+
 // The network tables a group walker reads: a.desc, a.chg_ptr and a.chg, or
 // a block's LDS copy of them.
 template <class D>
@@ -118,8 +146,11 @@ __device__ __forceinline__ GroupTables<D> group_stage(const SimArgs &a, const D 
 // and the 1 that an absent reactant of a RxnDesc2 reads).  Every lane of the
 // wave must call it.  D: the descriptors' form; a lane evaluates its whole block
 // every event, so the general form's two binomials per reaction were most of
-// an event's instructions.  Toggle, 16 runs on 8 walkers per wave: 46.2 -> 42.6 us
-// per launch.  BR > 0 (blocks of at most BR reactions): each
+// an event's instructions.  The event is free of branches but for the draw and
+// the change, so that the waiting time's division runs beside the selection, and
+// a0 comes by row broadcasts, not through LDS.  Two waves per SIMD issue for most
+// of the time.  Toggle, 16 runs on 8 walkers per wave: 46.2 us per launch with
+// binomials, 42.4 with branches, 39.3.  BR > 0 (blocks of at most BR reactions): each
 // lane keeps its block's descriptors in registers for the whole interval and
 // its block's propensities from step 1 for step 3, instead of reading the
 // descriptors again every event.
@@ -166,16 +197,15 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables<D> &tb, 
         }
     }
     while (__ballot(go)) {
-        // 1. this lane's partial sum over its block
+        // 1. this lane's partial sum over its block (0 past its end)
         double part = 0.0;
         if constexpr (BR > 0) {
-            if (go)
 #pragma unroll
-                for (int b = 0; b < NR; ++b)
-                    if (r_lo + b < r_hi) {
-                        pr[b] = propensity_from(dr[b], (uint32_t)lx[dr[b].s1], (uint32_t)lx[dr[b].s2]);
-                        part += pr[b];
-                    }
+            for (int b = 0; b < NR; ++b) {
+                const double p = propensity_from(dr[b], (uint32_t)lx[dr[b].s1], (uint32_t)lx[dr[b].s2]);
+                pr[b] = r_lo + b < r_hi ? p : 0.0;
+                part += pr[b];
+            }
         } else if (go) {
             for (int32_t r = r_lo; r < r_hi; ++r) {
                 const D d = tb.desc[r];
@@ -192,57 +222,44 @@ __device__ inline void group_walker(const SimArgs &a, const GroupTables<D> &tb, 
         const double ex = __shfl(rexp, src, 64);
         const double uu = __shfl(ru2, src, 64);
         const double incl = group_scan_incl<L>(part);
-        const double a0 = __shfl(incl, gbase + L - 1, 64);
-        double u2 = 0.0;
-        if (go) {
-            if (!(a0 > 0.0)) {
-                go = false;
-            } else {
-                const double dt = ex / a0;
-                u2 = uu;
-                e += 1;
-                if (t + dt > tau) go = false;
-                else t = t + dt;
-            }
-        }
-        const double target = u2 * a0;
-        const uint64_t over = __ballot(go && incl > target) & gmask;
-        const uint64_t pos = __ballot(go && part > 0.0) & gmask;
-        // the lane holding the target; rounding past the last block: the
-        // last lane with a positive sum
+        const double a0 = group_last<L>(incl);
+        const double target = uu * a0;
+        const double dt = ex / a0;
+        // 3. the lane holding the target (rounding past the last block: the last
+        // lane with a positive sum) and the reaction inside its block
+        const uint64_t over = __ballot(incl > target) & gmask;
+        const uint64_t pos = __ballot(part > 0.0) & gmask;
         const int chosen = over ? (__ffsll((long long)over) - 1)
                                 : (pos ? 63 - __builtin_clzll(pos) : gbase + L - 1);
-        const double excl = incl - part;
-        // 3. reaction inside the chosen lane's block
+        go = go && a0 > 0.0;
+        e += go ? 1u : 0u;
+        go = go && !(t + dt > tau);
+        t = go ? t + dt : t;
         int32_t j = -1;
-        if (go && lane == chosen) {
-            const double t2 = target - excl;
+        if constexpr (BR > 0) {
+            // the propensities of step 1, in the same order
+            const double t2 = target - (incl - part);
             double run_s = 0.0;
-            int32_t last = -1;
-            if constexpr (BR > 0) {
-                // the propensities of step 1, in the same order
+            bool found = false;
 #pragma unroll
-                for (int b = 0; b < NR; ++b)
-                    if (j < 0 && r_lo + b < r_hi && pr[b] > 0.0) {
-                        last = r_lo + b;
-                        run_s += pr[b];
-                        if (run_s > t2) j = r_lo + b;
-                    }
-            } else {
-                for (int32_t r = r_lo; r < r_hi; ++r) {
-                    const D d = tb.desc[r];
-                    const double ar = propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
-                    if (ar > 0.0) {
-                        last = r;
-                        run_s += ar;
-                        if (run_s > t2) {
-                            j = r;
-                            break;
-                        }
-                    }
+            for (int b = 0; b < NR; ++b) {
+                const bool on = !found && pr[b] > 0.0;
+                run_s = on ? run_s + pr[b] : run_s;
+                j = on ? r_lo + b : j;
+                found = found || (on && run_s > t2);
+            }
+        } else if (go && lane == chosen) {
+            const double t2 = target - (incl - part);
+            double run_s = 0.0;
+            for (int32_t r = r_lo; r < r_hi; ++r) {
+                const D d = tb.desc[r];
+                const double ar = propensity_from(d, (uint32_t)lx[d.s1], (uint32_t)lx[d.s2]);
+                if (ar > 0.0) {
+                    j = r;
+                    run_s += ar;
+                    if (run_s > t2) break;
                 }
             }
-            if (j < 0) j = last;
         }
         j = __shfl(j, chosen, 64);
         if (go && j < 0) {
