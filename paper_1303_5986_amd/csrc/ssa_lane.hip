@@ -338,6 +338,7 @@ hipError_t launch_ssa_lane(const SimArgs &a, int32_t *xs, hipStream_t st) {
     }
     if (a.S <= 1 && a.R <= 4) return launch_pool<1, 4>(a, xs, st);
     if (a.S <= 2 && a.R <= 8) return launch_pool<2, 8>(a, xs, st);
+    if (a.S <= 8 && a.R <= 8) return launch_pool<8, 8>(a, xs, st);
     if (a.S <= 8 && a.R <= 16) return launch_pool<8, 16>(a, xs, st);
     if (a.S <= 16 && a.R <= 32) return launch_fixed<16, 32>(a, xs, st);
     if (a.S <= 32 && a.R <= 64) return launch_fixed<32, 64>(a, xs, st);
@@ -352,6 +353,7 @@ const char *ssa_lane_name(const SimArgs &a) {
     if (a.hill) return a.S <= 2 && a.R <= 8 ? "ssa_lane_hill_kernel<2,8>" : "ssa_lane_hill_kernel<8,16>";
     if (a.S <= 1 && a.R <= 4) return "ssa_lane_pool_kernel<1,4>";
     if (a.S <= 2 && a.R <= 8) return "ssa_lane_pool_kernel<2,8>";
+    if (a.S <= 8 && a.R <= 8) return "ssa_lane_pool_kernel<8,8>";
     if (a.S <= 8 && a.R <= 16) return "ssa_lane_pool_kernel<8,16>";
     if (a.S <= 16 && a.R <= 32) return "ssa_lane_kernel<16,32>";
     return "ssa_lane_kernel<32,64>";
