@@ -86,8 +86,8 @@ struct PoolQueue {
 // its busiest walker's chain of events: with the branch-free event, one Schloegl
 // run of 80 bins x 32 walkers (1158 events at most) 719 -> 304 ns per event of
 // that walker, 32 such runs 783 -> 422 ns.
-template <int SMAX, int RMAX, bool HILL>
-__device__ __forceinline__ void lane_team(const SimArgs &a, const LaneNet<SMAX, RMAX, HILL> &net, LaneWalker &w,
+template <int SMAX, int RMAX, bool HILL, bool PAIR>
+__device__ __forceinline__ void lane_team(const SimArgs &a, const LaneNet<SMAX, RMAX, HILL, PAIR> &net, LaneWalker &w,
                                           int32_t (&x)[SMAX], int32_t *__restrict__ xs, int32_t *xr, size_t gslot,
                                           bool active, uint32_t iter, double tau) {
     const int lane = threadIdx.x & 63;
@@ -142,11 +142,11 @@ __device__ __forceinline__ void lane_team(const SimArgs &a, const LaneNet<SMAX, 
     }
 }
 
-template <int SMAX, int RMAX, bool HILL, bool LEAP>
+template <int SMAX, int RMAX, bool HILL, bool LEAP, bool PAIR>
 __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict__ xs, int32_t *wrows) {
     constexpr bool REG = RMAX <= LANE_REG_RMAX;
     if constexpr (!REG) lane_stage_rows<SMAX>(a, wrows);
-    LaneNet<SMAX, RMAX, HILL> net;
+    LaneNet<SMAX, RMAX, HILL, PAIR> net;
     net.load(a, wrows);
     uint32_t hor[LEAP ? SMAX : 1], hnu[LEAP ? SMAX : 1];
     if constexpr (LEAP) leap_orders(net, hor, hnu);
@@ -206,7 +206,7 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
             }
         } else {
             if (exhausted && nneed >= 32) {
-                lane_team<SMAX, RMAX, HILL>(a, net, w, x, xs, xr, gslot, active, iter, tau);
+                lane_team<SMAX, RMAX, HILL, PAIR>(a, net, w, x, xs, xr, gslot, active, iter, tau);
                 break;
             }
             if (active && !lane_event(net, w, x, tau, [&]() { return lane_draw(w.rs, w.e++); })) {
@@ -218,11 +218,12 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
 }
 
 // Five waves per SIMD for the smallest networks, whose registers allow it.
-template <int SMAX, int RMAX>
+// PAIR: reactions of at most two molecules (LanePair).
+template <int SMAX, int RMAX, bool PAIR>
 __global__ __launch_bounds__(256, SMAX == 1 ? 5 : 1) void ssa_lane_pool_kernel(SimArgs a, int32_t *__restrict__ xs) {
     constexpr int ROWS = RMAX <= LANE_REG_RMAX ? 1 : RMAX * LaneRow<SMAX>::W;
     __shared__ int32_t rows[4 * ROWS];
-    lane_pool<SMAX, RMAX, false, false>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
+    lane_pool<SMAX, RMAX, false, false, PAIR>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
 }
 
 // The same for networks with Hill-type rates (Sec. III.C).
@@ -230,7 +231,7 @@ template <int SMAX, int RMAX>
 __global__ __launch_bounds__(256) void ssa_lane_hill_kernel(SimArgs a, int32_t *__restrict__ xs) {
     constexpr int ROWS = RMAX <= LANE_REG_RMAX ? 1 : RMAX * LaneRow<SMAX>::W;
     __shared__ int32_t rows[4 * ROWS];
-    lane_pool<SMAX, RMAX, true, false>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
+    lane_pool<SMAX, RMAX, true, false, false>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
 }
 
 // The same with tau-leaping instead of the exact direct method.
@@ -238,7 +239,7 @@ template <int SMAX, int RMAX>
 __global__ __launch_bounds__(256) void ssa_lane_leap_kernel(SimArgs a, int32_t *__restrict__ xs) {
     constexpr int ROWS = RMAX <= LANE_REG_RMAX ? 1 : RMAX * LaneRow<SMAX>::W;
     __shared__ int32_t rows[4 * ROWS];
-    lane_pool<SMAX, RMAX, false, true>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
+    lane_pool<SMAX, RMAX, false, true, false>(a, xs, rows + (threadIdx.x >> 6) * ROWS);
 }
 
 // Fixed assignment, one walker per lane: used for the two largest variants,
@@ -262,13 +263,13 @@ __global__ __launch_bounds__(256) void ssa_lane_kernel(SimArgs a, int32_t *__res
 namespace {
 // Persistent grid: as many blocks as stay resident on the device, capped at
 // LANE_POOL_PER_CU per CU.
-template <int SMAX, int RMAX, int VARIANT>   // 0: exact, 1: Hill-type rates, 2: tau-leaping
+template <int SMAX, int RMAX, int VARIANT, bool PAIR>   // 0: exact, 1: Hill-type rates, 2: tau-leaping
 unsigned pool_blocks(const SimArgs &a) {
     static int per_cu = -1, n_cu = 0;   // one cache per kernel
     void (*kernel)(SimArgs, int32_t *);
     if constexpr (VARIANT == 1) kernel = ssa_lane_hill_kernel<SMAX, RMAX>;
     else if constexpr (VARIANT == 2) kernel = ssa_lane_leap_kernel<SMAX, RMAX>;
-    else kernel = ssa_lane_pool_kernel<SMAX, RMAX>;
+    else kernel = ssa_lane_pool_kernel<SMAX, RMAX, PAIR>;
     if (per_cu < 0) {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
@@ -300,22 +301,22 @@ hipError_t launch_fixed(const SimArgs &a, int32_t *xs, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int SMAX, int RMAX>
+template <int SMAX, int RMAX, bool PAIR = false>
 hipError_t launch_pool(const SimArgs &a, int32_t *xs, hipStream_t st) {
-    hipLaunchKernelGGL((ssa_lane_pool_kernel<SMAX, RMAX>), dim3(pool_blocks<SMAX, RMAX, 0>(a)),
+    hipLaunchKernelGGL((ssa_lane_pool_kernel<SMAX, RMAX, PAIR>), dim3(pool_blocks<SMAX, RMAX, 0, PAIR>(a)),
                        dim3(256), 0, st, a, xs);
     return hipGetLastError();
 }
 
 template <int SMAX, int RMAX>
 hipError_t launch_hill(const SimArgs &a, int32_t *xs, hipStream_t st) {
-    hipLaunchKernelGGL((ssa_lane_hill_kernel<SMAX, RMAX>), dim3(pool_blocks<SMAX, RMAX, 1>(a)),
+    hipLaunchKernelGGL((ssa_lane_hill_kernel<SMAX, RMAX>), dim3(pool_blocks<SMAX, RMAX, 1, false>(a)),
                        dim3(256), 0, st, a, xs);
     return hipGetLastError();
 }
 template <int SMAX, int RMAX>
 hipError_t launch_leap(const SimArgs &a, int32_t *xs, hipStream_t st) {
-    hipLaunchKernelGGL((ssa_lane_leap_kernel<SMAX, RMAX>), dim3(pool_blocks<SMAX, RMAX, 2>(a)),
+    hipLaunchKernelGGL((ssa_lane_leap_kernel<SMAX, RMAX>), dim3(pool_blocks<SMAX, RMAX, 2, false>(a)),
                        dim3(256), 0, st, a, xs);
     return hipGetLastError();
 }
@@ -338,7 +339,12 @@ hipError_t launch_ssa_lane(const SimArgs &a, int32_t *xs, hipStream_t st) {
     }
     if (a.S <= 1 && a.R <= 4) return launch_pool<1, 4>(a, xs, st);
     if (a.S <= 2 && a.R <= 8) return launch_pool<2, 8>(a, xs, st);
-    if (a.S <= 8 && a.R <= 8) return launch_pool<8, 8>(a, xs, st);
+    // Up to eight reactions: tables in scalar registers (10 futile-cycle runs of 101
+    // bins x 100 walkers, 6 species: <8,16> 61.4 us per interval, <8,8> 41.8), and
+    // where no reaction takes three molecules the pair form (26.5).  Networks of two
+    // species keep the general form: its branches cost them less than the picks (64
+    // switch runs of 465 bins x 16, Hill-type rates: 59 us, in pair form 66).
+    if (a.S <= 8 && a.R <= 8) return a.desc2 ? launch_pool<8, 8, true>(a, xs, st) : launch_pool<8, 8>(a, xs, st);
     if (a.S <= 8 && a.R <= 16) return launch_pool<8, 16>(a, xs, st);
     if (a.S <= 16 && a.R <= 32) return launch_fixed<16, 32>(a, xs, st);
     if (a.S <= 32 && a.R <= 64) return launch_fixed<32, 64>(a, xs, st);
