@@ -881,7 +881,7 @@ we_status read_back(we_sim *s, ReadPlan &p, int32_t *n_out = nullptr) {
 
 we_status we_read_err(we_sim *s) { return read_err(s); }
 
-// Everything after propagation: recycle and bin, resample and gather,
+// Everything after propagation: recycle and bin, resample, gather and
 // observables, the device iteration counter, records; flips the buffers.
 // ev (optional) points at three events: ev[0] already recorded after the
 // SSA step; ev[1] and ev[2] are recorded here.

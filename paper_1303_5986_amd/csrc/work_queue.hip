@@ -7,7 +7,7 @@
 // seen in their bin during the last interval, busiest first -- longest-
 // processing-time-first scheduling, so the long walkers start early and the
 // short ones fill the tail.  The propagation kernels then take walkers from the front
-// of the queue with one atomic per request.  The order is a scheduling hint
+// of the queue (the lane kernels' has several heads) with one atomic per request.  The order is a scheduling hint
 // only: every result depends on (seed, iteration, slot, event), never on
 // which lane or wave runs a walker.
 #include "we_common.h"
