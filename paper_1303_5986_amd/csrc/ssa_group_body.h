@@ -148,9 +148,9 @@ __device__ __forceinline__ GroupTables<D> group_stage(const SimArgs &a, const D 
 // every event, so the general form's two binomials per reaction were most of
 // an event's instructions.  The event is free of branches but for the draw and
 // the change, so that the waiting time's division runs beside the selection, and
-// a0 comes by row broadcasts, not through LDS.  Two waves per SIMD issue for most
-// of the time.  Toggle, 16 runs on 8 walkers per wave: 46.2 us per launch with
-// binomials, 42.4 with branches, 39.3.  BR > 0 (blocks of at most BR reactions): each
+// a0 comes by row broadcasts, not through LDS.  What bounds it is an event's chain
+// through LDS and the scan.  Toggle, 16 runs on 8 walkers per wave: 46.2 us per
+// launch with binomials, 42.4 with branches, 39.3, and 37.9 with no idle slots.  BR > 0 (blocks of at most BR reactions): each
 // lane keeps its block's descriptors in registers for the whole interval and
 // its block's propensities from step 1 for step 3, instead of reading the
 // descriptors again every event.
