@@ -60,7 +60,7 @@ __device__ __forceinline__ void wave_sort_desc(float &key, int32_t &idx, int lan
 // order.  What bounds it is the latency of its few phases: 465 bins, 64 runs
 // took 36 us, 60 bins, 2048 runs 16.8, 80 bins, 32 runs 17.7 and 100 bins, 10 runs
 // 16 us with a bitonic sort over the block (a barrier per step, one wave per bin
-// for the sums); this form takes 5.1, 8.5, 8.2 and 6.4 us.  The counters' layout
+// for the sums); this form takes 5.1, 8.5, 7.6 and 6.1 us.  The counters' layout
 // also took the runs' adds in resampling (2048 runs: 61 -> 55.5 us with them).
 #define QUEUE_MAX_BINS 8192
 #define QUEUE_SMALL_SEGS 4096
@@ -77,11 +77,15 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
     __shared__ int32_t part_n[1024], part_occ[1024];
     __shared__ uint32_t key_max;
     __shared__ int32_t wave_tot[16];
-    // SMALL only: per counter, segments / first position / fill cursor, and
-    // each (run, segment)'s bin (-1: no walkers)
+    // SMALL only: segments and next position per counter; per thread, up to
+    // PER (run, segment) pairs' walkers and counter (-1: none) and one counter's
+    // statistics, all fetched at once
     __shared__ int32_t s_occ[SMALL ? QUEUE_SMALL_BINS : 1];
     __shared__ int32_t s_off[SMALL ? QUEUE_SMALL_BINS : 1];
-    __shared__ int16_t s_bin[SMALL ? QUEUE_SMALL_SEGS : 1];
+    constexpr int PER = SMALL ? QUEUE_SMALL_SEGS / 1024 : 1;
+    int32_t sg_n[PER], sg_c[PER];
+    float my_ev = 0.0f;
+    int32_t my_nw = 0;
     const int32_t NB = a.n_bins, tid = threadIdx.x, nthr = blockDim.x;
     const int32_t rep = a.seg_rep, NC = NB * rep;
     const int lane = tid & 63, wv = tid >> 6;
@@ -89,18 +93,28 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
     step[tid] = 0;
     if (tid == 0) key_max = 0u;
     if constexpr (SMALL) {
-        if (tid < NC) s_occ[tid] = 0;
-        __syncthreads();
-        for (int32_t sg = tid; sg < n_seg; sg += nthr) {
-            const int32_t run = sg / NB, j = sg - run * NB;
-            const int64_t first = (int64_t)j * a.m_targ;
-            int32_t b = -1;
-            if (first < a.n_walk[run]) {
-                b = min(max(a.bin[(size_t)run * a.cap + first], 0), NB - 1);
-                atomicAdd(&s_occ[run % rep * NB + b], 1);
-            }
-            s_bin[sg] = (int16_t)b;
+        if (tid < NC) {
+            s_occ[tid] = 0;
+            my_ev = a.ev_bin[tid];
+            my_nw = a.n_bin[tid];
         }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int32_t sg = tid + u * nthr;
+            sg_n[u] = sg < n_seg ? a.n_walk[sg / NB] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int32_t sg = tid + u * nthr, run = sg / NB;
+            const int64_t first = (int64_t)(sg - run * NB) * a.m_targ;
+            sg_c[u] = -1;
+            if (first < sg_n[u])
+                sg_c[u] = run % rep * NB + min(max(a.bin[(size_t)run * a.cap + first], 0), NB - 1);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (sg_c[u] >= 0) atomicAdd(&s_occ[sg_c[u]], 1);
     }
     __syncthreads();
     auto occ = [&](int32_t c) { return SMALL ? s_occ[SMALL ? c : 0] : a.occ_bin[c]; };
@@ -111,11 +125,17 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
         const int32_t sub = i / NB, b = i - sub * NB;
         float ev = 0.0f;
         int32_t nw = 0, oc = 0;
+        if constexpr (SMALL) {   // NB * rep <= 1024: a thread per counter
+            ev = my_ev;
+            nw = my_nw;
+            oc = s_occ[i];
+        } else {
 #pragma unroll 8
-        for (int32_t r = sub; r < rep; r += G) {
-            ev += a.ev_bin[r * NB + b];
-            nw += a.n_bin[r * NB + b];
-            oc += occ(r * NB + b);
+            for (int32_t r = sub; r < rep; r += G) {
+                ev += a.ev_bin[r * NB + b];
+                nw += a.n_bin[r * NB + b];
+                oc += occ(r * NB + b);
+            }
         }
         if (G > 1) {
             part_ev[i] = ev;
@@ -196,14 +216,14 @@ __global__ __launch_bounds__(1024) void queue_order_kernel(SimArgs a) {
     if constexpr (SMALL) {
         __syncthreads();
         // the segment list, as queue_fill_kernel lays it out
-        for (int32_t sg = tid; sg < n_seg; sg += nthr) {
-            const int32_t b = s_bin[sg];
-            if (b < 0) continue;
-            const int32_t run = sg / NB, j = sg - run * NB;
-            const int32_t n = a.n_walk[run];
-            const int64_t first = (int64_t)j * a.m_targ;
-            const int32_t pos = atomicAdd(&s_off[run % rep * NB + b], 1);
-            a.seg[pos] = make_int2((int32_t)((size_t)run * a.cap + first), (int32_t)min((int64_t)a.m_targ, n - first));
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (sg_c[u] < 0) continue;
+            const int32_t sg = tid + u * nthr, run = sg / NB;
+            const int64_t first = (int64_t)(sg - run * NB) * a.m_targ;
+            const int32_t pos = atomicAdd(&s_off[sg_c[u]], 1);
+            a.seg[pos] =
+                make_int2((int32_t)((size_t)run * a.cap + first), (int32_t)min((int64_t)a.m_targ, sg_n[u] - first));
         }
     }
 }
