@@ -58,7 +58,14 @@ enum Variant {
 #define BATCH_GROUP_REG 8
 #define BATCH_GROUP_TABLES (48 * 1024)
 #define BATCH_WAVES 8                       // waves per workgroup of the wave variant, at most
-#define BATCH_LDS (160 * 1024)
+// Dynamic LDS of a workgroup, at most: a CU's 160 KB less next_chunk's word, which
+// takes a 16-byte unit (the dynamic part starts on 16 bytes).
+#define BATCH_LDS (160 * 1024 - 16)
+// Species of any member, at most.
+#define BATCH_MAX_SPECIES 3968
+// The largest wave-variant member (4096 descriptors and a wave's 64 chunk sums
+// and counts) leaves room for five waves.
+static_assert(16 * 4096 + 5 * (64 * 8 + 4 * (BATCH_MAX_SPECIES + 4)) <= BATCH_LDS, "wave variant");
 // Chunk counters per variant, on 128-byte lines of their own: one counter for
 // every walker tile bound the launches (an atomic on one address takes 11.4 ns).
 // Batch of 64 networks of 8 to 3680 reactions, by chunks with tables in LDS: wave
@@ -262,7 +269,6 @@ struct we_batch {
     size_t resample_shmem = 0;
     bool observe = false;
     int32_t iter = 0, max_iters = 0;
-    int32_t s_pad = 4;                // largest species count, padded
     hipGraphExec_t graph_exec = nullptr;
     hipStream_t capture_stream = nullptr;
     int32_t graph_iters = 0;
@@ -423,8 +429,8 @@ we_status build_chunks(we_batch *b) {
         const int32_t round = slots_per_round(v, b->wave_waves);
         int per_cu = 0;
         const void *fn = v < V_GROUP ? (const void *)lane_kernel_of(v) : (const void *)table_kernel_of(v);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, b->shmem[v]) != hipSuccess || per_cu < 1)
-            per_cu = 1;
+        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, b->shmem[v]));
+        if (per_cu < 1) return we_fail(WE_EINVAL, "a batched propagation kernel's workgroup does not fit a CU");
         double total = 0.0;
         for (int32_t i : of) total += walker_cost(v, b->sims[i]) * b->sims[i]->n_runs * b->sims[i]->cap;
         const double aim = total / ((double)BATCH_CHUNKS * per_cu * cus);
@@ -528,6 +534,7 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
     b->stream = (hipStream_t)hip_stream;
     std::map<std::string, int> cache = read_cache(cache_path);
     bool cache_dirty = false;
+    int32_t s_most = 0;
     for (int32_t i = 0; i < n; ++i) {
         we_params p = params[i];
         if (p.rw_period > 0) {
@@ -584,11 +591,11 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         if (r != WE_OK) { we_batch_destroy(b); return r; }
         b->sims.push_back(s);
         b->var.push_back(variant_of(s));
-        b->s_pad = std::max(b->s_pad, (S + 3) & ~3);
+        s_most = std::max(s_most, S);
         b->max_iters = (i == 0) ? s->max_iters : std::min(b->max_iters, s->max_iters);
     }
     if (cache_dirty) write_cache(cache_path, cache);
-    if (4 * (64 * sizeof(double) + 4 * (size_t)b->s_pad) > 64 * 1024) {
+    if (s_most > BATCH_MAX_SPECIES) {
         we_batch_destroy(b);
         return we_fail(WE_EINVAL, "species count too large for the batched wave kernel");
     }
