@@ -57,6 +57,10 @@
 // Cursor rows for placing walkers in parallel: one row of n_bins per wave, as
 // long as the rows hold at most this many counters.
 #define RESAMPLE_PLACE_INTS 8192   // 16 rows of 512 bins
+// With more bins than this (up to 8192) the tables, 20 bytes a bin beside the 8 KB
+// of event totals, would pass a CU's 160 KB (from 7782 bins on).  The events per bin
+// then lie where the output offsets are written once they are read; 16 bytes a bin.
+#define RESAMPLE_EVB_BINS 7600
 // Bin-parallel resampling: runs fewer than this, bins at least this many.
 #define RESAMPLE_BIN_PARALLEL_RUNS 256
 #define RESAMPLE_BIN_PARALLEL_BINS 32
@@ -1222,8 +1226,10 @@ __device__ void resample_run_t(const SimArgs &a, int32_t *__restrict__ x_cur, co
     // the walkers of those chunks, then holds where the next one goes
     const int32_t P = max(1, min(n_waves, a.place_rows));
     int32_t *cursor = ostart + NB + 1;                  // [a.place_rows][NB]
-    float *evb = reinterpret_cast<float *>(cursor + (size_t)max(1, a.place_rows) * NB); // [NB] events per bin
-    unsigned char *tail = reinterpret_cast<unsigned char *>(evb + NB);
+    int32_t *after = cursor + (size_t)max(1, a.place_rows) * NB;
+    const bool evb_shared = !LDS && NB > RESAMPLE_EVB_BINS;
+    float *evb = reinterpret_cast<float *>(evb_shared ? ostart : after);   // [NB] events per bin
+    unsigned char *tail = reinterpret_cast<unsigned char *>(after + NB);    // LDS: the working arrays
     tail += (16 - ((uintptr_t)tail & 15)) & 15;
 
     const uint32_t iter = *a.iter_dev;
@@ -1307,6 +1313,7 @@ __device__ void resample_run_t(const SimArgs &a, int32_t *__restrict__ x_cur, co
                 atomicAdd(&a.ev_bin[c], evb[b]);
                 atomicAdd(&a.n_bin[c], cnt[b]);
             }
+    if (evb_shared) __syncthreads();
 
     // wave 0: bin offsets (walkers ordered by bin, then slot)
     if (wave == 0) {
@@ -1716,7 +1723,8 @@ hipError_t launch_recycle_bin(const SimArgs &a, int32_t *x_cur, bool grid_bins, 
 
 bool resample_uses_lds(const SimArgs &a);
 static size_t lds_bytes_rows(const SimArgs &a, bool use_lds, int32_t rows) {
-    size_t b = sizeof(int32_t) * ((4 + (size_t)rows) * a.n_bins + 2) + 16;
+    const size_t tables = !use_lds && a.n_bins > RESAMPLE_EVB_BINS ? 3 : 4;
+    size_t b = sizeof(int32_t) * ((tables + rows) * a.n_bins + 2) + 16;
     if (use_lds) b += (size_t)a.cap * (sizeof(double) + sizeof(int32_t) + 2 * sizeof(uint16_t));
     return b;
 }
