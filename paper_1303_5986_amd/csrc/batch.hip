@@ -239,11 +239,16 @@ struct BatchPtrs {
     int32_t *const *binfo;
     const int32_t *grid_bins;
 };
+struct BatchBins {
+    int64_t *first;
+    int64_t total;
+    int32_t max_blocks;
+};
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
-                                    int64_t max_cells, int32_t max_bins, uint32_t m_sizes, size_t shmem, bool observe,
+                                    int64_t max_cells, const BatchBins *bins, size_t shmem, bool observe,
                                     const CmBatchModel *models,
                                     int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st);
-uint32_t resample_m_size(int32_t m);
+int32_t batch_bins_blocks(const SimArgs &a, int variant);
 size_t resample_lds_bytes(const SimArgs &a, bool use_lds);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
 
@@ -264,8 +269,8 @@ struct we_batch {
     int32_t **d_binfo = nullptr;
     int32_t *d_grid_bins = nullptr;
     int64_t max_slots = 0, max_cells = 0;
-    int32_t max_runs = 0, max_bins = 0;
-    uint32_t m_sizes = 0;
+    int32_t max_runs = 0;
+    BatchBins bins[2] = {};           // split/merge: targets up to 128, and above
     size_t resample_shmem = 0;
     bool observe = false;
     int32_t iter = 0, max_iters = 0;
@@ -509,7 +514,7 @@ we_status launch_batch_iteration(we_batch *b, hipStream_t st, bool capture) {
                  (const double *const *)b->d_wptr[parity], b->d_wptr[1 - parity], b->d_binfo,
                  b->d_grid_bins};
     HIP_TRY(launch_batch_bookkeeping(bp, (int32_t)b->sims.size(), b->max_slots, b->max_runs, b->max_cells,
-                                     b->max_bins, b->m_sizes, b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
+                                     b->bins, b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
                                      b->s_max_cm, b->d_counters, V_COUNT * BATCH_HEADS, st));
     for (we_sim *s : b->sims) s->cur = 1 - s->cur;
     if (!capture)
@@ -618,12 +623,22 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         binfo.push_back(s->rs_binfo);
         grid_bins.push_back(1);
         b->resample_shmem = std::max(b->resample_shmem, resample_lds_bytes(args.back(), false));
-        b->max_bins = std::max(b->max_bins, s->NB);
-        b->m_sizes |= resample_m_size(s->M);
         b->max_slots = std::max<int64_t>(b->max_slots, (int64_t)s->n_runs * s->cap);
         b->max_cells = std::max<int64_t>(b->max_cells, (int64_t)s->n_runs * s->cap * s->S);
         b->max_runs = std::max(b->max_runs, s->n_runs);
         b->observe = b->observe || s->args.nh > 0 || s->args.n_joint > 0;
+    }
+    for (int v = 0; v < 2; ++v) {
+        BatchBins &bb = b->bins[v];
+        std::vector<int64_t> first(1, 0);
+        for (we_sim *s : b->sims) {
+            const int32_t blocks = batch_bins_blocks(s->args, v);
+            first.push_back(first.back() + (int64_t)s->n_runs * blocks);
+            bb.max_blocks = std::max(bb.max_blocks, blocks);
+        }
+        bb.total = first.back();
+        HIP_TRY(hipMalloc(&bb.first, sizeof(int64_t) * first.size()));
+        HIP_TRY(hipMemcpy(bb.first, first.data(), sizeof(int64_t) * first.size(), hipMemcpyHostToDevice));
     }
     HIP_TRY(hipMalloc(&b->d_wptr[0], sizeof(double *) * n));
     HIP_TRY(hipMalloc(&b->d_wptr[1], sizeof(double *) * n));
@@ -744,6 +759,7 @@ extern "C" void we_batch_destroy(we_batch *b) {
     (void)hipFree(b->d_wptr[0]);
     (void)hipFree(b->d_wptr[1]);
     (void)hipFree(b->d_binfo);
+    for (BatchBins &bb : b->bins) (void)hipFree(bb.first);
     (void)hipFree(b->d_grid_bins);
     (void)hipFree(b->d_models);
     if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);

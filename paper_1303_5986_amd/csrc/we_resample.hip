@@ -1527,6 +1527,12 @@ struct BinsBlock {
     static constexpr size_t LDS = WAVES * merge_lds_bytes<CAP>();
 };
 
+// Workgroups per run.
+template <int CAP>
+__host__ __device__ constexpr int32_t bins_blocks(int32_t n_bins) {
+    return (n_bins + BinsBlock<CAP>::WAVES - 1) / BinsBlock<CAP>::WAVES;
+}
+
 template <int RULE, int CAP>
 __global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_resample_bins_kernel(SimArgs a, double *__restrict__ w_nxt,
                                                                                     const int32_t *__restrict__ binfo) {
@@ -1538,9 +1544,8 @@ __global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_resample_bins_k
 
 template <int RULE, int CAP>
 void launch_bins(const SimArgs &a, double *w_nxt, const int32_t *binfo, hipStream_t st) {
-    constexpr int W = BinsBlock<CAP>::WAVES;
-    hipLaunchKernelGGL((we_resample_bins_kernel<RULE, CAP>), dim3((unsigned)((a.n_bins + W - 1) / W), (unsigned)a.n_runs),
-                       dim3(64 * W), BinsBlock<CAP>::LDS, st, a, w_nxt, binfo);
+    hipLaunchKernelGGL((we_resample_bins_kernel<RULE, CAP>), dim3((unsigned)bins_blocks<CAP>(a.n_bins), (unsigned)a.n_runs),
+                       dim3(64 * BinsBlock<CAP>::WAVES), BinsBlock<CAP>::LDS, st, a, w_nxt, binfo);
 }
 
 // New state rows from their parents: one lane per copy number.
@@ -1626,6 +1631,14 @@ struct BatchPtrs {
     const int32_t *grid_bins;
 };
 
+// The members' workgroups on one variant of the split/merge: each member's first
+// one and their number, and the most blocks of bins that a member has.
+struct BatchBins {
+    int64_t *first;    // device, [members + 1]
+    int64_t total;
+    int32_t max_blocks;
+};
+
 __global__ __launch_bounds__(256) void we_batch_recycle_bin_kernel(BatchPtrs b) {
     const int32_t i = blockIdx.y;
     recycle_bin_one(b.args[i], b.x_cur[i], b.grid_bins[i], (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
@@ -1643,15 +1656,38 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_batch_place_kernel(BatchP
     resample_run_t<int32_t, false, 0, true>(a, nullptr, b.w_cur[i], b.w_nxt[i], blockIdx.x, lds, b.binfo[i]);
 }
 
-template <int CAP>
-__global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_batch_bins_kernel(BatchPtrs b) {
+// The members' split/merge, runs side by side: workgroups go to the XCDs in turn, and
+// the busy bins of every run are the same few.  EVEN: grid (runs, blocks of bins,
+// members), sized for the largest of each.  Else as many workgroups as the members
+// on this variant have, which find their member by bisecting the members' first
+// workgroups (first[n_sims]: their number).
+template <int CAP, bool EVEN>
+__global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_batch_bins_kernel(BatchPtrs b,
+                                                                                  const int64_t *__restrict__ first,
+                                                                                  int32_t n_sims) {
     extern __shared__ __align__(16) unsigned char mlds[];
-    const int32_t i = blockIdx.z;
-    const SimArgs &a = b.args[i];
-    if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != (CAP >= MERGE_ROUNDS_MAX)) return;
     const int32_t wave = (int32_t)(threadIdx.x >> 6);
-    resample_bins_wave<-1, CAP>(a, b.w_nxt[i], b.binfo[i], blockIdx.x, (int32_t)blockIdx.y * BinsBlock<CAP>::WAVES + wave,
-                                mlds + wave * merge_lds_bytes<CAP>());
+    unsigned char *wlds = mlds + wave * merge_lds_bytes<CAP>();
+    if constexpr (EVEN) {
+        const int32_t i = blockIdx.z;
+        const SimArgs &a = b.args[i];
+        if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != (CAP >= MERGE_ROUNDS_MAX)) return;
+        resample_bins_wave<-1, CAP>(a, b.w_nxt[i], b.binfo[i], blockIdx.x,
+                                    (int32_t)blockIdx.y * BinsBlock<CAP>::WAVES + wave, wlds);
+    } else {
+        for (int64_t g = blockIdx.x; g < first[n_sims]; g += gridDim.x) {
+            int32_t i = 0, end = n_sims;
+            while (end - i > 1) {
+                const int32_t mid = (i + end) >> 1;
+                if (first[mid] <= g) i = mid;
+                else end = mid;
+            }
+            const SimArgs &a = b.args[i];
+            const int32_t at = (int32_t)(g - first[i]), block = at / a.n_runs;
+            resample_bins_wave<-1, CAP>(a, b.w_nxt[i], b.binfo[i], at - block * a.n_runs,
+                                        block * BinsBlock<CAP>::WAVES + wave, wlds);
+        }
+    }
 }
 
 // Grid-strided over each member's own cells: a grid sized for the largest
@@ -1684,12 +1720,35 @@ __global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n, uint32_t *__rest
 // cells): 64 members then give 32768 workgroups, 128 per CU.
 #define BATCH_GATHER_BLOCKS 512
 
-// m_sizes: bit 0, some member has at most RESAMPLE_BIG_M walkers per bin; bit
-// 1, some member has more.
-uint32_t resample_m_size(int32_t m) { return m > RESAMPLE_BIG_M ? 2u : 1u; }
+// A member's workgroups per run on the batched split/merge's variant for at most
+// RESAMPLE_BIG_M walkers per bin (variant 0), or for more (1).
+int32_t batch_bins_blocks(const SimArgs &a, int variant) {
+    if ((a.m_targ > RESAMPLE_BIG_M) != (variant == 1)) return 0;
+    return variant == 1 ? bins_blocks<MERGE_ROUNDS_MAX>(a.n_bins) : bins_blocks<256>(a.n_bins);
+}
+
+// An empty workgroup takes 0.21 ns of a launch, finding the member about 1.1 ns per
+// workgroup: the even grid where at most five in six are empty, or all are few.
+// Two members of 2048 Schloegl runs 1.67 ms per step on the even grid and 1.74
+// on the other, 512 runs of 16 bins with one of 4000 bins and 30 small members 3.50 and
+// 0.070 ms.
+#define BATCH_BINS_FEW 8192
+#define BATCH_BINS_BLOCKS (1 << 20)   // workgroups stride from here on
+template <int CAP>
+void launch_batch_bins(const BatchPtrs &b, const BatchBins &n, int32_t n_sims, int32_t max_runs, hipStream_t st) {
+    if (n.total == 0) return;
+    const int64_t even = (int64_t)max_runs * n.max_blocks * n_sims;
+    const dim3 block(64 * BinsBlock<CAP>::WAVES);
+    if (even <= std::max<int64_t>(6 * n.total, BATCH_BINS_FEW))
+        hipLaunchKernelGGL((we_batch_bins_kernel<CAP, true>), dim3(max_runs, n.max_blocks, n_sims), block,
+                           BinsBlock<CAP>::LDS, st, b, n.first, n_sims);
+    else
+        hipLaunchKernelGGL((we_batch_bins_kernel<CAP, false>), dim3((unsigned)std::min<int64_t>(n.total, BATCH_BINS_BLOCKS)),
+                           block, BinsBlock<CAP>::LDS, st, b, n.first, n_sims);
+}
 
 hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t max_slots, int32_t max_runs,
-                                    int64_t max_cells, int32_t max_bins, uint32_t m_sizes, size_t shmem, bool observe,
+                                    int64_t max_cells, const BatchBins *bins, size_t shmem, bool observe,
                                     const CmBatchModel *models,
                                     int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st) {
     const unsigned gs = (unsigned)((max_slots + 255) / 256);
@@ -1700,12 +1759,8 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
     }
     hipLaunchKernelGGL(we_batch_place_kernel, dim3(max_runs, n_sims),
                        dim3(resample_threads((int64_t)max_runs * n_sims)), shmem, st, b);
-    if (m_sizes & 2u)
-        hipLaunchKernelGGL(we_batch_bins_kernel<MERGE_ROUNDS_MAX>, dim3(max_runs, max_bins, n_sims), dim3(64),
-                           BinsBlock<MERGE_ROUNDS_MAX>::LDS, st, b);
-    if (m_sizes & 1u)
-        hipLaunchKernelGGL(we_batch_bins_kernel<256>, dim3(max_runs, (max_bins + 3) / 4, n_sims), dim3(256),
-                           BinsBlock<256>::LDS, st, b);
+    launch_batch_bins<MERGE_ROUNDS_MAX>(b, bins[1], n_sims, max_runs, st);
+    launch_batch_bins<256>(b, bins[0], n_sims, max_runs, st);
     const unsigned gg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_cells + 255) / 256, BATCH_GATHER_BLOCKS));
     hipLaunchKernelGGL(we_batch_gather_kernel, dim3(gg, n_sims), dim3(256), 0, st, b);
     if (observe) hipLaunchKernelGGL(we_batch_observe_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
