@@ -238,6 +238,7 @@ struct BatchPtrs {
     double *const *w_nxt;
     int32_t *const *binfo;
     const int32_t *grid_bins;
+    const int32_t *bins_cap;
 };
 struct BatchBins {
     int64_t *first;
@@ -248,7 +249,9 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
                                     int64_t max_cells, const BatchBins *bins, size_t shmem, bool observe,
                                     const CmBatchModel *models,
                                     int32_t s_max_cm, uint32_t *counters, int32_t n_counters, hipStream_t st);
-int32_t batch_bins_blocks(const SimArgs &a, int variant);
+int32_t batch_bins_cap(const SimArgs &a, int64_t waves);
+int64_t batch_big_waves(const SimArgs &a);
+int32_t batch_bins_blocks(const SimArgs &a, int64_t waves, int variant);
 size_t resample_lds_bytes(const SimArgs &a, bool use_lds);
 int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
 
@@ -270,7 +273,8 @@ struct we_batch {
     int32_t *d_grid_bins = nullptr;
     int64_t max_slots = 0, max_cells = 0;
     int32_t max_runs = 0;
-    BatchBins bins[2] = {};           // split/merge: targets up to 128, and above
+    BatchBins bins[BATCH_BINS] = {};   // split/merge, by variant
+    int32_t *d_bins_cap = nullptr;     // each member's
     size_t resample_shmem = 0;
     bool observe = false;
     int32_t iter = 0, max_iters = 0;
@@ -512,7 +516,7 @@ we_status launch_batch_iteration(we_batch *b, hipStream_t st, bool capture) {
     // advance: one launch per step for all members
     BatchPtrs bp{b->d_args, b->d_xptr[parity], b->d_xptr[1 - parity],
                  (const double *const *)b->d_wptr[parity], b->d_wptr[1 - parity], b->d_binfo,
-                 b->d_grid_bins};
+                 b->d_grid_bins, b->d_bins_cap};
     HIP_TRY(launch_batch_bookkeeping(bp, (int32_t)b->sims.size(), b->max_slots, b->max_runs, b->max_cells,
                                      b->bins, b->resample_shmem, b->observe, b->any_cm ? b->d_models : nullptr,
                                      b->s_max_cm, b->d_counters, V_COUNT * BATCH_HEADS, st));
@@ -628,11 +632,17 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         b->max_runs = std::max(b->max_runs, s->n_runs);
         b->observe = b->observe || s->args.nh > 0 || s->args.n_joint > 0;
     }
-    for (int v = 0; v < 2; ++v) {
+    int64_t big_waves = 0;
+    for (we_sim *s : b->sims) big_waves += batch_big_waves(s->args);
+    std::vector<int32_t> caps;
+    for (we_sim *s : b->sims) caps.push_back(batch_bins_cap(s->args, big_waves));
+    HIP_TRY(hipMalloc(&b->d_bins_cap, sizeof(int32_t) * n));
+    HIP_TRY(hipMemcpy(b->d_bins_cap, caps.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice));
+    for (int v = 0; v < BATCH_BINS; ++v) {
         BatchBins &bb = b->bins[v];
         std::vector<int64_t> first(1, 0);
         for (we_sim *s : b->sims) {
-            const int32_t blocks = batch_bins_blocks(s->args, v);
+            const int32_t blocks = batch_bins_blocks(s->args, big_waves, v);
             first.push_back(first.back() + (int64_t)s->n_runs * blocks);
             bb.max_blocks = std::max(bb.max_blocks, blocks);
         }
@@ -760,6 +770,7 @@ extern "C" void we_batch_destroy(we_batch *b) {
     (void)hipFree(b->d_wptr[1]);
     (void)hipFree(b->d_binfo);
     for (BatchBins &bb : b->bins) (void)hipFree(bb.first);
+    (void)hipFree(b->d_bins_cap);
     (void)hipFree(b->d_grid_bins);
     (void)hipFree(b->d_models);
     if (b->graph_exec) (void)hipGraphExecDestroy(b->graph_exec);

@@ -136,6 +136,9 @@ const char *ssa_lane_name(const SimArgs &a);
 const char *ssa_wave_name(const SimArgs &a);
 hipError_t launch_ssa_group(const SimArgs &a, int32_t *xs, int32_t lanes, hipStream_t st);
 const char *ssa_group_name(const SimArgs &a, int32_t lanes);
+// we_resample.hip: variants of the batched split/merge
+#define BATCH_BINS 4
+
 // reweight.hip
 #define WE_RW_MAX_BINS 512
 bool rw_solve_in_lds(int32_t n_bins);

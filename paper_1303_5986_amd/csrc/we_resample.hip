@@ -966,7 +966,7 @@ __device__ __forceinline__ int32_t merge_rounds(double *W, int32_t nb, int32_t M
     // AHEAD pairs of a lane are read before the first is written: the largest bins
     // of a 64-network batch (700 walkers) 123 -> 111 us, ten futile-cycle runs of
     // 101 bins x 100 38 -> 35.6.  A wave alone on its SIMD, it is bound by issue now.
-    constexpr int AHEAD = CAP >= MERGE_ROUNDS_MAX ? 8 : 2;
+    constexpr int AHEAD = CAP >= 1024 ? 8 : CAP >= 512 ? 4 : 2;
     int32_t P = 1;
     while (P < nb) P <<= 1;
     for (int32_t size = 2; size <= P; size <<= 1)
@@ -1145,21 +1145,21 @@ __device__ __forceinline__ void equalize_bin_rounds(const RunWork<int32_t> &wk, 
 // One bin's split/merge (and its row of the reweighting flux matrix) on the
 // calling wave: the walkers at positions [p0, p0 + nb) of wk, the output at
 // slots [o0, o0 + M).  RULE: the sim's rs_rule (-1: read from a).  CAP: walkers
-// the wave's LDS lds holds for merges in rounds.  With MERGE_ROUNDS_MAX the bins
-// to split or equalize in registers reach 512 walkers, eight per lane (more than
-// a 1024-thread workgroup has room for; else 128 and 256).
+// the wave's LDS lds holds for merges in rounds (bins_cap).  With 512 or more the
+// bins to split or equalize in registers reach 512 walkers, eight per lane (more
+// than a 1024-thread workgroup has room for; else 128 and 256).
 template <class Idx, int RULE, int CAP>
 __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const BinOut &out, int32_t run, int32_t b,
                              int32_t nb, int32_t p0, int32_t o0, uint32_t iter, uint32_t k0, uint32_t k1,
                              bool rw_acc, int lane, unsigned char *lds = nullptr) {
-    constexpr bool BIG = CAP >= MERGE_ROUNDS_MAX;
+    constexpr bool BIG = CAP >= 512;
     const int32_t NB = a.n_bins, M = a.m_targ;
     if (rw_acc) rw_flux_bin(a.rw_F + ((size_t)run * NB + b) * NB, wk, p0, nb, NB > 1 ? 32 - __clz(NB - 1) : 0, lane);
     if (RULE < 0 ? a.rs_rule == 1 : RULE == 1) {
         if (nb <= 64) equalize_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if constexpr (CAP > 0) {
-            if (CAP >= 128 && nb <= 128) equalize_bin_rounds<2, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
-            else if (CAP >= 256 && nb <= 256) equalize_bin_rounds<4, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
+            if (nb <= 128) equalize_bin_rounds<2, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
+            else if (nb <= 256) equalize_bin_rounds<4, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
             else if (BIG && nb <= 512) equalize_bin_rounds<8, CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
             else merge_bin<Idx, true>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         }
@@ -1182,7 +1182,7 @@ __device__ void resample_bin(const SimArgs &a, const RunWork<Idx> &wk, const Bin
         if (nb <= 64) merge_bin_lanes<1>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 128) merge_bin_lanes<2>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
         else if (nb <= 256) merge_bin_lanes<4>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
-        else if (BIG && nb <= MERGE_ROUNDS_MAX) {
+        else if (BIG && nb <= CAP) {
             if constexpr (BIG) merge_bin_rounds<CAP>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lds, lane);
         }
         else merge_bin<Idx, false>(wk, p0, nb, M, b, o0, out, iter, k0, k1, lane);
@@ -1520,10 +1520,10 @@ __device__ __forceinline__ void resample_bins_wave(const SimArgs &a, double *__r
                                      (uint32_t)(seed >> 32), a.rw_F != nullptr && iter >= 1u, lane, mlds);
 }
 
-// Waves (bins) per workgroup.
+// Waves (bins) per workgroup: one where its LDS alone would keep others off the CU.
 template <int CAP>
 struct BinsBlock {
-    static constexpr int WAVES = CAP >= MERGE_ROUNDS_MAX ? 1 : 4;
+    static constexpr int WAVES = CAP >= 1024 ? 1 : 4;
     static constexpr size_t LDS = WAVES * merge_lds_bytes<CAP>();
 };
 
@@ -1629,6 +1629,7 @@ struct BatchPtrs {
     double *const *w_nxt;
     int32_t *const *binfo;
     const int32_t *grid_bins;
+    const int32_t *bins_cap;
 };
 
 // The members' workgroups on one variant of the split/merge: each member's first
@@ -1671,7 +1672,7 @@ __global__ __launch_bounds__(64 * BinsBlock<CAP>::WAVES) void we_batch_bins_kern
     if constexpr (EVEN) {
         const int32_t i = blockIdx.z;
         const SimArgs &a = b.args[i];
-        if ((int32_t)blockIdx.x >= a.n_runs || (a.m_targ > RESAMPLE_BIG_M) != (CAP >= MERGE_ROUNDS_MAX)) return;
+        if ((int32_t)blockIdx.x >= a.n_runs || b.bins_cap[i] != CAP) return;
         resample_bins_wave<-1, CAP>(a, b.w_nxt[i], b.binfo[i], blockIdx.x,
                                     (int32_t)blockIdx.y * BinsBlock<CAP>::WAVES + wave, wlds);
     } else {
@@ -1720,11 +1721,38 @@ __global__ void we_batch_advance_kernel(BatchPtrs b, int32_t n, uint32_t *__rest
 // cells): 64 members then give 32768 workgroups, 128 per CU.
 #define BATCH_GATHER_BLOCKS 512
 
-// A member's workgroups per run on the batched split/merge's variant for at most
-// RESAMPLE_BIG_M walkers per bin (variant 0), or for more (1).
-int32_t batch_bins_blocks(const SimArgs &a, int variant) {
-    if ((a.m_targ > RESAMPLE_BIG_M) != (variant == 1)) return 0;
-    return variant == 1 ? bins_blocks<MERGE_ROUNDS_MAX>(a.n_bins) : bins_blocks<256>(a.n_bins);
+// The walkers a bin may have for its merges to go in rounds, by the wave's LDS (20
+// bytes each; 0: none).  Targets of at most 128 leave few bins past 256.  Above,
+// room for 2048 pays as long as the waves are few: it leaves three to a CU, and
+// with more waves than that the bins wait for one another, so the room is then what
+// the target's bins need, and none where they are past the rounds (512 for the
+// weight-equalizing rule) or so large that the serial merges of more waves win.
+// us per interval without rounds / with 512, 1024, 2048 walkers' room, tau-leaping
+// runs in steady state: 8 runs of 64 bins x 256 228 / 139, 153, 154; 128 such runs
+// 782 / 618, 763, 1056, equalizing 1382 / 667, 842, 1224; 128 runs of 32 bins x 512
+// 829 / 973, 706, 905, equalizing 1710 / 2402, 2917, 4813; 64 runs of 32 bins x
+// 1000 1331 / 1336, 1792, 2427.
+#define BINS_FEW_WAVES 512
+static int32_t bins_cap(const SimArgs &a, int64_t waves) {
+    const bool eq = a.rs_rule == 1;
+    if (a.m_targ > RESAMPLE_BIG_M) {
+        if (waves <= BINS_FEW_WAVES) return MERGE_ROUNDS_MAX;
+        if (a.m_targ <= 384) return 512;
+        if (!eq && a.m_targ <= 768) return 1024;
+    }
+    return eq ? 256 : 0;
+}
+
+// The batched split/merge's variants.
+static constexpr int BATCH_CAPS[BATCH_BINS] = {256, 512, 1024, MERGE_ROUNDS_MAX};
+
+// Member a's variant, and its workgroups per run; waves: batch_big_waves over the members.
+int32_t batch_bins_cap(const SimArgs &a, int64_t waves) { return std::max(bins_cap(a, waves), BATCH_CAPS[0]); }
+int64_t batch_big_waves(const SimArgs &a) { return a.m_targ > RESAMPLE_BIG_M ? (int64_t)a.n_runs * a.n_bins : 0; }
+int32_t batch_bins_blocks(const SimArgs &a, int64_t waves, int variant) {
+    if (batch_bins_cap(a, waves) != BATCH_CAPS[variant]) return 0;
+    return variant == 0 ? bins_blocks<BATCH_CAPS[0]>(a.n_bins) : variant == 1 ? bins_blocks<BATCH_CAPS[1]>(a.n_bins)
+           : variant == 2 ? bins_blocks<BATCH_CAPS[2]>(a.n_bins) : bins_blocks<BATCH_CAPS[3]>(a.n_bins);
 }
 
 // An empty workgroup takes 0.21 ns of a launch, finding the member about 1.1 ns per
@@ -1759,8 +1787,10 @@ hipError_t launch_batch_bookkeeping(const BatchPtrs &b, int32_t n_sims, int64_t 
     }
     hipLaunchKernelGGL(we_batch_place_kernel, dim3(max_runs, n_sims),
                        dim3(resample_threads((int64_t)max_runs * n_sims)), shmem, st, b);
-    launch_batch_bins<MERGE_ROUNDS_MAX>(b, bins[1], n_sims, max_runs, st);
-    launch_batch_bins<256>(b, bins[0], n_sims, max_runs, st);
+    launch_batch_bins<BATCH_CAPS[3]>(b, bins[3], n_sims, max_runs, st);
+    launch_batch_bins<BATCH_CAPS[2]>(b, bins[2], n_sims, max_runs, st);
+    launch_batch_bins<BATCH_CAPS[1]>(b, bins[1], n_sims, max_runs, st);
+    launch_batch_bins<BATCH_CAPS[0]>(b, bins[0], n_sims, max_runs, st);
     const unsigned gg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((max_cells + 255) / 256, BATCH_GATHER_BLOCKS));
     hipLaunchKernelGGL(we_batch_gather_kernel, dim3(gg, n_sims), dim3(256), 0, st, b);
     if (observe) hipLaunchKernelGGL(we_batch_observe_kernel, dim3(gs, n_sims), dim3(256), 0, st, b);
@@ -1837,13 +1867,19 @@ hipError_t launch_resample(const SimArgs &a, int32_t *x_cur, const double *w_cur
     if (split) {
         // the placement takes no rule
         hipLaunchKernelGGL((we_resample_kernel<RS_PLACE, 0>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, binfo);
-        // targets of at most 128 walkers leave few bins past 256, and the
-        // larger register files would cost the small bins occupancy
-        const bool big = a.m_targ > RESAMPLE_BIG_M;
-        if (eq && big) launch_bins<1, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
-        else if (eq) launch_bins<1, 256>(a, w_nxt, binfo, st);
-        else if (big) launch_bins<0, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
-        else launch_bins<0, 0>(a, w_nxt, binfo, st);
+        switch (bins_cap(a, (int64_t)a.n_runs * a.n_bins)) {
+        case MERGE_ROUNDS_MAX:
+            if (eq) launch_bins<1, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
+            else launch_bins<0, MERGE_ROUNDS_MAX>(a, w_nxt, binfo, st);
+            break;
+        case 1024: launch_bins<0, 1024>(a, w_nxt, binfo, st); break;
+        case 512:
+            if (eq) launch_bins<1, 512>(a, w_nxt, binfo, st);
+            else launch_bins<0, 512>(a, w_nxt, binfo, st);
+            break;
+        case 256: launch_bins<1, 256>(a, w_nxt, binfo, st); break;
+        default: launch_bins<0, 0>(a, w_nxt, binfo, st);
+        }
     } else if (use_lds) {
         if (eq) hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 1>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
         else hipLaunchKernelGGL((we_resample_kernel<RS_LDS, 0>), gr, br, shmem, st, a, x_cur, w_cur, w_nxt, nullptr);
