@@ -257,6 +257,7 @@ int32_t resample_place_rows(const SimArgs &a, int64_t blocks);
 
 struct we_batch {
     hipStream_t stream = nullptr;
+    ReadStage stage;
     std::vector<we_sim *> sims;
     std::vector<Variant> var;
     // per variant: its chunks, dynamic LDS bytes (tables in front) and workgroups
@@ -598,6 +599,7 @@ extern "C" we_status we_batch_create(int32_t n, const we_network *const *nets, c
         we_sim *s = nullptr;
         we_status r = we_init(nets[i], &grids[i], &p, b->stream, nullptr, 0, &s);
         if (r != WE_OK) { we_batch_destroy(b); return r; }
+        s->stage = &b->stage;
         b->sims.push_back(s);
         b->var.push_back(variant_of(s));
         s_most = std::max(s_most, S);

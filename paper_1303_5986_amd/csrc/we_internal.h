@@ -80,6 +80,22 @@ struct SimConfig {
     size_t ws_bytes = 0;
 };
 
+// Readback (we_runtime.hip): pinned memory the device writes results to, two
+// halves of `half` bytes when a result is longer than one.  At most 2 MiB, and
+// one for all members of a batch, which share its stream: with one each, the first
+// read of 64 members of 4000 walkers spent 12 of 33 ms on pinning memory.
+struct ReadStage {
+    std::mutex mu;
+    unsigned char *mem = nullptr;
+    size_t half = 0;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    ~ReadStage() {
+        if (mem) (void)hipHostFree(mem);
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+    }
+};
+
 struct we_sim {
     const we_network *net = nullptr;
     hipStream_t stream = nullptr;
@@ -108,13 +124,8 @@ struct we_sim {
     hipStream_t capture_stream = nullptr;
     int32_t graph_iters = 0;
     bool capturing = false;
-    // readback (we_runtime.hip): pinned memory the device writes results to, two
-    // halves of stage_half bytes when a result is longer than one
-    std::mutex read_mu;
     int32_t device = 0;
-    unsigned char *stage = nullptr;
-    size_t stage_half = 0;
-    hipEvent_t read_ev[2] = {nullptr, nullptr};
+    ReadStage own_stage, *stage = &own_stage;   // readback; a batch's members share the batch's
     // committor
     Records rec;
     Committor cm;

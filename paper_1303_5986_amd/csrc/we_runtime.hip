@@ -782,26 +782,26 @@ __global__ __launch_bounds__(256) void we_read_kernel(Read r, uint32_t *__restri
     }
 }
 
-// The sim's pinned memory for a result of `bytes`: one piece, or two halves of
+// Pinned memory for a result of `bytes`: one piece, or two halves of
 // READ_HALF_MAX which the device and the host take in turns.
 #define READ_HALF_MAX ((size_t)1 << 20)
-bool read_stage(we_sim *s, size_t bytes) {
+bool read_stage(ReadStage &s, size_t bytes) {
     size_t half = (size_t)64 << 10;
     while (half < bytes && half < READ_HALF_MAX) half <<= 1;
-    if (half > s->stage_half) {
-        if (s->stage) (void)hipHostFree(s->stage);
-        s->stage = nullptr;
-        s->stage_half = 0;
+    if (half > s.half) {
+        if (s.mem) (void)hipHostFree(s.mem);
+        s.mem = nullptr;
+        s.half = 0;
         void *p = nullptr;
         if (hipHostMalloc(&p, half < READ_HALF_MAX ? half : 2 * half, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-        s->stage = (unsigned char *)p;
-        s->stage_half = half;
+        s.mem = (unsigned char *)p;
+        s.half = half;
     }
-    for (hipEvent_t &e : s->read_ev)
-        if (bytes > s->stage_half && !e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+    for (hipEvent_t &e : s.ev)
+        if (bytes > s.half && !e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
@@ -825,28 +825,29 @@ we_status read_plain(we_sim *s, const ReadPlan &p, int32_t *n_out) {
 
 // Waits for the sim's stream, reports latched faults and fetches the pieces.
 we_status read_back(we_sim *s, ReadPlan &p, int32_t *n_out = nullptr) {
-    std::lock_guard<std::mutex> lock(s->read_mu);
+    ReadStage &rs = *s->stage;
+    std::lock_guard<std::mutex> lock(rs.mu);
     p.r.err = s->args.err;
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev != s->device || !read_stage(s, 4 * p.most))
+    if (hipGetDevice(&dev) != hipSuccess || dev != s->device || !read_stage(rs, 4 * p.most))
         return read_plain(s, p, n_out);
-    const uint64_t half = s->stage_half / 4;
+    const uint64_t half = rs.half / 4;
     uint64_t total = p.most;
     const bool one = total <= half;
     auto launch = [&](uint64_t c) -> we_status {   // chunk c into its half
         const uint64_t lo = c * half, count = std::min(half, total - lo);
         hipLaunchKernelGGL(we_read_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s->stream, p.r,
-                           (uint32_t *)(s->stage + (c & 1) * s->stage_half), lo, count);
+                           (uint32_t *)(rs.mem + (c & 1) * rs.half), lo, count);
         HIP_TRY(hipGetLastError());
-        if (!one) HIP_TRY(hipEventRecord(s->read_ev[c & 1], s->stream));
+        if (!one) HIP_TRY(hipEventRecord(rs.ev[c & 1], s->stream));
         return WE_OK;
     };
     we_status st = launch(0);
     if (st == WE_OK && !one) st = launch(1);
     if (st != WE_OK) return st;
     for (uint64_t c = 0; c * half < total; ++c) {
-        HIP_TRY(one ? hipStreamSynchronize(s->stream) : hipEventSynchronize(s->read_ev[c & 1]));
-        const uint32_t *got = (const uint32_t *)(s->stage + (c & 1) * s->stage_half);
+        HIP_TRY(one ? hipStreamSynchronize(s->stream) : hipEventSynchronize(rs.ev[c & 1]));
+        const uint32_t *got = (const uint32_t *)(rs.mem + (c & 1) * rs.half);
         if (c == 0) {
             const int32_t n = (int32_t)got[1];
             st = err_status((int32_t)got[0]);
@@ -1230,9 +1231,6 @@ extern "C" void we_destroy(we_sim *s) {
     if (!s) return;
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     else (void)hipDeviceSynchronize();
-    if (s->stage) (void)hipHostFree(s->stage);
-    for (hipEvent_t e : s->read_ev)
-        if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_pool) (void)hipEventDestroy(e);
     if (s->graph_exec) (void)hipGraphExecDestroy(s->graph_exec);
     committor_free(s);

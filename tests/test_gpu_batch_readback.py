@@ -1,0 +1,61 @@
+"""Reading a batch's members: they share the batch's pinned memory, so the first
+read of every member costs about what a later one does, and threads that read
+different members at once each get their own."""
+import dataclasses
+import threading
+import time
+
+import numpy as np
+import pytest
+
+from paper_1303_5986_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(n, m):
+    from paper_1303_5986_amd import we
+    base = wl.birth_death_config()
+    cfgs = [dataclasses.replace(base, m_targ=m, edges=wl.uniform_edges(0.0, 100.0, 20), seeds=np.array([i + 1], np.uint64))
+            for i in range(n)]
+    return we.Batch(cfgs, max_iters=4, kernels=[we.WE_KERNEL_LANE] * n)
+
+
+def test_first_read_of_every_member():
+    print("case: first read of 64 members of 4000 walker slots", flush=True)
+    b = _batch(64, 200)
+    b.step(4)
+    b.synchronize()
+    took = []
+    for _ in range(5):
+        t0 = time.perf_counter()
+        for m in b.members:
+            m.walkers(0)
+        took.append(time.perf_counter() - t0)
+    print(f"   ms {[round(1e3 * t, 2) for t in took]}", flush=True)
+    assert took[0] < 3 * min(took[1:])
+
+
+@pytest.mark.parametrize("m", [5, 4000])
+def test_threads_read_members(m):
+    """20 m slots a member: far below the first size, and several halves."""
+    print(f"case: four threads read members of {20 * m} slots", flush=True)
+    b = _batch(4, m)
+    rng = np.random.default_rng(m)
+    sent = [(rng.integers(0, 90, (n, 1)).astype(np.int32), rng.random(n)) for n in (20 * m, 1, 9 * m, 13 * m)]
+    for mem, (x, w) in zip(b.members, sent):
+        mem.set_ensemble(0, x, w)
+    bad = []
+
+    def read(i):
+        for _ in range(8):
+            x, w, _, _ = b.members[i].walkers(0)
+            if not (np.array_equal(x, sent[i][0]) and np.array_equal(w, sent[i][1])):
+                bad.append(i)
+
+    threads = [threading.Thread(target=read, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
