@@ -800,8 +800,10 @@ bool read_stage(ReadStage &s, size_t bytes) {
         s.mem = (unsigned char *)p;
         s.half = half;
     }
+    // an event's default release need not make host memory visible to the host
+    const unsigned flags = hipEventDisableTiming | hipEventReleaseToSystem;
     for (hipEvent_t &e : s.ev)
-        if (bytes > s.half && !e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        if (bytes > s.half && !e && hipEventCreateWithFlags(&e, flags) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
