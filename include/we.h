@@ -188,8 +188,8 @@ WE_API we_status we_init(const we_network *net, const we_grid *grid, const we_pa
                          we_sim **out);
 
 /* Name of the propagation kernel the sim's steps launch (the variant is
- * chosen from the network and the launch shape); "" for NULL.  The string is
- * static. */
+ * chosen from the network and the launch shape), with its leading template
+ * arguments; "" for NULL.  The string is static. */
 WE_API const char *we_propagation_kernel(const we_sim *s);
 
 /* Switch a sim's bins (Sec. II.B bins the state space; Sec. IV calls the

@@ -18,7 +18,10 @@
 
 #define GROUP_WAVES 4
 
-template <int L, bool LT, int BR, class D>
+// LT: the tables in LDS.  BR: the most reactions of a lane's block that the variant
+// is for, 4 or 8 (0: any number, nothing kept in registers), and NS its register slots,
+// 2 of the 4 where a block needs no more.
+template <int L, bool LT, int BR, class D, int NS>
 __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, int32_t *__restrict__ xs) {
     extern __shared__ __align__(16) unsigned char gsm[];
     constexpr int G = 64 / L;
@@ -54,7 +57,7 @@ __global__ __launch_bounds__(64 * GROUP_WAVES) void ssa_group_kernel(SimArgs a, 
                 live = true;
             }
         }
-        group_walker<L, BR, D>(a, tb, xs, run, k, live, iter, lx);
+        group_walker<L, NS, D>(a, tb, xs, run, k, live, iter, lx);
         // every lane executes the atomic (lane 0 adds G, the others zero) and
         // lane 0's result is broadcast, so no lane leaves the wave's path
         const uint32_t got = atomicAdd(&a.queue[0], lane == 0 ? (uint32_t)G : 0u);
@@ -91,7 +94,7 @@ int group_regs(const SimArgs &a, int32_t lanes) {
     return B <= 2 ? 2 : B <= 4 ? 4 : B <= 8 ? 8 : 0;
 }
 
-template <int L, bool LT, int BR, class D>
+template <int L, bool LT, int BR, class D, int NS = BR>
 hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
     constexpr int G = 64 / L;
     const size_t shmem =
@@ -99,7 +102,7 @@ hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
     static size_t last_shmem = 0;
     static int per_cu = 0;
     if (per_cu == 0 || shmem != last_shmem) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ssa_group_kernel<L, LT, BR, D>, 64 * GROUP_WAVES,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, ssa_group_kernel<L, LT, BR, D, NS>, 64 * GROUP_WAVES,
                                                          shmem) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
@@ -108,16 +111,16 @@ hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
     const int64_t walkers = (int64_t)a.n_runs * a.cap;
     const int64_t need = (walkers + (int64_t)GROUP_WAVES * G - 1) / ((int64_t)GROUP_WAVES * G);
     const unsigned blocks = (unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)per_cu * group_cus()));
-    hipLaunchKernelGGL((ssa_group_kernel<L, LT, BR, D>), dim3(blocks), dim3(64 * GROUP_WAVES), shmem, st, a, xs);
+    hipLaunchKernelGGL((ssa_group_kernel<L, LT, BR, D, NS>), dim3(blocks), dim3(64 * GROUP_WAVES), shmem, st, a, xs);
     return hipGetLastError();
 }
 
 template <int L, class D>
 hipError_t launch_group(const SimArgs &a, int32_t *xs, hipStream_t st) {
-    const int br = group_regs(a, L);
-    if (br == 2) return launch_group<L, true, 2, D>(a, xs, st);
-    if (br == 4) return launch_group<L, true, 4, D>(a, xs, st);
-    if (br == 8) return launch_group<L, true, 8, D>(a, xs, st);
+    const int ns = group_regs(a, L);
+    if (ns == 2) return launch_group<L, true, 4, D, 2>(a, xs, st);
+    if (ns == 4) return launch_group<L, true, 4, D>(a, xs, st);
+    if (ns == 8) return launch_group<L, true, 8, D>(a, xs, st);
     return group_tables_in_lds(a) ? launch_group<L, true, 0, D>(a, xs, st) : launch_group<L, false, 0, D>(a, xs, st);
 }
 
@@ -139,7 +142,8 @@ hipError_t launch_ssa_group(const SimArgs &a, int32_t *xs, int32_t lanes, hipStr
 }
 
 const char *ssa_group_name(const SimArgs &a, int32_t lanes) {
-    // 5 lane counts x (up to 4 or 8 register slots, tables in LDS, through the cache)
+    // the kernel's first three template arguments: 5 lane counts x (blocks of up to 4 or
+    // 8 reactions in registers, tables in LDS, through the cache)
     static const char *const names[5][4] = {
         {"ssa_group_kernel<2, true, 4>", "ssa_group_kernel<2, true, 8>", "ssa_group_kernel<2, true, 0>",
          "ssa_group_kernel<2, false, 0>"},
@@ -152,7 +156,7 @@ const char *ssa_group_name(const SimArgs &a, int32_t lanes) {
         {"ssa_group_kernel<32, true, 4>", "ssa_group_kernel<32, true, 8>", "ssa_group_kernel<32, true, 0>",
          "ssa_group_kernel<32, false, 0>"}};
     const int li = lanes == 2 ? 0 : lanes == 4 ? 1 : lanes == 8 ? 2 : lanes == 16 ? 3 : 4;
-    const int br = group_regs(a, lanes);
-    const int vi = br == 2 || br == 4 ? 0 : br == 8 ? 1 : group_tables_in_lds(a) ? 2 : 3;
+    const int ns = group_regs(a, lanes);
+    const int vi = ns == 2 || ns == 4 ? 0 : ns == 8 ? 1 : group_tables_in_lds(a) ? 2 : 3;
     return names[li][vi];
 }
