@@ -13,7 +13,7 @@
 //      weight (ties: the lowest bin).
 //   3. The pivot's strongly connected component among the candidates, edge
 //      j -> i where F[i][j] > 0: forward and backward reachability over
-//      64-bit adjacency masks, run by one wave (OR-reductions, no barriers).
+//      64-bit adjacency masks, one wave each (OR-reductions, no barriers).
 //   4. Eq. ss on the component, with rates r(a -> b) = F[b][a] / W_a, by
 //      state reduction (Grassmann, Taksar and Heyman 1985): states are
 //      removed from the highest index down, each time with
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
     double *fac = sm + NB;                            // [NB]
     int32_t *cand = reinterpret_cast<int32_t *>(fac + NB);  // [NB] candidate -> bin
     int32_t *act = cand + NB;                               // [NB] component -> bin
-    int32_t *pos = act + NB;                                // [NB] per bin
+    int32_t *pos = act + NB;                                // [NB] a bin's end, then its walkers
     unsigned long long *succ =
         reinterpret_cast<unsigned long long *>(lds + rw_align8(40 * (size_t)NB + 12 * (size_t)NB));
     unsigned long long *pred = succ + (size_t)NB * NW;
@@ -222,11 +222,10 @@ __global__ __launch_bounds__(RW_THREADS) void we_reweight_kernel(SimArgs a, doub
             const bool is = i < NB && pos[i] > 0 && wb[i] > 0.0 && Wc[i] > 0.0;
             const unsigned long long m = __ballot(is);
             const int32_t idx = nc + __popcll(m & ((1ull << lane) - 1ull));
-            rw_wave_sync();
-            if (i < NB) pos[i] = is ? idx : -1;
             if (is) cand[idx] = i;
             nc += __popcll(m);
         }
+        rw_wave_sync();
         double bv = -1.0;
         int32_t bc = INT32_MAX;
         for (int32_t c = lane; c < nc; c += 64) {

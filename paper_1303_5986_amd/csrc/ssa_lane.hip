@@ -88,7 +88,7 @@ struct PoolQueue {
 // that walker, 32 such runs 783 -> 422 ns.
 template <int SMAX, int RMAX, bool HILL, bool PAIR>
 __device__ __forceinline__ void lane_team(const SimArgs &a, const LaneNet<SMAX, RMAX, HILL, PAIR> &net, LaneWalker &w,
-                                          int32_t (&x)[SMAX], int32_t *__restrict__ xs, int32_t *xr, size_t gslot,
+                                          int32_t (&x)[SMAX], int32_t *__restrict__ xs, size_t gslot,
                                           bool active, uint32_t iter, double tau) {
     const int lane = threadIdx.x & 63;
     int T = 1;
@@ -206,7 +206,7 @@ __device__ __forceinline__ void lane_pool(const SimArgs &a, int32_t *__restrict_
             }
         } else {
             if (exhausted && nneed >= 32) {
-                lane_team<SMAX, RMAX, HILL, PAIR>(a, net, w, x, xs, xr, gslot, active, iter, tau);
+                lane_team<SMAX, RMAX, HILL, PAIR>(a, net, w, x, xs, gslot, active, iter, tau);
                 break;
             }
             if (active && !lane_event(net, w, x, tau, [&]() { return lane_draw(w.rs, w.e++); })) {

@@ -52,9 +52,9 @@ struct __align__(16) RxnDesc2 {
     double c;        // c_j, halved for a pair of equal molecules
     uint16_t s1, s2; // reactant species (S: none)
     uint8_t hom;     // 1: s1 and s2 are the same species
-    uint8_t pad;
+    uint8_t pad0;
     uint8_t nchg;    // as in RxnDesc
-    uint8_t order;
+    uint8_t pad1;
 };
 
 // A reaction's Hill-type repression (Sec. III.C): its propensity is divided

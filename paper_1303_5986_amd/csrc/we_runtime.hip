@@ -240,7 +240,6 @@ extern "C" we_status we_create_network(int32_t S, int32_t R, const int32_t *reac
             q.s1 = d.nu1 ? d.s1 : (uint16_t)S;
             q.s2 = q.hom ? d.s1 : d.nu2 ? d.s2 : (uint16_t)S;
             q.nchg = d.nchg;
-            q.order = d.order;
         }
         e = up((void **)&net->d_desc2, desc2.data(), sizeof(RxnDesc2) * R_pad);
     }
