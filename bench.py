@@ -991,19 +991,24 @@ def lds_bytes_per_event_fact(net) -> float:
     """LDS bytes one event of the factored-table wave kernel moves, as built:
       the chosen chunk: 64 x (16 B descriptor + 8 B header + 2 x 4 B counts);
       the changed species: old count and incidence word (8 B), the store (4 B);
-      each dependent (mean list length d, repeats included): 2 B id, 16 B
+      each dependent (mean list length d, repeats included): in the pair form
+        (reactions of at most two molecules, at most 4096 of them) 4 B entry, 8 B
+        rate constant and 4 B for the other reactant's count; else 2 B id, 16 B
         descriptor, 2 x 4 B counts before and 2 x 4 B after the firing;
       the chunk sums: one LDS atomic add per dependent (8 B read, 8 B
         written), then the 64 chunk lanes reload their sums (512 B)."""
     users = [0] * net.S
+    order = [0] * net.R
     for j in range(net.R):
         for p in range(net.reac_ptr[j], net.reac_ptr[j + 1]):
             users[int(net.reac_species[p])] += 1
+            order[j] += int(net.reac_mult[p])
     dl = [sum(users[int(net.chg_species[p])] for p in range(net.chg_ptr[j], net.chg_ptr[j + 1]))
           for j in range(net.R)]
     d = float(np.mean(dl))
     nchg = float(np.diff(net.chg_ptr).mean())
-    return 64 * (16 + 8 + 8) + nchg * 12 + d * (2 + 16 + 8 + 8) + d * 16 + 512
+    pair = max(order) <= 2 and net.R <= 4096
+    return 64 * (16 + 8 + 8) + nchg * 12 + d * ((4 + 8 + 4) if pair else (2 + 16 + 8 + 8)) + d * 16 + 512
 
 
 def _cpu_model() -> str:

@@ -125,8 +125,9 @@ __global__ __launch_bounds__(64 * WAVE_LDS_MAX_WAVES, 4) void ssa_wave_lds_kerne
 
 // Factored-table variant: the block copies the descriptors (16 bytes per
 // reaction), the change headers (8 bytes), the per-species incidence words
-// (4 bytes) and the incidence lists (2 bytes per entry) into LDS -- 98 KB at
-// 354 species / 3680 reactions -- and each wave keeps its walker's counts and
+// (4 bytes) and the incidence lists (4 bytes per entry in the pair form, else 2)
+// into LDS -- 110,352 bytes at 354 species / 3680 reactions in the pair form, 100,048
+// in the other -- and each wave keeps its walker's counts and
 // its 64 chunk sums beside them (16 walkers per CU at that size); waves take
 // walkers from the work queue until it is empty.  Nothing
 // in the event loop reads global memory.
