@@ -1,8 +1,8 @@
 """The joint histogram of rows that the observation itself copies (up to 16 species)
 and of gathered ones (17), cell by cell: few and many runs, one to four species in
-the histogram, cells shared by many walkers, more cells than a workgroup's table
-walkers give each cell's weights, which add up in another order (rtol n u for the
-n of a run)."""
+the histogram, cells shared by many walkers, counts past the last cell.  The
+oracle's walkers give each cell's weights, which add up in another order (rtol n u
+for the n of a run)."""
 import numpy as np
 import pytest
 
