@@ -1159,7 +1159,9 @@ def main():
     def line_large():
         cfg = wl.large_network_config(n_iters=max_iters)
         if args.large_runs > 1:
+            joint = cfg.joint_species
             cfg = cfg.with_seeds(np.arange(2024, 2024 + args.large_runs, dtype=np.uint64))
+            cfg.joint_species = joint
         sim = we.sim_from_config(cfg, kernel=we.WE_KERNEL_WAVE, max_iters=max_iters, joint=True)
         m = _measure(sim, K, W)
         ops_ev = alg_ops_per_event_wave(cfg.net)
