@@ -23,7 +23,10 @@
  *    on the device (a count leaving [0, WE_COUNT_MAX], a selection guard
  *    firing with no positive propensity) are latched in device memory and
  *    returned by the next synchronous call (we_synchronize and every getter).
- *  - Calls on one sim must not overlap (one host thread at a time).
+ *  - Calls on one sim must not overlap (one host thread at a time); getters
+ *    of a batch's members may, each member from one thread.
+ *  - The first call that reads results pins host memory: up to 2 MiB per sim,
+ *    one piece for all members of a batch, until the sim or batch is destroyed.
  */
 #ifndef WE_H
 #define WE_H
@@ -460,9 +463,9 @@ WE_API we_status we_measure_peaks(void *hip_stream, we_peaks *out);
  * stream (the paper runs independent replicas, Sec. IV).  Member i is an
  * ordinary sim built from nets[i], grids[i], params[i] (library-allocated
  * workspace; no reweighting, tau-leaping or Hill rates); the propagation of
- * all members is one persistent launch per kernel variant whose waves pull
- * (run, walker-tile) work items from a device counter, so uneven runs
- * balance across the chip.
+ * all members is one persistent launch per kernel variant whose workgroups
+ * take chunks (member, run, range of walker slots) from device counters, so
+ * uneven runs balance across the chip.
  * autotune_iters > 0: for a member with params.kernel AUTO, every kernel
  * its network fits -- lane (64 walkers per wave), group (32, 16, 8, 4 or 2
  * walkers per wave), wave (1) -- is timed on one interval of a pilot sim of
@@ -501,8 +504,11 @@ WE_API void we_batch_destroy(we_batch *b);
  * every launch.  we_profile(s, 1) clears and starts the accumulators,
  * we_profile(s, 0) stops recording.  we_profile_read waits for the stream
  * and returns the summed device time in milliseconds of the propagation
- * (SSA) kernels, the recycle/bin/resample kernels and the observable
- * kernels, and the number of iterations they cover.  Synchronous. */
+ * (SSA) kernels (with their work queue), the recycle/bin/resample (and
+ * reweighting) kernels and the observable kernels, and the number of
+ * iterations they cover.  Copying the new state rows from their parents counts
+ * with the observables, whose kernel does it for rows of up to 16 species.
+ * Synchronous. */
 WE_API we_status we_profile(we_sim *s, int32_t enable);
 WE_API we_status we_profile_read(we_sim *s, double *ms_propagate, double *ms_resample,
                                  double *ms_observe, int64_t *iterations);

@@ -42,7 +42,8 @@ struct __align__(16) RxnDesc {
 // that needs no case distinction: h = x1 (x2 - hom) with the counts of s1 and
 // s2, where an absent reactant is the extra species S, whose count is always
 // 1, and a pair of equal molecules takes its species twice with hom = 1 and
-// half the rate constant.  h is an integer below 2^35, and halving c is exact,
+// half the rate constant.  h is an integer below 2^35, and halving c is exact (but
+// for c below 2^-1021, where no event falls within any interval),
 // so c h rounds as c_j h_j does: the same propensity in 7 instructions where
 // the general form's two binomials take about 40.  Each event of a wave kernel
 // evaluates three of them per lane; what bounds those kernels is the length and
