@@ -1496,7 +1496,7 @@ __global__ __launch_bounds__(RESAMPLE_THREADS) void we_resample_kernel(SimArgs a
 }
 
 // Bin-parallel split/merge after we_resample_kernel's placement: grid
-// (ceil(n_bins / 4), runs), one wave per bin, the same per-bin steps on the
+// (bins_blocks, runs), one wave per bin, the same per-bin steps on the
 // run's arrays in device memory; bins of one run write disjoint ranges.
 template <int RULE, int CAP>
 __device__ __forceinline__ void resample_bins_wave(const SimArgs &a, double *__restrict__ w_nxt,
