@@ -21,7 +21,8 @@
  *    crosses this interface.
  *  - we_step_intervals is asynchronous on the sim's HIP stream.  Errors met
  *    on the device (a count leaving [0, WE_COUNT_MAX], a selection guard
- *    firing with no positive propensity) are latched in device memory and
+ *    firing with no positive propensity, a weight that is infinite or not a
+ *    number when walkers are resampled) are latched in device memory and
  *    returned by the next synchronous call (we_synchronize and every getter).
  *  - Calls on one sim must not overlap (one host thread at a time); getters
  *    of a batch's members may, each member from one thread.

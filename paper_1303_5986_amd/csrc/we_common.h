@@ -27,6 +27,7 @@ enum : int32_t {
     WE_DERR_OVERFLOW = 1,   // a count left [0, WE_COUNT_MAX]
     WE_DERR_SELECT = 2,     // no reaction with positive propensity at selection
     WE_DERR_CAPACITY = 4,   // resampling would exceed the slot reservation
+    WE_DERR_WEIGHT = 8,     // a weight that is infinite or not a number at resampling
 };
 
 // One reaction's reactants and rate, packed for wave-uniform (scalar) loads.

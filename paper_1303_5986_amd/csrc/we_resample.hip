@@ -1428,6 +1428,10 @@ __device__ void resample_run_t(const SimArgs &a, int32_t *__restrict__ x_cur, co
             a.flux[(size_t)run * a.max_iters + rec_slot] = f;
         }
     }
+    // the weights in bin-major order.  One that is infinite or not a number (sums
+    // that overflowed, a reweighting of rates past the range) is a fault, and goes on
+    // as 0: the hand-out of copies ends by comparing shares, and the rounds rank
+    // walkers by them.
     // flux matrix of reweighting: from the second interval on (the first
     // one's walkers carry no bin yet); the start bins go to aux, which only
     // the split/merge of the same bin uses afterwards
@@ -1446,7 +1450,9 @@ __device__ void resample_run_t(const SimArgs &a, int32_t *__restrict__ x_cur, co
         for (int u = 0; u < 4; ++u) {
             const int32_t p = p4 + u * nthr;
             if (p < n) {
-                wk.w[p] = ws[u];
+                const bool finite = ws[u] < __builtin_huge_val();
+                if (!finite) atomicOr(a.err, WE_DERR_WEIGHT);
+                wk.w[p] = finite ? ws[u] : 0.0;
                 if (rw_acc) wk.aux[p] = (Idx)from[u];
             }
         }

@@ -718,6 +718,7 @@ we_status err_status(int32_t err) {
     if (err & WE_DERR_OVERFLOW) return fail(WE_EOVERFLOW, "a copy number left [0, WE_COUNT_MAX]");
     if (err & WE_DERR_CAPACITY) return fail(WE_ECAPACITY, "resampling exceeded the slot reservation");
     if (err & WE_DERR_SELECT) return fail(WE_EDEVICE, "reaction selection found no positive propensity");
+    if (err & WE_DERR_WEIGHT) return fail(WE_EDEVICE, "a walker's weight is infinite or not a number");
     return WE_OK;
 }
 
