@@ -381,7 +381,7 @@ __device__ __forceinline__ bool lane_event(const LaneNet<SMAX, RMAX, HILL, PAIR>
         any |= xn[s];
     }
     // (the running sums end in a0: the same additions in the same order)
-    const bool over = !(a0 > 0.0) || t > tau;
+    const bool over = !(a0 > 0.0) || !(t <= tau);   // recip(a0) below 2^-1024: t is not a number
     const bool past = !(a0 > target);
     // a count left [0, 2^17 - 1] iff a bit outside the low 17 is set
     const bool odd = over || past || (any & ~WE_COUNT_MAX_DEV) != 0;
@@ -586,7 +586,7 @@ __device__ __forceinline__ bool lane_leap_step(const LaneNet<SMAX, RMAX, HILL> &
         const double u1 = uniform53(r.x, r.y);
         const double u2 = uniform53(r.z, r.w);
         const double dt = neg_log1m(u1) * recip(a0);
-        if (w.t + dt > tau) return false;
+        if (!(w.t + dt <= tau)) return false;
         w.t = w.t + dt;
         const double target = u2 * a0;
         // the first j whose running sum exceeds the target (one pass from the

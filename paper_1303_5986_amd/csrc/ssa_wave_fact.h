@@ -106,7 +106,7 @@ __device__ inline void wave_walker_fact(const SimArgs &a, const FactTables &tab,
         const double u2 = lane_value(ru2, (int)(e & 63u));
         e += 1;
         const double dt = ex * recip(a0);
-        if (t + dt > tau) break;
+        if (!(t + dt <= tau)) break;   // recip(a0) below 2^-1024: not a number
         t = t + dt;
         if ((e & 15u) == 1u) chain_priority((tau - t) * a0);
         const double target = u2 * a0;

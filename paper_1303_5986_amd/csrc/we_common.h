@@ -246,7 +246,9 @@ __device__ __forceinline__ double uniform53(uint32_t a, uint32_t b) {
 }
 
 // 1/d for a positive normal double: the hardware reciprocal estimate and two
-// Newton steps r <- r + r (1 - d r); within an ulp or so of the quotient.
+// Newton steps r <- r + r (1 - d r); within an ulp or so of the quotient.  Where
+// 1/d is past the range the steps give NaN: callers test for the interval's end
+// so that it ends there too.
 __device__ __forceinline__ double recip(double d) {
     double r = __builtin_amdgcn_rcp(d);
     r = fma(r, fma(-d, r, 1.0), r);
